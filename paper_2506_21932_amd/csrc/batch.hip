@@ -501,16 +501,14 @@ hipError_t fill_tables(smg_batch_s* B) {
       a.sd = v.psd;
       a.h = Fp<PT>(B, s, l);
       a.x = (V*)v.ua;
-      a.next = UBp<PT>(B, s, l);
-      a.next_dir = -1;
+      a.strip = (V*)v.strip;
+      a.par = v.par;
       a.sys = s;
       pre.push_back(a);
       WfArgs<V> c = a;
       c.pk = v.pk[1];
       c.h = (const V*)v.h;
       c.x = UBp<PT>(B, s, l);
-      c.next = (V*)v.ua;
-      c.next_dir = +1;
       post.push_back(c);
       L.pre.nt.push_back(v.tl.ntx * v.tl.nty);
       rr.push_back(RRArgs<M>{v.g, v.cmask, PT::A(v), Fp<PT>(B, s, l), (const V*)v.ua, (V*)H->lev[l + 1].f, s});
@@ -578,7 +576,7 @@ hipError_t bvcycle(smg_batch_s* B, const int* gate, hipStream_t st) {
   }
   for (int l = 0; l + 1 < B->maxlev; ++l) {
     const LevelPh& L = B->lv[l];
-    e = launch_wavefront_group<E>(L.pre.pat, +1, (const WfArgs<V>*)L.pre.segs, L.pre.tmap, L.pre.total, B->grid,
+    e = launch_wavefront_group<E>(L.pre.pat, +1, (const WfArgs<V>*)L.pre.segs, (int)L.sys.size(), L.pre.tmap, L.pre.total, B->grid,
                                   gate, B->ctr, B->err, st);
     if (e == hipSuccess) e = launch_rr_group<M>(L.rr.pat, L.rr.small, (const RRArgs<M>*)L.rr.segs, L.rr.bmap, L.rr.nblocks, gate, st);
     if (e != hipSuccess) return e;
@@ -589,7 +587,7 @@ hipError_t bvcycle(smg_batch_s* B, const int* gate, hipStream_t st) {
     const LevelPh& L = B->lv[l];
     e = launch_pp_group<M>(L.pp.pat, false, L.pp.small, L.pp.stage, (const PPArgs<M>*)L.pp.segs, L.pp.bmap, L.pp.nblocks, gate, st);
     if (e == hipSuccess)
-      e = launch_wavefront_group<E>(L.post.pat, -1, (const WfArgs<V>*)L.post.segs, L.post.tmap, L.post.total, B->grid,
+      e = launch_wavefront_group<E>(L.post.pat, -1, (const WfArgs<V>*)L.post.segs, (int)L.sys.size(), L.post.tmap, L.post.total, B->grid,
                                     gate, B->ctr, B->err, st);
     if (e != hipSuccess) return e;
   }

@@ -29,6 +29,9 @@ struct Level {
   long nsk_cap = 0;                 // schedule positions the packed sweep data has room for (either tile shape)
   void* pk[2] = {nullptr, nullptr};  // packed sweep data, forward / backward (V-cycle precision; FP16: halves)
   float* psd = nullptr;             // FP16: {row scale, diagonal scaling} per schedule position
+  void* strip = nullptr;            // scalar tiled sweeps: two strip buffers (values tiles exchange)
+  long strip_cap = 0;               // entries of both (room for either tile shape)
+  unsigned* par = nullptr;          // bit 0: the buffer of the level's next sweep
   int hp_steps = 0;                 // small level: hyperplanes of the one-workgroup sweep (0: tiled sweep)
   int* hp_pts = nullptr;            // its point schedule [step][256]
   void* hp_cf[2] = {nullptr, nullptr};  // its step-ordered coefficients, forward / backward

@@ -27,9 +27,11 @@ struct WfArgs {
   const void* pk;            // packed sweep data of this direction (launch_wf_pack)
   const float* sd;           // FP16 storage: {row scale, diagonal scaling} per position
   const V* h;                // right-hand side of the triangular system
-  V* x;                      // output; positions read by other tiles hold the sentinel
-  V* next;                   // output buffer of the next sweep on this level (sentinel prefill), or null
+  V* x;                      // output (block sweep: positions read by other tiles hold the sentinel)
+  V* next;                   // block sweep: output buffer of the level's next sweep (sentinel prefill), or null
   int next_dir;              // direction of that next sweep
+  V* strip;                  // scalar sweep: two buffers of wf_strip_elems entries, through which tiles exchange values
+  unsigned* par;             // scalar sweep: bit 0 names the buffer of the level's next sweep (it holds sentinels)
   const V* addv;             // optional: addout = addv + x
   V* addout;
   unsigned* ctr;             // [0] ticket counter, [1] exit counter; zero between launches
@@ -44,6 +46,8 @@ void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape = 0);
 // ebytes bytes; offsets within a tile must stay below 2^31 bytes.
 int wf_pack_count(int pat, int ebytes);
 bool wf_ranges_ok(const Grid& g, const WfTiling& t, int pat, int vbytes, int ebytes);
+// entries of one strip buffer
+long wf_strip_elems(const WfTiling& t, int pat);
 
 // E = double / float / __half (FP16 storage, FP32 arithmetic)
 template <class E>
@@ -60,15 +64,15 @@ hipError_t launch_wf_pack_h(int pat, const Grid& g, const WfTiling& tl, int dir,
                             const float* rd, __half* out, float* sd, hipStream_t st);
 
 // One sweep over many independent grids of pattern pat in one launch.
-// segs[k]: the arguments of grid k (their ctr / err are not used);
+// segs[k]: the arguments of grid k of nseg (their ctr / err are not used);
 // tmap[t] = (k << 20) | r: ticket t is the r-th tile of grid k in its own
 // forward dependence order (each grid's tiles appear in increasing r);
 // total tickets; grid workgroups (0: one per tile); ctr / err as in WfArgs;
 // tiles of a grid whose system is finished (live[sys] == 0) are skipped.
 template <class E>
-hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<E>::V>* segs, const unsigned* tmap,
-                                  unsigned total, unsigned grid, const int* live, unsigned* ctr, unsigned* err,
-                                  hipStream_t st);
+hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<E>::V>* segs, int nseg,
+                                  const unsigned* tmap, unsigned total, unsigned grid, const int* live, unsigned* ctr,
+                                  unsigned* err, hipStream_t st);
 
 // ---- small levels: one-workgroup hyperplane sweep (hpsweep.hip) ---------
 // hp_plan: hyperplanes of the level, or 0 when it does not fit (pts: host

@@ -130,9 +130,16 @@ const char* check_cfg(const smg_config* c) {
   return nullptr;
 }
 
+// Words of the handle's counter block: the sweeps' ticket and exit counters,
+// then one strip-buffer word per level.
+constexpr int CTR_WORDS = 64, CTR_PAR = 8;
+static_assert(CTR_PAR + MAXLEV <= CTR_WORDS, "counter block too small");
+
 // Lays out every device array of the handle in the workspace (base == null:
-// size only).  Returns the number of bytes.
-size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, int* nc_out, Level* Lext = nullptr) {
+// size only).  Returns the number of bytes; *core receives those without the
+// strip buffers, which come last.
+size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, int* nc_out, Level* Lext = nullptr,
+            size_t* core = nullptr) {
   Arena ar{base};
   const int bs = cfg.block, be = bs * bs;
   const int maxc = cfg.max_coarse > 0 ? cfg.max_coarse : 4096;
@@ -205,6 +212,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       wf_tiling(v.g, v.Ssw, &t2, 2);
       wf_tiling(v.g, v.Ssw, &v.tl);
       v.nsk_cap = std::max(t1.nsk, t2.nsk);
+      v.strip_cap = 2 * std::max(wf_strip_elems(t1, v.Ssw), wf_strip_elems(t2, v.Ssw));
       const size_t pbytes = (size_t)wf_pack_count(v.Ssw, eb) * 16 * v.nsk_cap;
       v.pk[0] = ar.take<char>(pbytes);
       v.pk[1] = ar.take<char>(pbytes);
@@ -237,7 +245,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     }
   }
   double* aug = ar.take<double>((size_t)nc * 2 * nc + coarse_invert_extra(nc));
-  unsigned* ctr = ar.take<unsigned>(64);
+  unsigned* ctr = ar.take<unsigned>(CTR_WORDS);
   unsigned* err = ar.take<unsigned>(64);
   int* info = ar.take<int>(64);
   double* dpart = ar.take<double>(DOT_BLOCKS);
@@ -268,13 +276,19 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     H->kZ = kZ;
     H->kV_m = cfg.gmres_restart;
   }
+  if (core) *core = ar.off + 256;
+  for (int l = 0; l + 1 < nlev; ++l) {
+    Level& v = L[l];
+    if (v.strip_cap > 0) v.strip = ar.take<char>((size_t)v.strip_cap * vsz);
+    v.par = ctr ? ctr + CTR_PAR + l : nullptr;
+  }
   return ar.off + 256;
 }
 
 template <class E, class V>
-hipError_t sweep(smg_handle_s* H, const Level& L, int dir, bool unitd, const V* hin, V* x, V* next, int next_dir,
-                 const V* addv, V* addout, hipStream_t st) {
-  // small level: every sweep on it runs in one workgroup (no sentinels used)
+hipError_t sweep(smg_handle_s* H, const Level& L, int dir, bool unitd, const V* hin, V* x, const V* addv, V* addout,
+                 hipStream_t st) {
+  // small level: every sweep on it runs in one workgroup
   if (L.hp_steps > 0 && H->hp_on && !unitd && addout == nullptr)
     return launch_hpsweep<V>(L.S, dir, L.g, L.hp_steps, L.hp_pts, (const V*)L.hp_cf[dir > 0 ? 0 : 1], hin, x, st);
   WfArgs<V> a{};
@@ -284,8 +298,8 @@ hipError_t sweep(smg_handle_s* H, const Level& L, int dir, bool unitd, const V* 
   a.sd = L.psd;
   a.h = hin;
   a.x = x;
-  a.next = next;
-  a.next_dir = next_dir;
+  a.strip = (V*)L.strip;
+  a.par = L.par;
   a.addv = addv;
   a.addout = addout;
   a.ctr = H->ctr;
@@ -442,9 +456,10 @@ hipError_t old_terms(smg_handle_s* H, const Level& v, int dir, const typename PT
 // operations to each value.
 //
 // GS step k of a level (0 <= k < T = pre + post) runs in direction D(k) and
-// writes X(k); the step before it left the sentinels of direction D(k) in
-// X(k) (the last step of a cycle prepares X(0) of the next cycle, setup
-// prepares every buffer once).  X alternates between u_a and the level's
+// writes X(k).  Line GS and 3x3 blocks exchange values through the output:
+// the step before left the sentinels of direction D(k) in X(k) (the last step
+// of a cycle prepares X(0) of the next cycle, setup prepares every buffer
+// once).  X alternates between u_a and the level's
 // output, so X(k + 1) = X(k - 1): that buffer's old values were consumed by
 // the old-value pass (GS) or are read only by columns this sweep waits for
 // (line GS) before it receives sentinels.  With T odd, X(0) is a third
@@ -488,52 +503,34 @@ hipError_t vcycle_gen_t(smg_handle_s* H, const typename PT::V* f0, typename PT::
       hin = (const V*)v.h;
     }
     if (bs == 3) return bsweep<E, V>(H, v, D(k), hin, x, nx, D(kn), st);
-    return sweep<E, V>(H, v, D(k), false, hin, x, nx, D(kn), nullptr, nullptr, st);
+    return sweep<E, V>(H, v, D(k), false, hin, x, nullptr, nullptr, st);
   };
   // ILU(0) step k: out = u + U^-1 L^-1 (f - A u) (u null: the ZeroGuess
-  // solve into u_a).  The L solve of step k writes LB(k), alternately y1 and
-  // y2, whose sentinels the U solve of step k - 1 (which reads the other one)
-  // has written; the U solve writes zz (sentinels from the L solve) or u_a.
-  // With T odd the last step would have to prepare the buffer it reads, so
-  // the cycle refills y1 before its first step instead.
-  auto LB = [&](const Level& v, int k) -> V* { return k % 2 == 0 ? (V*)v.y1 : (V*)v.y2; };
-  auto ilu_step = [&](int l, int k, const V* u, V* out, int kind) -> hipError_t {
+  // solve into u_a): the L solve writes y1, the U solve zz or u_a.
+  auto ilu_step = [&](int l, const V* u, V* out, int kind) -> hipError_t {
     const Level& v = H->lev[l];
     const auto A = PT::A(v);
-    V* nxt = k + 1 < T ? LB(v, k + 1) : (T % 2 == 0 ? LB(v, 0) : nullptr);
     hipError_t e;
     Timed t(H, l, kind, st);
     if (!u) {
-      e = sweep<E, V>(H, v, +1, true, F(l), LB(v, k), (V*)v.ua, -1, nullptr, nullptr, st);
-      if (e == hipSuccess) e = sweep<E, V>(H, v, -1, false, (const V*)LB(v, k), (V*)v.ua, nxt, +1, nullptr, nullptr, st);
+      e = sweep<E, V>(H, v, +1, true, F(l), (V*)v.y1, nullptr, nullptr, st);
+      if (e == hipSuccess) e = sweep<E, V>(H, v, -1, false, (const V*)v.y1, (V*)v.ua, nullptr, nullptr, st);
       return e;
     }
     e = launch_spmv(v.S, v.g, A, u, F(l), (V*)v.h, true, st);
-    if (e == hipSuccess) e = sweep<E, V>(H, v, +1, true, (const V*)v.h, LB(v, k), (V*)v.zz, -1, nullptr, nullptr, st);
-    if (e == hipSuccess) e = sweep<E, V>(H, v, -1, false, (const V*)LB(v, k), (V*)v.zz, nxt, +1, u, out, st);
+    if (e == hipSuccess) e = sweep<E, V>(H, v, +1, true, (const V*)v.h, (V*)v.y1, nullptr, nullptr, st);
+    if (e == hipSuccess) e = sweep<E, V>(H, v, -1, false, (const V*)v.y1, (V*)v.zz, u, out, st);
     return e;
   };
-  V sent;
-  if (sizeof(V) == 8) {
-    uint64_t b = SENT64;
-    memcpy(&sent, &b, 8);
-  } else {
-    uint32_t b = SENT32;
-    memcpy(&sent, &b, 4);
-  }
   hipError_t e;
   std::vector<V*> upre(NL);  // each level's pre-smoothed values
   for (int l = 0; l < NL - 1; ++l) {
     const Level& v = H->lev[l];
     if (ilu) {
-      if (T % 2 == 1) {
-        e = launch_fill_bits<V>((V*)v.y1, v.N, sent, st);
-        if (e != hipSuccess) return e;
-      }
       V* u = nullptr;
       for (int k = 0; k < m; ++k) {
         V* out = (u == (V*)v.ua) ? (V*)v.uo : (V*)v.ua;
-        e = ilu_step(l, k, k == 0 ? (zg ? nullptr : (const V*)v.uz) : u, out, 0);
+        e = ilu_step(l, k == 0 ? (zg ? nullptr : (const V*)v.uz) : u, out, 0);
         if (e != hipSuccess) return e;
         u = (k == 0 && zg) ? (V*)v.ua : out;
       }
@@ -573,7 +570,7 @@ hipError_t vcycle_gen_t(smg_handle_s* H, const typename PT::V* f0, typename PT::
       V* u = upre[l];
       for (int k = 0; k < p; ++k) {
         V* out = k == p - 1 ? UB(l) : (u == (V*)v.ua ? (V*)v.uo : (V*)v.ua);
-        e = ilu_step(l, m + k, u, out, 5);
+        e = ilu_step(l, u, out, 5);
         if (e != hipSuccess) return e;
         u = out;
       }
@@ -588,8 +585,8 @@ hipError_t vcycle_gen_t(smg_handle_s* H, const typename PT::V* f0, typename PT::
 }
 
 // One V-cycle on internal or caller vectors: f0 = level-0 right-hand side,
-// z0 = level-0 output (its positions read across tiles are given sentinels by
-// the pre-smoothing sweep).
+// z0 = level-0 output (line GS and 3x3 blocks: its positions read across
+// tiles are given sentinels by the pre-smoothing sweep).
 template <class PT>
 hipError_t vcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* z0, hipStream_t st) {
   using V = typename PT::V;
@@ -612,15 +609,15 @@ hipError_t vcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* z
       e = lgs_sweep<PT>(H, v, +1, F(l), nullptr, (V*)v.ua, UB(l), st);
     } else if (!ilu) {
       Timed t(H, l, 0, st);
-      e = sweep<typename PT::E, V>(H, v, +1, false, F(l), (V*)v.ua, UB(l), -1, nullptr, nullptr, st);
+      e = sweep<typename PT::E, V>(H, v, +1, false, F(l), (V*)v.ua, nullptr, nullptr, st);
     } else {
       {
         Timed t(H, l, 0, st);
-        e = sweep<typename PT::E, V>(H, v, +1, true, F(l), (V*)v.y1, (V*)v.ua, -1, nullptr, nullptr, st);
+        e = sweep<typename PT::E, V>(H, v, +1, true, F(l), (V*)v.y1, nullptr, nullptr, st);
       }
       if (e != hipSuccess) return e;
       Timed t(H, l, 1, st);
-      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y1, (V*)v.ua, (V*)v.y2, +1, nullptr, nullptr, st);
+      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y1, (V*)v.ua, nullptr, nullptr, st);
     }
     if (e != hipSuccess) return e;
     {
@@ -670,7 +667,7 @@ hipError_t vcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* z
       }
       if (e != hipSuccess) return e;
       Timed t(H, l, 5, st);
-      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, UB(l), (V*)v.ua, +1, nullptr, nullptr, st);
+      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, UB(l), nullptr, nullptr, st);
     } else {
       {
         Timed t(H, l, 4, st);
@@ -686,11 +683,11 @@ hipError_t vcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* z
       if (e != hipSuccess) return e;
       {
         Timed t(H, l, 5, st);
-        e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)v.h, (V*)v.y2, (V*)v.zz, -1, nullptr, nullptr, st);
+        e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)v.h, (V*)v.y2, nullptr, nullptr, st);
       }
       if (e != hipSuccess) return e;
       Timed t(H, l, 6, st);
-      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y2, (V*)v.zz, (V*)v.y1, +1, (const V*)v.uo, UB(l), st);
+      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y2, (V*)v.zz, (const V*)v.uo, UB(l), st);
     }
     if (e != hipSuccess) return e;
   }
@@ -853,12 +850,18 @@ hipError_t pack_sweep_data(smg_handle_s* H, Level& v, hipStream_t st) {
   return hipSuccess;
 }
 
-// Every smoothing buffer of a level filled with the sentinel: the state the
-// first sweep of a cycle expects whatever the tiling (each sweep then hands
-// the next one its sentinels).
+// The state the first sweep of a level expects whatever the tiling (each
+// sweep then leaves it for the next one): sentinels in the buffers through
+// which workgroups exchange values -- the strip buffers of the tiled scalar
+// sweeps, the sweep outputs of line GS and 3x3 blocks.
 hipError_t fill_sentinels(smg_handle_s* H, Level& v, hipStream_t st) {
-  const long nv = v.N * H->bs;
-  void* bufs[] = {v.ua, v.ub, v.y1, v.y2, v.zz, v.ux};
+  const bool strips = v.strip_cap > 0;
+  const long nv = strips ? v.strip_cap : v.N * H->bs;
+  void* bufs[] = {strips ? v.strip : v.ua, strips ? nullptr : v.ub, strips ? nullptr : v.ux};
+  if (strips) {
+    const hipError_t e = launch_fill_bits<unsigned>(v.par, 1, 0u, st);
+    if (e != hipSuccess) return e;
+  }
   for (void* p : bufs) {
     if (!p) continue;
     hipError_t e;
@@ -892,7 +895,7 @@ smg_status build_hierarchy(smg_handle_s* H, const double* coeffs, hipStream_t st
     hipError_t e_ = (expr);                                                                   \
     if (e_ != hipSuccess) return fail(H, SMG_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
-  SCHK(launch_fill_bits<unsigned>(H->ctr, 64, 0u, st));
+  SCHK(launch_fill_bits<unsigned>(H->ctr, CTR_WORDS, 0u, st));
   SCHK(launch_fill_bits<unsigned>(H->err, 64, 0u, st));
   SCHK(launch_fill_bits<unsigned>((unsigned*)H->info, 64, 0u, st));
   // level 0 copy (Dirichlet couplings zeroed), coarse operators by RAP
@@ -1080,15 +1083,18 @@ extern "C" {
 
 // Workspace bytes of cfg; with automatic coarsening the largest over the
 // possible numbers of leading x,y-only levels.
-size_t plan_bytes(const smg_config& cfg, int* nlev, int* nc) {
-  if (cfg.coarsen != SMG_COARSEN_AUTO) return plan(cfg, nullptr, nullptr, nlev, nc);
+size_t plan_bytes(const smg_config& cfg, int* nlev, int* nc, size_t* core = nullptr) {
+  if (cfg.coarsen != SMG_COARSEN_AUTO) return plan(cfg, nullptr, nullptr, nlev, nc, nullptr, core);
   size_t best = 0;
+  if (core) *core = 0;
   for (int s = MAXLEV; s >= 0; --s) {
     smg_config e = cfg;
     e.coarsen = SMG_COARSEN_FULL;
     e.semi_levels = s;
     int nl = 0, ncc = 0;
-    const size_t b = plan(e, nullptr, nullptr, &nl, &ncc);
+    size_t c = 0;
+    const size_t b = plan(e, nullptr, nullptr, &nl, &ncc, nullptr, &c);
+    if (core && b > 0) *core = std::max(*core, c);
     if (b > best || s == MAXLEV) {
       *nlev = nl;
       *nc = ncc;
@@ -1197,7 +1203,11 @@ static smg_status setup_impl(const smg_config* cfg, const double* coeffs, void* 
 // ends).  Host code never passes the array's name to a kernel or copy: its
 // device address is taken once per device with hipGetSymbolAddress and kept
 // in g_scratch_ptr.
-static __device__ __align__(256) unsigned char scratch[SMG_SCRATCH_BYTES];
+// SMG_SCRATCH_BYTES bound the hierarchy without its strip buffers, which take
+// at most 1/32 of it (7-point FP64 / FP32 and FP16: a strip entry pair per 64
+// bytes of packed sweep data, two buffers and two directions) plus alignment.
+constexpr size_t SCRATCH_ALL = SMG_SCRATCH_BYTES + SMG_SCRATCH_BYTES / 16;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_ALL];
 constexpr int SMG_SCRATCH_DEVICES = 64;
 static void* g_scratch_ptr[SMG_SCRATCH_DEVICES];
 static std::mutex g_scratch_mu;
@@ -1227,16 +1237,17 @@ smg_status smg_setup_noalloc(const smg_config* cfg, const double* coeffs, void* 
   const char* why = check_cfg(cfg);
   if (why) return fail(nullptr, SMG_EINVAL, "%s", why);
   int nlev = 0, nc = 0;
-  const size_t need = plan_bytes(*cfg, &nlev, &nc);
+  size_t core = 0;
+  const size_t need = plan_bytes(*cfg, &nlev, &nc, &core);
   if (need == 0) return fail(nullptr, SMG_EINVAL, "coarsest level has %d unknowns (> max_coarse)", nc);
-  if (need > SMG_SCRATCH_BYTES)
+  if (core > SMG_SCRATCH_BYTES || need > SCRATCH_ALL)
     return fail(nullptr, SMG_ENOMEM,
-                "hierarchy needs %zu bytes; the static scratch array holds %zu (use smg_setup with a workspace)", need,
+                "hierarchy needs %zu bytes; the static scratch array holds %zu (use smg_setup with a workspace)", core,
                 (size_t)SMG_SCRATCH_BYTES);
   void* p = nullptr;
   const smg_status s = scratch_address(&p);
   if (s != SMG_OK) return s;
-  return setup_impl(cfg, coeffs, p, SMG_SCRATCH_BYTES, stream, out, false);
+  return setup_impl(cfg, coeffs, p, SCRATCH_ALL, stream, out, false);
 }
 
 smg_status smg_resetup(smg_handle h, const double* coeffs, void* stream) {
@@ -1583,23 +1594,16 @@ static hipError_t op_presmooth_t(smg_handle_s* H, const Level& v, const void* f,
     if (e == hipSuccess) e = bsweep<typename PT::E, V>(H, v, +1, (const V*)f, (V*)u, nullptr, 0, st);
     return e;
   }
-  if (H->cfg.smoother == SMG_SMOOTH_GS) {
-    e = launch_fill_bits<V>((V*)u, nv, sent, st);
-    if (e == hipSuccess)
-      e = sweep<typename PT::E, V>(H, v, +1, false, (const V*)f, (V*)u, nullptr, 0, nullptr, nullptr, st);
-    return e;
-  }
+  if (H->cfg.smoother == SMG_SMOOTH_GS)
+    return sweep<typename PT::E, V>(H, v, +1, false, (const V*)f, (V*)u, nullptr, nullptr, st);
   if (H->cfg.smoother == SMG_SMOOTH_LGS) {
     e = launch_fill_bits<V>((V*)u, nv, sent, st);
     if (e == hipSuccess) e = lgs_sweep<PT>(H, v, +1, (const V*)f, nullptr, (V*)u, nullptr, st);
     return e;
   }
-  e = launch_fill_bits<V>((V*)v.h, nv, sent, st);
-  if (e == hipSuccess) e = launch_fill_bits<V>((V*)u, nv, sent, st);
+  e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)f, (V*)v.h, nullptr, nullptr, st);
   if (e == hipSuccess)
-    e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)f, (V*)v.h, nullptr, 0, nullptr, nullptr, st);
-  if (e == hipSuccess)
-    e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, (V*)u, nullptr, 0, nullptr, nullptr, st);
+    e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, (V*)u, nullptr, nullptr, st);
   return e;
 }
 
@@ -1639,24 +1643,21 @@ static hipError_t op_postsmooth_t(smg_handle_s* H, const Level& v, const void* f
   }
   if (H->cfg.smoother == SMG_SMOOTH_GS) {
     // the V-cycle's kernels for this level: h = f - lower(A) u_old with
-    // u_old = u_in + P ec (large levels: formed in u_a, whose sentinels are
-    // restored after)
+    // u_old = u_in + P ec (large levels: formed in u_a)
     if (split_rp(v) || H->cfg.interp != SMG_INTERP_VERTEX || v.qa) {
       e = hipMemcpyAsync(v.ua, uin, sizeof(V) * nv, hipMemcpyDeviceToDevice, st);
       if (e == hipSuccess && ec != nullptr) e = prolong_in_place<V>(H, v, (const V*)ec, (V*)v.ua, st);
       if (e == hipSuccess) e = old_terms<PT>(H, v, -1, (const V*)f, (const V*)v.ua, (V*)v.h, st);
-      if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.ua, nv, sent, st);
     } else {
       e = launch_prolong_post(v.S, v.g, v.cmask, A, (const V*)f, (const V*)uin, (const V*)ec, (V*)v.h,
                               (V*)nullptr, false, st);
     }
-    if (e == hipSuccess) e = launch_fill_bits<V>((V*)uout, nv, sent, st);
     if (e == hipSuccess)
-      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, (V*)uout, nullptr, 0, nullptr, nullptr, st);
+      e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.h, (V*)uout, nullptr, nullptr, st);
     return e;
   }
   // ILU correction: r = f - A u_old; u_out = u_old + U^-1 L^-1 r.  Scratch: the
-  // level's y1/y2/zz buffers, whose sentinel state is restored afterwards.
+  // level's y2 and zz buffers.
   if (H->cfg.interp != SMG_INTERP_VERTEX) {
     e = ec ? prolong_cell<V>(H, v, (const V*)ec, (const V*)uin, (V*)v.uo, st)
            : hipMemcpyAsync(v.uo, uin, sizeof(V) * nv, hipMemcpyDeviceToDevice, st);
@@ -1665,14 +1666,10 @@ static hipError_t op_postsmooth_t(smg_handle_s* H, const Level& v, const void* f
     e = launch_prolong_post(v.S, v.g, v.cmask, A, (const V*)f, (const V*)uin, (const V*)ec, (V*)v.h, (V*)v.uo,
                             true, st);
   }
-  if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.y2, nv, sent, st);
-  if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.zz, nv, sent, st);
   if (e == hipSuccess)
-    e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)v.h, (V*)v.y2, nullptr, 0, nullptr, nullptr, st);
+    e = sweep<typename PT::E, V>(H, v, +1, true, (const V*)v.h, (V*)v.y2, nullptr, nullptr, st);
   if (e == hipSuccess)
-    e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y2, (V*)v.zz, nullptr, 0, (const V*)v.uo, (V*)uout, st);
-  if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.y2, nv, sent, st);
-  if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.zz, nv, sent, st);
+    e = sweep<typename PT::E, V>(H, v, -1, false, (const V*)v.y2, (V*)v.zz, (const V*)v.uo, (V*)uout, st);
   return e;
 }
 

@@ -27,24 +27,20 @@
 //    four cycles at best) plus one exchange of values through LDS, so the
 //    workgroup splits the work by role, each role in waves of its own, and
 //    all waves meet at one workgroup barrier per step:
-//      - four compute waves, one column per lane: per step they read the
-//        right-hand side and the neighbours' values from LDS, run the chain
-//        of fmas, write the result to LDS, and prefetch the step's packed
-//        coefficients (a schedule-ordered copy, 16-byte coalesced loads,
-//        P steps ahead) -- about twenty instructions, no global stores and
-//        no waits on memory other than their own coefficient loads;
-//      - a halo wave: fetches the values of neighbouring tiles' columns
-//        (device-coherent loads PH steps ahead, checked against the
-//        sentinel) into the LDS ring;
+//      - four compute waves, one column per lane: the chain of fmas, the
+//        result to LDS, and the packed coefficients (a schedule-ordered copy,
+//        16-byte coalesced loads, P steps ahead); no global stores and no
+//        waits on memory other than their own coefficient loads;
+//      - a halo wave: fetches the values of neighbouring tiles' columns from
+//        their strips (below) into the LDS ring;
 //      - a load wave: streams the right-hand side into LDS as runs of 16
 //        consecutive z per column, two chunks of 16 steps ahead;
-//      - a store wave: stores the tile's own columns that other tiles read
-//        (device-coherent, one step after they are computed), and streams
-//        the results out of LDS as runs one chunk behind, together with the
-//        sentinels for the next sweep on the level.
+//      - a store wave: streams the results out of LDS as runs, one chunk
+//        behind;
+//      - an export wave: writes the tile's strip.
 //    Loads and stores never share a wave: a wave's vector memory operations
 //    retire in issue order, so a wave that waits for a load would also wait
-//    for every store issued before it, whose acknowledgement is slow.
+//    for every store issued before it, and no more than 63 may be in flight.
 //    Values that cross waves move through an LDS ring of 16 steps (the tile's
 //    columns plus a halo of neighbouring tiles' columns) and three chunk
 //    buffers (one filled, one computed, one drained).
@@ -52,15 +48,27 @@
 //    that step) have zero coefficients, scaling and right-hand side, so
 //    their result is zero without a test: the LDS is zeroed once per launch
 //    and every value in it stays finite.
-//  * Every position read by another tile holds a signalling-NaN sentinel
-//    until it is written; a value is ready when it is no longer the
-//    sentinel.  The sentinels for the next sweep on the same level are
-//    written by this sweep into that sweep's output.
-//  * A halo wave that finds a value not yet written first waits for the value
-//    WF_AHEAD steps further along the same column and then refetches its
-//    other prefetched halo values: the tile then runs far enough behind its
-//    producer that later prefetches find their values written, instead of
-//    paying one coherent round trip per step.
+//  * Tiles exchange values through strips: per step a tile writes the values
+//    of the columns that others read (31 of 256, 46 with 19/27 points) as one
+//    contiguous run, device-coherently.  A hyperplane has one step number per
+//    tile, so what a tile needs at a step from one neighbour is one step's
+//    run of that neighbour: two or three line reads instead of one scattered
+//    8-byte access per column, and the results themselves are plain full-line
+//    stores.  An entry holds a signalling-NaN sentinel until it is written; a
+//    value is ready when it is no longer the sentinel.  Each level has two
+//    strip buffers: a sweep uses one and restores the sentinels of the other
+//    (the last workgroup to finish switches them), so any sequence of sweeps,
+//    in either direction and onto any output, finds its buffer ready.
+//    Forward sweep before / after (exports and sentinels in the output, one
+//    wave for results and exports -> strips, an export wave; MI355X, FP64):
+//    256^3 7-point 757 -> 383 us, 128^3 27-point 840 -> 641 us, 512x512x64
+//    19-point 2662 -> 1846 us; an isolated 7-point tile steps in 0.166
+//    instead of 0.283 us (the store wave's limit of 63 stores in flight).
+//  * A halo wave that finds a value not yet written waits for the values
+//    AHEAD steps further on and refetches its prefetched values with them:
+//    the tile then runs far enough behind its producer that later prefetches
+//    find their values written, instead of paying one coherent round trip
+//    per step.
 //  * Tiles are handed out by an atomic ticket in dependence order, so a
 //    persistent grid of any size always makes progress.  Waits are bounded
 //    by a watchdog that raises an error flag instead of hanging.
@@ -76,9 +84,9 @@ namespace smg {
 constexpr int WF_HIST = 16;                  // LDS ring rows (steps)
 constexpr int WF_CH = 16;                    // steps per chunk of right-hand side / results
 constexpr int WF_NL = WF_TX * WF_TY;         // compute lanes (columns) per tile
-constexpr int WF_NH = 104;                   // halo slots around a tile
+constexpr int WF_NH = 52;                    // halo slots around a tile
 constexpr int WF_NB = 3;                     // chunk buffers: filled, computed, drained
-constexpr int WF_NW = 7;                     // waves: 4 compute, halo, load, store
+constexpr int WF_NW = 8;                     // waves: 4 compute, halo, load, store, export
 constexpr int WF_THREADS = 64 * WF_NW;
 constexpr int WF_GRP = WF_NL * WF_CH / 64;   // column-run groups per chunk (4 columns x 16 steps)
 constexpr int WF_GPS = WF_GRP / WF_CH;       // groups moved per step
@@ -118,6 +126,19 @@ __host__ __device__ constexpr int wf_kb(int pat) {
     m = d > m ? d : m;
   }
   return m;
+}
+
+// Term m of a sweep's triangle (canonical order): step distance of its
+// neighbour (in [-KB, -1]) and, leading terms only, how many have a value at
+// least two steps old.
+__host__ __device__ constexpr int wf_back(int pat, int dir, int m) {
+  const int so = dir > 0 ? m : pat / 2 + 1 + m;
+  return dir * (hp_wx(pat) * pat_off(pat, so, 0) + hp_wy(pat) * pat_off(pat, so, 1) + pat_off(pat, so, 2));
+}
+__host__ __device__ constexpr int wf_prefix(int pat, int dir) {
+  int n = 0;
+  while (n < pat / 2 && wf_back(pat, dir, n) <= -2) ++n;
+  return n;
 }
 
 // 16-byte packs per point and direction: the pat/2 coefficients of the
@@ -160,29 +181,38 @@ bool wf_ranges_ok(const Grid& g, const WfTiling& t, int pat, int vbytes, int eby
   return vec < 2147483647.0 && tile < 2147483647.0;
 }
 
-// Halo slot of column (qx, qy) relative to a tile (outside [0,TX) x [0,TY)):
-// the columns x-1 and x+TX with y in [-2, TY+2), and for x inside the tile the
-// rows y in {-2, -1, TY, TY+1}.  Every neighbour column of a tile lies there.
-__host__ __device__ constexpr int wf_halo_slot(int qx, int qy) {
-  return qx == -1 ? qy + 2
-                  : (qx == WF_TX ? 22 + qy
-                                 : (qy < 0 ? 40 + 2 * qx + (qy + 2) : 72 + 2 * qx + (qy - WF_TY)));
+// Halo slot of column (qx, qy) relative to a tile (outside [0,TX) x [0,TY)).
+// In the forward frame (a backward sweep mirrors both axes) these are the
+// column x-1 with y in [-2, TY+2), the row y = -1 and one second row: y = -2
+// (sheared tiles) or y = TY (rectangles, whose lower neighbours reach
+// (x-1, y+1)).
+__host__ __device__ constexpr int wf_halo_slot(int dir, int qx, int qy) {
+  const int fx = dir > 0 ? qx : WF_TX - 1 - qx, fy = dir > 0 ? qy : WF_TY - 1 - qy;
+  return fx < 0 ? fy + 2 : (fy == -1 ? 20 + fx : 36 + fx);
 }
-__device__ inline void wf_halo_pos(int hs, int* qx, int* qy) {
-  if (hs < 20) {
-    *qx = -1;
-    *qy = hs - 2;
-  } else if (hs < 40) {
-    *qx = WF_TX;
-    *qy = hs - 22;
-  } else if (hs < 72) {
-    *qx = (hs - 40) / 2;
-    *qy = (hs - 40) % 2 - 2;
-  } else {
-    *qx = (hs - 72) / 2;
-    *qy = WF_TY + (hs - 72) % 2;
+// Forward-frame position of slot t.
+__device__ inline void wf_halo_pos(int sh, int t, int* fx, int* fy) {
+  *fx = t < 20 ? -1 : (t < 36 ? t - 20 : t - 36);
+  *fy = t < 20 ? t - 2 : (t < 36 ? -1 : (sh ? -2 : WF_TY));
+}
+
+// Export strips.  Per step a tile publishes the values of the columns that
+// other tiles read as one contiguous line group of wf_es entries: entries
+// 0..15 the columns lx = TX-1, 16..31 the columns ly = TY-1, 32..47 (19/27
+// points) the second row (ly = TY-2 of sheared tiles, ly = 0 of rectangles),
+// all in the forward frame.  Entry e of step s of a tile is at
+// ((tile*NS + s)*wf_es + e).
+__host__ __device__ constexpr int wf_es(int pat) { return pat == 7 ? 32 : 48; }
+__device__ inline int wf_export_lane(int dir, int sh, int e) {
+  int lx = e < 16 ? WF_TX - 1 : (e < 32 ? e - 16 : e - 32);
+  int ly = e < 16 ? e : (e < 32 ? WF_TY - 1 : (sh ? WF_TY - 2 : 0));
+  if (dir < 0) {
+    lx = WF_TX - 1 - lx;
+    ly = WF_TY - 1 - ly;
   }
+  return lx * WF_TY + ly;
 }
+long wf_strip_elems(const WfTiling& t, int pat) { return (long)t.ntx * t.nty * t.ns * wf_es(pat); }
 
 // Is halo column (qx, qy) a neighbour column of some lane of the tile in a
 // sweep of direction dir?
@@ -201,30 +231,29 @@ __device__ inline __amdgpu_buffer_rsrc_t wf_rsrc(const void* p, unsigned bytes) 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
 template <class V, int CP>
-__device__ inline V bld(__amdgpu_buffer_rsrc_t r, unsigned off);
-template <>
-__device__ inline double bld<double, 0>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+__device__ inline V bld(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0u) {
+  if constexpr (sizeof(V) == 8)
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, CP));
+  else
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, CP));
 }
-template <>
-__device__ inline double bld<double, WF_SC1>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, WF_SC1));
+template <int CP, class V>
+__device__ inline void bst(V v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0u) {
+  if constexpr (sizeof(V) == 8)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, soff, CP);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, soff, CP);
 }
-template <>
-__device__ inline float bld<float, 0>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+
+template <class V>
+__device__ inline V wf_coherent_load(const V* p) {
+  using U = typename VBits<V>::U;
+  return VBits<V>::val(__hip_atomic_load(reinterpret_cast<const U*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
-template <>
-__device__ inline float bld<float, WF_SC1>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, WF_SC1));
-}
-template <int CP>
-__device__ inline void bst(double v, __amdgpu_buffer_rsrc_t r, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, CP);
-}
-template <int CP>
-__device__ inline void bst(float v, __amdgpu_buffer_rsrc_t r, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, CP);
+template <class V>
+__device__ inline void wf_coherent_store(V* p, V v) {
+  using U = typename VBits<V>::U;
+  __hip_atomic_store(reinterpret_cast<U*>(p), VBits<V>::bits(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Storage element traits: arithmetic type V, elements per 16-byte pack K,
@@ -264,54 +293,13 @@ struct WfE<__half> {
   }
 };
 
-// Columns of a tile that no lane of another tile reads in a sweep of
-// direction dir: the lanes whose consumers (lane - neighbour-column offset,
-// sheared) all lie inside the tile, an intersection of shifted copies of the
-// tile, hence a rectangle [xl, xh) x [yl, yh).
-struct WfRect {
-  int xl, xh, yl, yh;
-};
-__host__ __device__ constexpr WfRect wf_inner(int pat, int dir, int sh) {
-  WfRect r{0, WF_TX, 0, WF_TY};
-  for (int c = 0; c < 4; ++c) {
-    if (!col_used(pat, c)) continue;
-    const int cx = dir * col_dx(c), cy = dir * col_dy(c) + sh * dir * col_dx(c);
-    r.xl = r.xl > cx ? r.xl : cx;
-    r.xh = r.xh < WF_TX + cx ? r.xh : WF_TX + cx;
-    r.yl = r.yl > cy ? r.yl : cy;
-    r.yh = r.yh < WF_TY + cy ? r.yh : WF_TY + cy;
-  }
-  return r;
-}
-__host__ __device__ constexpr int wf_exported_count(const WfRect& r) {
-  return WF_NL - (r.xh - r.xl) * (r.yh - r.yl);
-}
-// Lane (lx*TY + ly) of the e-th column outside the rectangle, in lane order.
-__device__ inline int wf_exported_lane(const WfRect& r, int e) {
-  const int nm = WF_TY - (r.yh - r.yl);  // outside columns per row inside [xl, xh)
-  int lx, ly;
-  if (e < WF_TY * r.xl) {
-    lx = e / WF_TY;
-    ly = e % WF_TY;
-  } else if (e < WF_TY * r.xl + nm * (r.xh - r.xl)) {
-    const int q = e - WF_TY * r.xl;
-    lx = r.xl + q / nm;
-    const int w = q % nm;
-    ly = w < r.yl ? w : r.yh + (w - r.yl);
-  } else {
-    const int q = e - WF_TY * r.xl - nm * (r.xh - r.xl);
-    lx = r.xh + q / WF_TY;
-    ly = q % WF_TY;
-  }
-  return lx * WF_TY + ly;
-}
-
 // Geometry of one tile shared by all roles.
 struct WfGeo {
   int X, Y, sh, NS, nsteps;
   int p0;             // first x plane of the vector buffers
   unsigned vbytes;    // bytes of the vector buffers (planes p0 .. p1-1)
   long vb;            // element offset of plane p0
+  bool full;          // every column of the tile lies in the grid
 };
 
 template <class V>
@@ -327,6 +315,8 @@ __device__ inline WfGeo wf_geo(const WfArgs<V>& a, unsigned tile) {
   const long pl = (long)a.g.ny * a.g.nz;
   q.vbytes = (unsigned)((p1 - q.p0) * pl * (long)sizeof(V));
   q.vb = q.p0 * pl;
+  const int y0 = q.Y * WF_TY;
+  q.full = q.X * WF_TX + WF_TX <= a.g.nx && y0 - q.sh * (WF_TX - 1) >= 0 && y0 + WF_TY <= a.g.ny;
   return q;
 }
 
@@ -359,7 +349,7 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
     const int cx = DIR * col_dx(c), cy = DIR * col_dy(c);
     const int qx = lx + cx, qy = ly + cy + q.sh * cx;
     const bool in = qx >= 0 && qx < WF_TX && qy >= 0 && qy < WF_TY;
-    nidx[c] = !col_used(PAT, c) ? 0 : (in ? qx * WF_TY + qy : WF_NL + wf_halo_slot(qx, qy));
+    nidx[c] = !col_used(PAT, c) ? 0 : (in ? qx * WF_TY + qy : WF_NL + wf_halo_slot(DIR, qx, qy));
   }
   const unsigned tbytes = (unsigned)NS * NPK * PACKB;
   const auto rp = wf_rsrc((const char*)a.pk + (size_t)tile * tbytes, tbytes);
@@ -374,62 +364,113 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
   const unsigned zlim = xt < a.g.nx && yt >= 0 && yt < a.g.ny ? (unsigned)a.g.nz : 0u;
   u32x4 cf[P][NPK];
   u32x2 sdv[P];
-  auto prefetch = [&](int k, int j) {
+  // Offsets of step k's packs; pack p (and, with the last, the FP16 scalars)
+  // into slot j.
+  struct Po {
+    unsigned so, vo, ss, vs;
+  };
+  auto pack_off = [&](int k) {
     const int s = wf_step<DIR>(NS, k);
     const bool sin = s >= 0 && s < NS;
-    const unsigned so = sin ? (unsigned)s * (NPK * PACKB) : WF_OOB;
     const bool pt = (unsigned)(s - skew) < zlim;
-    const unsigned vo = pt ? tid * 16u : WF_OOB;
-#pragma unroll
-    for (int p = 0; p < NPK; ++p)
-      cf[j][p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, vo, so + p * PACKB, 0));
-    if (T::HALF && !wf_sd_in_pack(PAT))
-      sdv[j] = __builtin_amdgcn_raw_buffer_load_b64(rs, pt ? tid * 8u : WF_OOB,
-                                                    sin ? (unsigned)s * (WF_NL * 8u) : WF_OOB, 0);
+    return Po{sin ? (unsigned)s * (NPK * PACKB) : WF_OOB, pt ? tid * 16u : WF_OOB,
+              sin ? (unsigned)s * (WF_NL * 8u) : WF_OOB, pt ? tid * 8u : WF_OOB};
   };
+  auto pack_load = [&](const Po& o, int j, int p) {
+    cf[j][p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, o.vo, o.so + p * PACKB, 0));
+    if (T::HALF && !wf_sd_in_pack(PAT) && p == NPK - 1)
+      sdv[j] = __builtin_amdgcn_raw_buffer_load_b64(rs, o.vs, o.ss, 0);
+  };
+  constexpr int NPRE = wf_prefix(PAT, DIR);
 #pragma unroll
-  for (int j = 0; j < P; ++j) prefetch(j, j);
-  V own_prev = V(0);
+  for (int j = 0; j < P; ++j) {
+    // (step 0 has no points: its prefix is skipped, so slot 0 starts with the
+    // prefix packs of step P)
+    const Po o = pack_off(j), on = pack_off(j + P);
+#pragma unroll
+    for (int p = 0; p < NPK; ++p) pack_load(j == 0 && p < NPRE / T::K ? on : o, j, p);
+  }
+  // A step's critical path is: barrier, LDS reads, chain of fmas, LDS write,
+  // barrier.  So a step reads after its barrier only the values of the step
+  // before (back == -1); older ones were read in the step before, and the
+  // leading terms made of older ones (8 of 13 forward, 27-point) are already
+  // summed.  Each step then prepares the next one behind its own LDS write.
+  constexpr bool SDP = T::HALF && wf_sd_in_pack(PAT);
+  V own_prev = V(0), tp = V(0);
+  V ve[NT];  // values at least two steps old of the current step's terms
+#pragma unroll
+  for (int m = 0; m < NT; ++m) ve[m] = V(0);
   __syncthreads();  // prologue: the first chunk is in LDS
+  tp = hbuf[tid];   // (the first step's coefficients are zero)
 
   for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
     V* hb = hbuf + ((k0 / WF_CH) % WF_NB) * (WF_CH * WF_HRW) + tid;
+    const V* hbn = hbuf + ((k0 / WF_CH + 1) % WF_NB) * (WF_CH * WF_HRW) + tid;
 #pragma unroll
     for (int j = 0; j < WF_HIST; ++j) {
-      const int jp = j % P;
-      constexpr bool SDP = T::HALF && wf_sd_in_pack(PAT);
-      const V sc = T::HALF ? __uint_as_float(SDP ? cf[jp][NPK - 1][2] : sdv[jp].x) : V(1);
-      V t = hb[j * WF_HRW];
-      // all neighbour values first (one wait), then the chain of fmas in
-      // canonical order of the triangle's offsets
-      V val[NT];
-#pragma unroll
-      for (int m = 0; m < NT; ++m) {
+      const int jp = j % P, jn = (j + 1) % P;
+      auto ring_value = [&](int m, int step) {
         const int so = DIR > 0 ? m : C + 1 + m;
-        const int dx = pat_off(PAT, so, 0), dy = pat_off(PAT, so, 1), dz = pat_off(PAT, so, 2);
-        if (dx == 0 && dy == 0) {
-          val[m] = own_prev;
-        } else {
-          const int c = col_of(DIR * dx, DIR * dy);
-          const int back = DIR * (WX * dx + WY * dy + dz);  // in [-KB, -1]
-          val[m] = ring[((j + back + WF_HIST) % WF_HIST) * WF_RW + nidx[c]];
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < NT; ++m) {
-        V cm;
+        const int c = col_of(DIR * pat_off(PAT, so, 0), DIR * pat_off(PAT, so, 1));
+        return ring[((step + wf_back(PAT, DIR, m) + WF_HIST) % WF_HIST) * WF_RW + nidx[c < 0 ? 0 : c]];
+      };
+      auto own = [](int m) {
+        const int so = DIR > 0 ? m : C + 1 + m;
+        return pat_off(PAT, so, 0) == 0 && pat_off(PAT, so, 1) == 0;
+      };
+      auto coeff = [&](int slot, int m) {
         if constexpr (T::HALF)
-          cm = T::scaled(cf[jp], m, sc);
+          return T::scaled(cf[slot], m, __uint_as_float(SDP ? cf[slot][NPK - 1][2] : sdv[slot].x));
         else
-          cm = T::get(cf[jp], m);
-        t = fma(-cm, val[m], t);
+          return T::get(cf[slot], m);
+      };
+      V val[NT], vn[NT];
+#pragma unroll
+      for (int m = 0; m < NT; ++m)
+        val[m] = wf_back(PAT, DIR, m) < -1 ? ve[m] : (own(m) ? own_prev : ring_value(m, j));
+#pragma unroll
+      for (int m = 0; m < NT; ++m)
+        if (wf_back(PAT, DIR, m) < -1) vn[m] = ring_value(m, j + 1);
+      const V hn = j + 1 < WF_HIST ? hb[(j + 1) * WF_HRW] : hbn[0];
+      __builtin_amdgcn_sched_barrier(0);
+      V t = tp;
+      const Po po = pack_off(k0 + j + P);
+#pragma unroll
+      for (int m = NPRE; m < NT; ++m) {
+        t = fma(-coeff(jp, m), val[m], t);
+        // without a prefix the refilling loads go between the fmas
+        if (NPRE == 0 && (m + 1) % T::K == 0 && m / T::K < NPK - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          pack_load(po, jp, m / T::K);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       const V dv = T::HALF ? __uint_as_float(SDP ? cf[jp][NPK - 1][3] : sdv[jp].y) : T::get(cf[jp], NT);
       const V xv = UNITD ? t : t * dv;
       own_prev = xv;
       ring[j * WF_RW + tid] = xv;
       hb[j * WF_HRW] = xv;
-      prefetch(k0 + j + P, jp);
+      __builtin_amdgcn_sched_barrier(0);
+      // refill the packs that were used for the last time (those of the prefix
+      // are refilled below, one step earlier)
+      constexpr int DONE = NPRE == 0 ? (NT / T::K < NPK - 1 ? NT / T::K : NPK - 1) : NPRE / T::K;
+#pragma unroll
+      for (int p = DONE; p < NPK; ++p) pack_load(po, jp, p);
+      tp = hn;
+      const Po pn = pack_off(k0 + j + 1 + P);
+#pragma unroll
+      for (int m = 0; m < NPRE; ++m) {
+        tp = fma(-coeff(jn, m), vn[m], tp);
+        if ((m + 1) % T::K == 0 && m / T::K < NPK - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          pack_load(pn, jn, m / T::K);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < NT; ++m)
+        if (wf_back(PAT, DIR, m) < -1) ve[m] = vn[m];
+      __builtin_amdgcn_sched_barrier(0);
       __syncthreads();
     }
   }
@@ -439,103 +480,81 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
 
 // ---- halo role (wave 4) ------------------------------------------------------
 template <int PAT, int DIR, class V>
-__device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, V* ring, unsigned* err) {
+__device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, const V* strip, V* ring, unsigned* err) {
   using B = VBits<V>;
-  constexpr int WX = hp_wx(PAT), WY = hp_wy(PAT);
-  constexpr int KB = wf_kb(PAT);
+  constexpr int WX = hp_wx(PAT), WY = hp_wy(PAT), ES = wf_es(PAT);
   constexpr int PH = WF_PH;
-  constexpr int WF_AHEAD = PH + WF_LAG_EXTRA;  // steps a stalled tile falls back behind its producer
+  constexpr int AHEAD = PH + WF_LAG_EXTRA;  // steps a stalled tile falls back behind its producer
   static_assert(WF_HIST % PH == 0 && PH >= 2, "halo prefetch distance");
   const int t = threadIdx.x - 4 * 64;
-  const int NS = q.NS, nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
-  const long vb = q.vb;
-  const auto rx = wf_rsrc(a.x + vb, q.vbytes);
+  const int NS = q.NS;
 
-  // halo slots t and 64 + t
-  bool hrole[2];
-  int hs[2], hskew[2];
-  unsigned hvo[2];
-  bool hcolv[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    hs[i] = t + 64 * i;
-    int hqx = 0, hqy = 0;
-    hrole[i] = false;
-    if (hs[i] < WF_NH) {
-      wf_halo_pos(hs[i], &hqx, &hqy);
-      hrole[i] = wf_halo_used(PAT, DIR, q.sh, hqx, hqy);
-    }
-    hskew[i] = (WX - q.sh * WY) * hqx + WY * hqy + KB;
-    const int gx = q.X * WF_TX + hqx, gy = q.Y * WF_TY + hqy - q.sh * hqx;
-    hcolv[i] = hrole[i] && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    hvo[i] = hcolv[i] ? (unsigned)(((gx - q.p0) * (long)ny + gy) * nz) : 0u;
+  // Halo slot t: the producing tile, its export entry and the distance dk
+  // between the producer's step and this tile's (a hyperplane has one step
+  // number per tile).
+  int fx = 0, fy = 0;
+  bool role = false;
+  if (t < WF_NH) {
+    wf_halo_pos(q.sh, t, &fx, &fy);
+    role = wf_halo_used(PAT, DIR, q.sh, DIR > 0 ? fx : WF_TX - 1 - fx, DIR > 0 ? fy : WF_TY - 1 - fy);
   }
-  V hb[2][PH];
-  auto halo_off = [&](int i, int k) {
-    const int s = wf_step<DIR>(NS, k);
-    const int hz = s - hskew[i];
-    const bool ok = s >= 0 && s < NS && hcolv[i] && hz >= 0 && hz < nz;
-    return ok ? (hvo[i] + (unsigned)hz) * (unsigned)sizeof(V) : WF_OOB;
+  const int ax = fx < 0 ? 1 : 0;
+  const int fyt = fy + (ax ? WF_TY * q.sh : 0) + 2 * WF_TY;  // >= 0
+  const int dyf = fyt / WF_TY - 2, lyf = fyt % WF_TY, lxf = ax ? WF_TX - 1 : fx;
+  const int PX = q.X - DIR * ax, PY = q.Y + DIR * dyf;
+  const bool have = role && PX >= 0 && PX < a.t.ntx && PY >= 0 && PY < a.t.nty;
+  const int dk = DIR * (WX * WF_TX * ax - WY * WF_TY * dyf);
+  const int e = lxf == WF_TX - 1 ? lyf : (lyf == WF_TY - 1 ? 16 + lxf : 32 + lxf);
+  const V* hp = have ? strip + (((long)PX * a.t.nty + PY) * NS) * ES + e : strip;
+  const int es = have ? ES : 0;
+
+  // does step k have a value, and its address (clamped to the producer's
+  // steps, so that every load is unconditional)
+  auto valid = [&](int k) {
+    const int s = wf_step<DIR>(NS, k), sp = s + dk;
+    return have && s >= 0 && s < NS && sp >= 0 && sp < NS;
   };
-  auto halo_fetch = [&](int k, int j) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) hb[i][j] = bld<V, WF_SC1>(rx, halo_off(i, k));
+  auto fetch = [&](int k) {
+    int sp = wf_step<DIR>(NS, k) + dk;
+    sp = sp < 0 ? 0 : (sp >= NS ? NS - 1 : sp);
+    return wf_coherent_load(hp + (long)sp * es);
   };
-  // Bounded wait until the value at byte offset off is no longer the
-  // sentinel (v: its last loaded value).
-  auto wait_value = [&](unsigned off, V v) {
-    unsigned spins = 0;
-    while (B::bits(v) == B::sent && spins < WF_SPIN_LIMIT) {
-      __builtin_amdgcn_s_sleep(1);
-      v = bld<V, WF_SC1>(rx, off);
-      ++spins;
-      // once any wait has timed out, stop waiting anywhere
-      if ((spins & 1023u) == 1023u && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-        spins = WF_SPIN_LIMIT;
-    }
-    if (spins >= WF_SPIN_LIMIT) atomicOr(err, 1u);
-    return v;
-  };
+  V hb[PH];
   // halo values of step k (slot j): wait for any that is still the sentinel,
   // then publish them in ring row k
-  auto halo_put = [&](int k, int j) {
-    bool miss = false;
+  auto put = [&](int k, int j) {
+    const bool ok = valid(k);
+    if (__builtin_amdgcn_ballot_w64(ok && B::bits(hb[j]) == B::sent) != 0) {
+      // fall back behind the producer: wait until the values AHEAD steps on
+      // are there, and with them this step's and the prefetched ones
+      unsigned spins = 0;
+      for (;;) {
+        const V far = fetch(k + AHEAD);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) miss |= B::bits(hb[i][j]) == B::sent;
-    if (__builtin_amdgcn_ballot_w64(miss) != 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (B::bits(hb[i][j]) == B::sent) {
-          // fall back behind the producer: wait for the value WF_AHEAD steps
-          // on (clamped to the column), then for this one
-          const int s = wf_step<DIR>(NS, k);
-          const int hz = s - hskew[i];
-          int zf = hz + DIR * WF_AHEAD;
-          zf = zf < 0 ? 0 : (zf >= nz ? nz - 1 : zf);
-          const unsigned offf = (hvo[i] + (unsigned)zf) * (unsigned)sizeof(V);
-          wait_value(offf, bld<V, WF_SC1>(rx, offf));
-          hb[i][j] = wait_value(halo_off(i, k), hb[i][j]);
+        for (int d = 0; d < PH; ++d) hb[(j + d) % PH] = fetch(k + d);
+        const bool miss = (ok && B::bits(hb[j]) == B::sent) || (have && B::bits(far) == B::sent);
+        if (__builtin_amdgcn_ballot_w64(miss) == 0) break;
+        if (++spins >= WF_SPIN_LIMIT) {
+          atomicOr(err, 1u);
+          break;
         }
+        // once any wait has timed out, stop waiting anywhere
+        if ((spins & 1023u) == 1023u && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u)) break;
+        __builtin_amdgcn_s_sleep(1);
       }
-      // the other prefetched halo values were fetched too early: fetch again
-#pragma unroll
-      for (int d = 1; d < PH; ++d) halo_fetch(k + d, (j + d) % PH);
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the refetched values are in
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      if (hrole[i]) ring[(k % WF_HIST) * WF_RW + WF_NL + hs[i]] = hb[i][j];
+    if (role) ring[(k % WF_HIST) * WF_RW + WF_NL + t] = ok ? hb[j] : V(0);
   };
 #pragma unroll
-  for (int j = 0; j < PH; ++j) halo_fetch(j, j);
+  for (int j = 0; j < PH; ++j) hb[j] = fetch(j);
   __syncthreads();  // prologue
 
   for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
 #pragma unroll
     for (int j = 0; j < WF_HIST; ++j) {
       const int k = k0 + j;
-      halo_put(k, j % PH);
-      halo_fetch(k + PH, j % PH);
+      put(k, j % PH);
+      hb[j % PH] = fetch(k + PH);
       __syncthreads();
     }
   }
@@ -583,15 +602,20 @@ struct WfRuns {
     sx = WX - q.sh * WY;
     gx = (ny - q.sh) * nz - sx;
     gy = 4 * (nz - WY);
+    vin = (unsigned)(cq * (nz - WY) + (DIR > 0 ? m : WF_CH - 1 - m)) * (unsigned)sizeof(V);
+    u0 = ((q.X * WF_TX - q.p0) * ny + q.Y * WF_TY) * nz - KB;
   }
   // Per-chunk bases of this lane's step s of the chunk.
   struct Base {
     int e;    // element offset of group 0
     int z;    // z of group 0
+    int u;    // inner chunks: uniform element offset of group 0
     int gx, gy, sx;
   };
-  __device__ Base base(int s) const { return Base{wf_keep(a0 + s), wf_keep(s - skq), wf_keep_s(gx), wf_keep_s(gy),
-                                                  wf_keep_s(sx)}; }
+  __device__ Base base(const WfGeo& q, int c) const {
+    const int s = wf_step<DIR>(q.NS, c * WF_CH + m), lo = wf_step<DIR>(q.NS, c * WF_CH + (DIR > 0 ? 0 : WF_CH - 1));
+    return Base{wf_keep(a0 + s), wf_keep(s - skq), u0 + lo, wf_keep_s(gx), wf_keep_s(gy), wf_keep_s(sx)};
+  }
   // Per-step bases: the four groups 4j .. 4j+3 moved at step j of a chunk
   // share the column row lx = j.
   struct Step {
@@ -602,9 +626,42 @@ struct WfRuns {
     const int y = q.X * WF_TX + j < nx ? y0 - q.sh * j : -WF_TY - 1;
     return Step{wf_keep(b.e + j * b.gx), wf_keep(b.z - j * b.sx), wf_keep(y), j};
   }
+  // Offsets of the groups 4j .. 4j+3 of a chunk (in: the chunk is inner),
+  // vector and scalar parts.
+  struct Offs {
+    unsigned v[WF_GPS], s[WF_GPS];
+  };
+  __device__ Offs offs(const WfArgs<V>& a, const WfGeo& q, const Base& b, int j, bool in) const {
+    Offs o;
+    if (in) {
+      const int us = wf_keep_s((b.u + j * b.gx) * (int)sizeof(V));
+#pragma unroll
+      for (int g = 0; g < WF_GPS; ++g) {
+        o.v[g] = vin;
+        o.s[g] = (unsigned)(us + g * b.gy * (int)sizeof(V));
+      }
+    } else {
+      const Step t = step(b, q, j);
+#pragma unroll
+      for (int g = 0; g < WF_GPS; ++g) {
+        o.v[g] = off_any(a, q, b, t, g);
+        o.s[g] = 0u;
+      }
+    }
+    return o;
+  }
   // byte offset of group 4*lx + g with every position in the grid
   __device__ static unsigned off_in(const Base& b, const Step& t, int g) {
     return (unsigned)(t.e + g * b.gy) * (unsigned)sizeof(V);
+  }
+  // Chunks whose 256 x 16 positions are all points (a full tile, away from
+  // both ends of its columns): one lane offset for the whole tile plus a
+  // uniform byte offset per group, so a group costs no vector arithmetic.
+  unsigned vin;          // lane part
+  int u0;                // uniform part of group 0 at step 0 (elements)
+  __device__ bool inner(const WfArgs<V>& a, const WfGeo& q, int c) const {
+    const int lo = wf_step<DIR>(q.NS, c * WF_CH + (DIR > 0 ? 0 : WF_CH - 1));  // steps [lo, lo + WF_CH)
+    return q.full && lo >= KB + sx * (WF_TX - 1) + WY * (WF_TY - 1) && lo + WF_CH - 1 - KB < a.g.nz;
   }
   // byte offset of group 4*lx + g, or WF_OOB where the position is outside the grid
   __device__ static unsigned off_any(const WfArgs<V>& a, const WfGeo& q, const Base& b, const Step& t, int g) {
@@ -625,171 +682,142 @@ __device__ __forceinline__ void wf_load(const WfArgs<V>& a, const WfGeo& q, V* h
   const auto rh = wf_rsrc(a.h + q.vb, q.vbytes);
   V reg[WF_GRP];
   // Per step j of a chunk: the registers of groups 4j .. 4j+3 (a chunk's
-  // runs) go to the chunk buffer hb, then take the runs of the chunk with
-  // bases b.
-  auto advance = [&](V* hb, const typename RU::Base& b, bool sync) {
+  // runs) go to the chunk buffer hb, then take the runs of chunk c.
+  auto advance = [&](V* hb, int c, bool sync) {
+    const typename RU::Base b = R.base(q, c);
+    const bool in = R.inner(a, q, c);
 #pragma unroll
     for (int j = 0; j < WF_HIST; ++j) {
+      // (the last two rows together: the compute waves read a chunk's first
+      // step one step ahead)
 #pragma unroll
-      for (int g = 0; g < WF_GPS; ++g) hb[4 * (j * WF_GPS + g)] = reg[j * WF_GPS + g];
-      const typename RU::Step t = R.step(b, q, j);
+      for (int i = j < WF_HIST - 2 ? j : WF_HIST - 2; i < WF_HIST && i <= (j < WF_HIST - 2 ? j : WF_HIST - 1); ++i) {
+        if (j == WF_HIST - 1) break;
 #pragma unroll
-      for (int g = 0; g < WF_GPS; ++g) reg[j * WF_GPS + g] = bld<V, 0>(rh, RU::off_any(a, q, b, t, g));
+        for (int g = 0; g < WF_GPS; ++g) hb[4 * (i * WF_GPS + g)] = reg[i * WF_GPS + g];
+        const typename RU::Offs o = R.offs(a, q, b, i, in);
+#pragma unroll
+        for (int g = 0; g < WF_GPS; ++g) reg[i * WF_GPS + g] = bld<V, 0>(rh, o.v[g], o.s[g]);
+      }
       if (sync)
         __syncthreads();
       else
         __builtin_amdgcn_sched_barrier(0);  // keep the refill behind this step's LDS writes
     }
   };
-  auto bases = [&](int c) { return R.base(wf_step<DIR>(q.NS, c * WF_CH + R.m)); };
   // prologue: chunk 0 into buffer 0, chunk 1 into the registers
   {
-    const typename RU::Base b = bases(0);
+    const typename RU::Base b = R.base(q, 0);
 #pragma unroll
     for (int j = 0; j < WF_HIST; ++j) {
-      const typename RU::Step t = R.step(b, q, j);
+      const typename RU::Offs o = R.offs(a, q, b, j, false);
 #pragma unroll
-      for (int g = 0; g < WF_GPS; ++g) reg[j * WF_GPS + g] = bld<V, 0>(rh, RU::off_any(a, q, b, t, g));
+      for (int g = 0; g < WF_GPS; ++g) reg[j * WF_GPS + g] = bld<V, 0>(rh, o.v[g], o.s[g]);
     }
   }
-  advance(hbuf + R.lds, bases(1), false);
+  advance(hbuf + R.lds, 1, false);
   __syncthreads();
 
   for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
     const int c = k0 / WF_CH;
     // chunk c+1's groups into LDS, then chunk c+2's into the registers freed
-    advance(hbuf + ((c + 1) % WF_NB) * (WF_CH * WF_HRW) + R.lds, bases(c + 2), true);
+    advance(hbuf + ((c + 1) % WF_NB) * (WF_CH * WF_HRW) + R.lds, c + 2, true);
   }
   __syncthreads();
   __syncthreads();
 }
 
-// ---- store role (wave 6): exports, results one chunk behind, sentinels -------
+// ---- store role (wave 6): results, one chunk behind ---------------------------
 template <int PAT, int DIR, class V>
-__device__ __forceinline__ void wf_store(const WfArgs<V>& a, const WfGeo& q, const V* ring, V* hbuf) {
-  using B = VBits<V>;
+__device__ __forceinline__ void wf_store(const WfArgs<V>& a, const WfGeo& q, V* hbuf) {
   using RU = WfRuns<PAT, DIR, V>;
-  constexpr int WX = hp_wx(PAT), WY = hp_wy(PAT), KB = wf_kb(PAT);
   const int lane = threadIdx.x - 6 * 64;
-  const int NS = q.NS, nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
   RU R;
   R.init(a, q, lane);
   const auto rx = wf_rsrc(a.x + q.vb, q.vbytes);
-  const auto rn = wf_rsrc((a.next != nullptr ? a.next : a.x) + q.vb, a.next != nullptr ? q.vbytes : 0u);
-  // Columns read by other tiles in this sweep (exported below) and in the
-  // next sweep (given the sentinel) lie outside the inner rectangles.  Bit r
-  // of xm / nm: is column 4r + cq outside (its run store dropped / its
-  // sentinel written)?  A set bit 31 puts an offset outside the buffer.
-  const WfRect ix = wf_inner(PAT, DIR, q.sh);
-  const WfRect inx = wf_inner(PAT, a.next_dir, q.sh);
-  unsigned long long xm = 0, nm = 0;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int ly = 4 * g + R.cq;
-    xm |= (ly < ix.yl || ly >= ix.yh) ? 0x1111111111111111ull << g : 0ull;
-    nm |= (ly < inx.yl || ly >= inx.yh) ? 0x1111111111111111ull << g : 0ull;
-  }
-#pragma unroll
-  for (int lx = 0; lx < WF_TX; ++lx) {
-    xm |= (lx < ix.xl || lx >= ix.xh) ? 0xFull << (4 * lx) : 0ull;
-    nm |= (lx < inx.xl || lx >= inx.xh) ? 0xFull << (4 * lx) : 0ull;
-  }
-  const unsigned xm0 = (unsigned)xm, xm1 = (unsigned)(xm >> 32);
-  const unsigned nm0 = ~(unsigned)nm, nm1 = ~(unsigned)(nm >> 32);  // set: no sentinel
-  // does group r hold a column that gets the sentinel (the same for all lanes)?
-  auto gsent = [&](int r) {
-    const int lx = r / 4, g = r % 4;
-    return lx < inx.xl || lx >= inx.xh || 4 * g < inx.yl || 4 * g + 3 >= inx.yh;
-  };
-  auto bit31 = [](unsigned w, int r) { return ((w >> (r % 32)) & 1u) << 31; };
-  auto put = [&](unsigned off, int r, const V* hb, bool nxt) {
-    const V v = hb[4 * r];
-    bst<0>(v, rx, off | bit31(r < 32 ? xm0 : xm1, r));
-    if (nxt && gsent(r)) bst<0>(B::val(B::sent), rn, off | bit31(r < 32 ? nm0 : nm1, r));
-  };
-  // exported column `lane` (in lane order) of the tile
-  const bool erole = lane < wf_exported_count(ix);
-  const int el = erole ? wf_exported_lane(ix, lane) : 0;
-  const int elx = el / WF_TY, ely = el % WF_TY;
-  const int exx = q.X * WF_TX + elx, eyy = q.Y * WF_TY + ely - q.sh * elx;
-  const bool ecolv = erole && exx < nx && eyy >= 0 && eyy < ny;
-  const unsigned evo = ecolv ? (unsigned)(((exx - q.p0) * (long)ny + eyy) * nz) : 0u;
-  const int eskew = (WX - q.sh * WY) * elx + WY * ely + KB;
-  // the exported columns' values of step k (ring row j = k mod 16), device-coherently
-  auto export_step = [&](int k, int j) {
-    const int s = wf_step<DIR>(NS, k);
-    const int z = s - eskew;
-    const bool ok = ecolv && k >= 0 && s >= 0 && s < NS && z >= 0 && z < nz;
-    const V v = ring[((j + WF_HIST) % WF_HIST) * WF_RW + el];
-    bst<WF_SC1>(v, rx, ok ? (evo + (unsigned)z) * (unsigned)sizeof(V) : WF_OOB);
-  };
-  auto chunk = [&](int k0, const typename RU::Base& b, int mode, const V* hb) {
+  auto chunk = [&](int c, bool sync) {
+    const V* hb = hbuf + (c % WF_NB) * (WF_CH * WF_HRW) + R.lds;
+    const typename RU::Base b = R.base(q, c);
+    const bool in = R.inner(a, q, c);
 #pragma unroll
     for (int j = 0; j < WF_HIST; ++j) {
-      export_step(k0 + j - 1, j - 1);
-      if (mode > 0) {
-        const typename RU::Step t = R.step(b, q, j);
+      const typename RU::Offs o = R.offs(a, q, b, j, in);
 #pragma unroll
-        for (int g = 0; g < WF_GPS; ++g) put(RU::off_any(a, q, b, t, g), j * WF_GPS + g, hb, mode == 2);
-      }
-      __syncthreads();
+      for (int g = 0; g < WF_GPS; ++g) bst<0>(hb[4 * (j * WF_GPS + g)], rx, o.v[g], o.s[g]);
+      if (sync) __syncthreads();
     }
   };
   __syncthreads();  // prologue
-
-  for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
-    const int c = k0 / WF_CH;
-    const V* hb = hbuf + ((c + WF_NB - 1) % WF_NB) * (WF_CH * WF_HRW) + R.lds;
-    const typename RU::Base b = R.base(wf_step<DIR>(q.NS, (c - 1) * WF_CH + R.m));
-    if (c == 0)
-      chunk(k0, b, 0, hb);
-    else if (a.next != nullptr)
-      chunk(k0, b, 2, hb);
-    else
-      chunk(k0, b, 1, hb);
-  }
+#pragma unroll 1
+  for (int j = 0; j < WF_HIST; ++j) __syncthreads();
+  for (int k0 = WF_HIST; k0 < q.nsteps; k0 += WF_HIST) chunk(k0 / WF_CH - 1, true);
   __syncthreads();
-  export_step(q.nsteps - 1, WF_HIST - 1);
-  {
-    const int c = q.nsteps / WF_CH - 1;
-    const V* hb = hbuf + (c % WF_NB) * (WF_CH * WF_HRW) + R.lds;
-    const typename RU::Base b = R.base(wf_step<DIR>(q.NS, c * WF_CH + R.m));
-#pragma unroll 4
-    for (int r = 0; r < WF_GRP; ++r) {
-      const unsigned off = RU::off_any(a, q, b, R.step(b, q, r / 4), r % 4);
-      const V v = hb[4 * r];
-      const unsigned xw = r < 32 ? xm0 : xm1, nw = r < 32 ? nm0 : nm1;
-      bst<0>(v, rx, off | (((xw >> (r % 32)) & 1u) << 31));
-      if (a.next != nullptr) bst<0>(B::val(B::sent), rn, off | (((nw >> (r % 32)) & 1u) << 31));
+  chunk(q.nsteps / WF_CH - 1, false);
+  __syncthreads();
+}
+
+// ---- export role (wave 7): the columns other tiles read -----------------------
+// One step after a value is computed it goes to this sweep's strip buffer
+// (device-coherently); the other buffer's entry gets the sentinel for the next
+// sweep on the level.
+template <int PAT, int DIR, class V>
+__device__ __forceinline__ void wf_export(const WfArgs<V>& a, const WfGeo& q, unsigned tile, V* strip, V* other,
+                                          const V* ring) {
+  using B = VBits<V>;
+  constexpr int ES = wf_es(PAT);
+  const int e = threadIdx.x - 7 * 64;
+  const bool role = e < ES;
+  const int el = role ? wf_export_lane(DIR, q.sh, e) : 0;
+  const long base = (long)tile * q.NS * ES + e;
+  auto step = [&](int k, int j) {
+    if (role && k >= 0 && k < q.NS) {
+      const long o = base + (long)wf_step<DIR>(q.NS, k) * ES;
+      wf_coherent_store(strip + o, ring[((j + WF_HIST) % WF_HIST) * WF_RW + el]);
+      other[o] = B::val(B::sent);
+    }
+  };
+  __syncthreads();  // prologue
+  for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
+#pragma unroll
+    for (int j = 0; j < WF_HIST; ++j) {
+      step(k0 + j - 1, j - 1);
+      __syncthreads();
     }
   }
+  __syncthreads();
+  step(q.nsteps - 1, WF_HIST - 1);
   __syncthreads();
 }
 
 // The LDS of a sweep workgroup: the value ring and the chunk buffers, zeroed
 // once per launch (inactive positions then compute zeros from zeros).
 template <class V>
-struct WfLds {
+struct alignas(16) WfLds {
   V ring[WF_HIST * WF_RW];
   V hbuf[WF_NB * WF_CH * WF_HRW];
 };
 template <class V>
 __device__ inline void wf_zero_lds(WfLds<V>* L) {
-  constexpr int n = (int)(sizeof(WfLds<V>) / 4);
-  unsigned* p = reinterpret_cast<unsigned*>(L);
-  for (int i = threadIdx.x; i < n; i += WF_THREADS) p[i] = 0u;
+  constexpr int n = (int)(sizeof(WfLds<V>) / 16);
+  u32x4* p = reinterpret_cast<u32x4*>(L);
+  for (int i = threadIdx.x; i < n; i += WF_THREADS) p[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
 }
 
-// The last workgroup to finish resets the ticket counters for the next launch.
-__device__ inline void wf_retire(unsigned* ctr) {
+// The last workgroup to finish resets the ticket counters for the next launch
+// and switches the strip buffers of the grids swept (flip(), every thread).
+template <class Flip>
+__device__ inline void wf_retire(unsigned* ctr, Flip flip) {
+  __shared__ unsigned s_last;
   if (threadIdx.x == 0) {
-    unsigned o = atomicAdd(&ctr[1], 1u);
-    if (o == gridDim.x - 1) {
+    s_last = atomicAdd(&ctr[1], 1u) == gridDim.x - 1 ? 1u : 0u;
+    if (s_last) {
       __hip_atomic_store(&ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&ctr[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+  __syncthreads();
+  if (s_last) flip();
 }
 
 __device__ inline unsigned wf_take_ticket(unsigned* ctr) {
@@ -810,14 +838,21 @@ __device__ __forceinline__ void wf_roles(Next next, unsigned* err, WfLds<typenam
   WfArgs<V> a;
   unsigned tile;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  // this sweep's strip buffer and the one of the level's next sweep
+  auto strip = [&](unsigned other) {
+    const unsigned par = __builtin_amdgcn_readfirstlane(*a.par) ^ other;
+    return a.strip + (par & 1u ? (long)a.t.ntx * a.t.nty * a.t.ns * wf_es(PAT) : 0l);
+  };
   if (wave < 4) {
     while (next(&a, &tile)) wf_compute<PAT, DIR, P, E, UNITD>(a, wf_geo(a, tile), tile, L->ring, L->hbuf);
   } else if (wave == 4) {
-    while (next(&a, &tile)) wf_halo<PAT, DIR, V>(a, wf_geo(a, tile), L->ring, err);
+    while (next(&a, &tile)) wf_halo<PAT, DIR, V>(a, wf_geo(a, tile), strip(0u), L->ring, err);
   } else if (wave == 5) {
     while (next(&a, &tile)) wf_load<PAT, DIR, V>(a, wf_geo(a, tile), L->hbuf);
+  } else if (wave == 6) {
+    while (next(&a, &tile)) wf_store<PAT, DIR, V>(a, wf_geo(a, tile), L->hbuf);
   } else {
-    while (next(&a, &tile)) wf_store<PAT, DIR, V>(a, wf_geo(a, tile), L->ring, L->hbuf);
+    while (next(&a, &tile)) wf_export<PAT, DIR, V>(a, wf_geo(a, tile), tile, strip(0u), strip(1u), L->ring);
   }
 }
 
@@ -836,7 +871,9 @@ __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<
     return true;
   };
   wf_roles<PAT, DIR, P, E, UNITD>(next, a.err, &L);
-  wf_retire(a.ctr);
+  wf_retire(a.ctr, [&] {
+    if (threadIdx.x == 0) *a.par ^= 1u;
+  });
 }
 
 // One sweep over many independent grids of the same pattern and precision in
@@ -845,9 +882,9 @@ __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<
 // tile's producers hold smaller tickets whatever the merge of the segments.
 template <int PAT, int DIR, int P, class E>
 __global__ __launch_bounds__(WF_THREADS) void k_wavefront_group(const WfArgs<typename WfVal<E>::V>* __restrict__ segs,
-                                                                const unsigned* __restrict__ tmap, unsigned total,
-                                                                const int* __restrict__ live, unsigned* ctr,
-                                                                unsigned* err) {
+                                                                int nseg, const unsigned* __restrict__ tmap,
+                                                                unsigned total, const int* __restrict__ live,
+                                                                unsigned* ctr, unsigned* err) {
   using V = typename WfVal<E>::V;
   __shared__ WfLds<V> L;
   wf_zero_lds(&L);
@@ -864,7 +901,10 @@ __global__ __launch_bounds__(WF_THREADS) void k_wavefront_group(const WfArgs<typ
     }
   };
   wf_roles<PAT, DIR, P, E, false>(next, err, &L);
-  wf_retire(ctr);
+  wf_retire(ctr, [&] {
+    for (int k = threadIdx.x; k < nseg; k += WF_THREADS)
+      if (live == nullptr || live[segs[k].sys] != 0) *segs[k].par ^= 1u;
+  });
 }
 
 // addout = addv + x (the correction step after an ILU(0) upper sweep)
@@ -1027,9 +1067,9 @@ static hipError_t launch_wf_t(const WfArgs<typename WfVal<E>::V>& a, hipStream_t
 }
 
 template <int PAT, int DIR, int P, class E>
-static hipError_t launch_wfg_t(const WfArgs<typename WfVal<E>::V>* segs, const unsigned* tmap, unsigned total,
+static hipError_t launch_wfg_t(const WfArgs<typename WfVal<E>::V>* segs, int nseg, const unsigned* tmap, unsigned total,
                                unsigned grid, const int* live, unsigned* ctr, unsigned* err, hipStream_t st) {
-  hipLaunchKernelGGL((k_wavefront_group<PAT, DIR, P, E>), dim3(grid), dim3(WF_THREADS), 0, st, segs, tmap, total,
+  hipLaunchKernelGGL((k_wavefront_group<PAT, DIR, P, E>), dim3(grid), dim3(WF_THREADS), 0, st, segs, nseg, tmap, total,
                      live, ctr, err);
   return hipGetLastError();
 }
@@ -1042,28 +1082,28 @@ constexpr int wf_prefetch() {
 }
 
 template <class E>
-hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<E>::V>* segs, const unsigned* tmap,
-                                  unsigned total, unsigned grid, const int* live, unsigned* ctr, unsigned* err,
-                                  hipStream_t st) {
+hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<E>::V>* segs, int nseg,
+                                  const unsigned* tmap, unsigned total, unsigned grid, const int* live, unsigned* ctr,
+                                  unsigned* err, hipStream_t st) {
   if (total == 0) return hipSuccess;
   if (grid == 0 || grid > total) grid = total;
   if (grid > (unsigned)WF_MAX_GRID) grid = WF_MAX_GRID;
 #define SMG_WFG_CASE(PATV)                                                                                       \
   if (pat == PATV && dir > 0)                                                                                    \
-    return launch_wfg_t<PATV, 1, wf_prefetch<PATV, E>(), E>(segs, tmap, total, grid, live, ctr, err, st);         \
+    return launch_wfg_t<PATV, 1, wf_prefetch<PATV, E>(), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);         \
   if (pat == PATV && dir < 0)                                                                                    \
-    return launch_wfg_t<PATV, -1, wf_prefetch<PATV, E>(), E>(segs, tmap, total, grid, live, ctr, err, st);
+    return launch_wfg_t<PATV, -1, wf_prefetch<PATV, E>(), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);
   SMG_WFG_CASE(7)
   SMG_WFG_CASE(19)
   SMG_WFG_CASE(27)
 #undef SMG_WFG_CASE
   return hipErrorInvalidValue;
 }
-template hipError_t launch_wavefront_group<double>(int, int, const WfArgs<double>*, const unsigned*, unsigned,
+template hipError_t launch_wavefront_group<double>(int, int, const WfArgs<double>*, int, const unsigned*, unsigned,
                                                    unsigned, const int*, unsigned*, unsigned*, hipStream_t);
-template hipError_t launch_wavefront_group<float>(int, int, const WfArgs<float>*, const unsigned*, unsigned, unsigned,
-                                                  const int*, unsigned*, unsigned*, hipStream_t);
-template hipError_t launch_wavefront_group<__half>(int, int, const WfArgs<float>*, const unsigned*, unsigned,
+template hipError_t launch_wavefront_group<float>(int, int, const WfArgs<float>*, int, const unsigned*, unsigned,
+                                                   unsigned, const int*, unsigned*, unsigned*, hipStream_t);
+template hipError_t launch_wavefront_group<__half>(int, int, const WfArgs<float>*, int, const unsigned*, unsigned,
                                                    unsigned, const int*, unsigned*, unsigned*, hipStream_t);
 
 template <class E>
