@@ -205,7 +205,7 @@ smg_status smg_set_graph(smg_handle h, int enable);
 
 /* Tile shape of the wavefront sweep of one level (the columns a workgroup
  * owns): 1 sheared (y offset by x, the default for 19/27-point levels with
- * more than one tile row), 2 rectangular 16 x 16 (the default otherwise), 0
+ * more than one tile row), 2 rectangular 8 x 16 (the default otherwise), 0
  * the default rule.  The sweep's results do not depend on it (every shape
  * runs the sequential lexicographic order; Sec. 4.4), only its time.
  * Rectangles of a 19/27-point sweep with more than one tile row are refused
@@ -312,8 +312,8 @@ smg_status smg_batch_solve(smg_batch b, const double* const* bv, double* const* 
                            smg_result* results, int* status, void* stream);
 
 /* Sweep schedule: merge order of the systems' tiles (0: system after system,
- * 1: round robin) and persistent grid of the batched sweeps (workgroups, one
- * per CU at most: larger values act as 256; 0: 256). */
+ * 1: round robin) and persistent grid of the batched sweeps (CUs, with two
+ * workgroups each; larger values act as 256; 0: 256). */
 smg_status smg_batch_set_schedule(smg_batch b, int order, int grid);
 /* Times batched V-cycles for every (order, grid) candidate and keeps the
  * fastest, then, level by level, the faster tile shape of the level's sweeps

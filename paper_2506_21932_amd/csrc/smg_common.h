@@ -133,7 +133,7 @@ struct BMatH {
   }
 };
 
-constexpr int WF_TX = 16, WF_TY = 16;  // columns per wavefront tile (256 lanes)
+constexpr int WF_TX = 8, WF_TY = 16;  // columns per wavefront tile (128 lanes)
 
 struct WfTiling {
   int sh, ntx, nty, ns;  // shear, tiles in x / y, steps per tile

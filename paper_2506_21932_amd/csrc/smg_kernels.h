@@ -8,7 +8,7 @@ namespace smg {
 
 // ---- wavefront triangular sweep --------------------------------------
 // Persistent grid of at most WF_MAX_GRID workgroups (one resident sweep
-// workgroup per CU: its LDS ring and chunk buffers take most of the CU's LDS).
+// workgroup per CU; grouped sweeps run two per CU).
 constexpr int WF_MAX_GRID = 256;
 
 template <class E>
@@ -42,6 +42,10 @@ struct WfArgs {
 // shape: 0 default (sheared for 19/27 points with more than one tile row),
 // 1 sheared, 2 rectangular
 void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape = 0);
+// Schedule positions a level reserves for a shape: those of tiles 16 columns
+// wide, whose padding is larger.  (The hierarchies that smg_setup_noalloc's
+// array takes then do not depend on the tile width.)
+long wf_reserve(const Grid& g, int pat, int shape);
 // 16-byte packs per schedule position and direction for storage elements of
 // ebytes bytes; offsets within a tile must stay below 2^31 bytes.
 int wf_pack_count(int pat, int ebytes);
@@ -67,7 +71,7 @@ hipError_t launch_wf_pack_h(int pat, const Grid& g, const WfTiling& tl, int dir,
 // segs[k]: the arguments of grid k of nseg (their ctr / err are not used);
 // tmap[t] = (k << 20) | r: ticket t is the r-th tile of grid k in its own
 // forward dependence order (each grid's tiles appear in increasing r);
-// total tickets; grid workgroups (0: one per tile); ctr / err as in WfArgs;
+// total tickets; 2 * grid workgroups (0: 2 * WF_MAX_GRID); ctr / err as in WfArgs;
 // tiles of a grid whose system is finished (live[sys] == 0) are skipped.
 template <class E>
 hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<E>::V>* segs, int nseg,

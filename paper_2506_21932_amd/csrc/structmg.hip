@@ -93,8 +93,8 @@ const char* check_cfg(const smg_config* c) {
   if (!c) return "null config";
   if (c->nx < 1 || c->ny < 1 || c->nz < 1) return "grid dimensions must be >= 1";
   if ((double)c->nx * c->ny * c->nz * (c->block > 1 ? c->block : 1) >= 2147483647.0) return "grid too large";
-  // sweep buffers address 18 x-planes and one tile's steps with 31-bit byte offsets
-  if ((double)(WF_TX + 2) * c->ny * c->nz * 8 >= 2147483647.0) return "ny * nz too large (limit 14.9e6)";
+  // sweep buffers address at most 18 x-planes and one tile's steps with 31-bit byte offsets
+  if (18.0 * c->ny * c->nz * 8 >= 2147483647.0) return "ny * nz too large (limit 14.9e6)";
   if (c->nz > 65536) return "nz too large (limit 65536)";
   if (c->block == 3 && (double)10 * c->ny * c->nz * 3 * 8 >= 2147483647.0) return "ny * nz too large for 3x3 blocks";
   if (c->block != 1 && c->block != 3) return "block must be 1 or 3";
@@ -206,13 +206,16 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
         v.tc32 = ar.take<float>((size_t)N);
       }
     } else if (bs == 1) {
-      // room for the sweep data of either tile shape (smg_set_tile_shape)
-      WfTiling t1, t2;
-      wf_tiling(v.g, v.Ssw, &t1, 1);
-      wf_tiling(v.g, v.Ssw, &t2, 2);
+      // room for the sweep data and strips of either tile shape
+      // (smg_set_tile_shape)
+      v.strip_cap = v.nsk_cap = 0;
+      for (int shape = 1; shape <= 2; ++shape) {
+        WfTiling t;
+        wf_tiling(v.g, v.Ssw, &t, shape);
+        v.nsk_cap = std::max(v.nsk_cap, wf_reserve(v.g, v.Ssw, shape));
+        v.strip_cap = std::max(v.strip_cap, 2 * wf_strip_elems(t, v.Ssw));
+      }
       wf_tiling(v.g, v.Ssw, &v.tl);
-      v.nsk_cap = std::max(t1.nsk, t2.nsk);
-      v.strip_cap = 2 * std::max(wf_strip_elems(t1, v.Ssw), wf_strip_elems(t2, v.Ssw));
       const size_t pbytes = (size_t)wf_pack_count(v.Ssw, eb) * 16 * v.nsk_cap;
       v.pk[0] = ar.take<char>(pbytes);
       v.pk[1] = ar.take<char>(pbytes);
@@ -853,15 +856,12 @@ hipError_t pack_sweep_data(smg_handle_s* H, Level& v, hipStream_t st) {
 // The state the first sweep of a level expects whatever the tiling (each
 // sweep then leaves it for the next one): sentinels in the buffers through
 // which workgroups exchange values -- the strip buffers of the tiled scalar
-// sweeps, the sweep outputs of line GS and 3x3 blocks.
+// sweeps (whose buffer word is zero: the counter block is cleared first), the
+// sweep outputs of line GS and 3x3 blocks.
 hipError_t fill_sentinels(smg_handle_s* H, Level& v, hipStream_t st) {
   const bool strips = v.strip_cap > 0;
   const long nv = strips ? v.strip_cap : v.N * H->bs;
   void* bufs[] = {strips ? v.strip : v.ua, strips ? nullptr : v.ub, strips ? nullptr : v.ux};
-  if (strips) {
-    const hipError_t e = launch_fill_bits<unsigned>(v.par, 1, 0u, st);
-    if (e != hipSuccess) return e;
-  }
   for (void* p : bufs) {
     if (!p) continue;
     hipError_t e;
@@ -1069,6 +1069,7 @@ hipError_t retile_level(smg_handle_s* H, int l, int shape, hipStream_t st, const
   if (t.sh == v.tl.sh) return hipSuccess;
   v.tl = t;
   hipError_t e = pack_sweep_data(H, v, st);
+  if (e == hipSuccess) e = launch_fill_bits<unsigned>(v.par, 1, 0u, st);
   if (e == hipSuccess) e = fill_sentinels(H, v, st);
   drop_vgraph(H);
   return e;
@@ -1203,9 +1204,10 @@ static smg_status setup_impl(const smg_config* cfg, const double* coeffs, void* 
 // ends).  Host code never passes the array's name to a kernel or copy: its
 // device address is taken once per device with hipGetSymbolAddress and kept
 // in g_scratch_ptr.
-// SMG_SCRATCH_BYTES bound the hierarchy without its strip buffers, which take
-// at most 1/32 of it (7-point FP64 / FP32 and FP16: a strip entry pair per 64
-// bytes of packed sweep data, two buffers and two directions) plus alignment.
+// SMG_SCRATCH_BYTES bound the hierarchy without its strip buffers.  Those take
+// at most 3/64 of it: two buffers of 24 entries a tile and step (7 points)
+// beside two directions of 128 columns of one pack (FP32) or two (FP64), at
+// least four entries each; 32 entries beside three packs with 19 points.
 constexpr size_t SCRATCH_ALL = SMG_SCRATCH_BYTES + SMG_SCRATCH_BYTES / 16;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_ALL];
 constexpr int SMG_SCRATCH_DEVICES = 64;

@@ -27,7 +27,7 @@
 //    four cycles at best) plus one exchange of values through LDS, so the
 //    workgroup splits the work by role, each role in waves of its own, and
 //    all waves meet at one workgroup barrier per step:
-//      - four compute waves, one column per lane: the chain of fmas, the
+//      - two compute waves, one column per lane: the chain of fmas, the
 //        result to LDS, and the packed coefficients (a schedule-ordered copy,
 //        16-byte coalesced loads, P steps ahead); no global stores and no
 //        waits on memory other than their own coefficient loads;
@@ -49,7 +49,7 @@
 //    their result is zero without a test: the LDS is zeroed once per launch
 //    and every value in it stays finite.
 //  * Tiles exchange values through strips: per step a tile writes the values
-//    of the columns that others read (31 of 256, 46 with 19/27 points) as one
+//    of the columns that others read (23 of 128, 30 with 19/27 points) as one
 //    contiguous run, device-coherently.  A hyperplane has one step number per
 //    tile, so what a tile needs at a step from one neighbour is one step's
 //    run of that neighbour: two or three line reads instead of one scattered
@@ -57,13 +57,21 @@
 //    stores.  An entry holds a signalling-NaN sentinel until it is written; a
 //    value is ready when it is no longer the sentinel.  Each level has two
 //    strip buffers: a sweep uses one and restores the sentinels of the other
-//    (the last workgroup to finish switches them), so any sequence of sweeps,
-//    in either direction and onto any output, finds its buffer ready.
-//    Forward sweep before / after (exports and sentinels in the output, one
-//    wave for results and exports -> strips, an export wave; MI355X, FP64):
-//    256^3 7-point 757 -> 383 us, 128^3 27-point 840 -> 641 us, 512x512x64
-//    19-point 2662 -> 1846 us; an isolated 7-point tile steps in 0.166
-//    instead of 0.283 us (the store wave's limit of 63 stores in flight).
+//    (the last workgroup switches them), so any sequence of sweeps, in either
+//    direction and onto any output, finds its buffer ready.  Forward sweep
+//    with 16 x 16 tiles before / after (exports and sentinels in the output,
+//    one wave for results and exports -> strips, an export wave; MI355X,
+//    FP64): 256^3 7-point 757 -> 383 us, 128^3 27-point 840 -> 641 us,
+//    512x512x64 19-point 2662 -> 1846 us; an isolated 7-point tile steps in
+//    0.166 instead of 0.283 us (the store wave's limit of 63 stores in flight).
+//  * Tiles are 8 columns wide in x.  A CU streams a tile's coefficients at
+//    40-70 GB/s whatever the prefetch depth, and LDS reads and 16-byte loads
+//    of four compute waves queue up in each step, so half the columns per CU
+//    nearly halve a step (27-point FP64 0.335 -> 0.18, FP32 0.22 -> 0.145,
+//    7-point 0.166 -> 0.124 us) while the hand-offs only grow by half.
+//    Forward sweep, 16 / 8 / 4 columns wide: 128^3 27-point FP64 638 / 396 /
+//    347 us, FP32 260 / 213 / 283 us; 64^3 FP64 197 / 132 / 164 us; 256^3
+//    7-point 384 / 330 / 426 us; 512x512x64 19-point 1844 / 1650 / 2114 us.
 //  * A halo wave that finds a value not yet written waits for the values
 //    AHEAD steps further on and refetches its prefetched values with them:
 //    the tile then runs far enough behind its producer that later prefetches
@@ -83,11 +91,11 @@ namespace smg {
 
 constexpr int WF_HIST = 16;                  // LDS ring rows (steps)
 constexpr int WF_CH = 16;                    // steps per chunk of right-hand side / results
-constexpr int WF_NL = WF_TX * WF_TY;         // compute lanes (columns) per tile
-constexpr int WF_NH = 52;                    // halo slots around a tile
 constexpr int WF_NB = 3;                     // chunk buffers: filled, computed, drained
-constexpr int WF_NW = 8;                     // waves: 4 compute, halo, load, store, export
-constexpr int WF_THREADS = 64 * WF_NW;
+constexpr int WF_NL = WF_TX * WF_TY;         // compute lanes (columns) per tile
+constexpr int WF_NCW = WF_NL / 64;           // compute waves
+constexpr int WF_THREADS = 64 * (WF_NCW + 4);  // ... and a halo, a load, a store and an export wave
+constexpr int WF_NH = 20 + 2 * WF_TX;        // halo slots around a tile
 constexpr int WF_GRP = WF_NL * WF_CH / 64;   // column-run groups per chunk (4 columns x 16 steps)
 constexpr int WF_GPS = WF_GRP / WF_CH;       // groups moved per step
 constexpr int WF_RW = WF_NL + WF_NH + 1;     // ring row length (padded)
@@ -153,7 +161,13 @@ __host__ __device__ constexpr int wf_npk(int pat, int ebytes) {
 // instead of two); otherwise (27-point) they come from a separate array.
 __host__ __device__ constexpr bool wf_sd_in_pack(int pat) { return pat / 2 + 4 <= 8 * wf_npk(pat, 2); }
 
-void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape) {
+// Does the last pack have a word that no step uses?
+__host__ __device__ constexpr bool wf_loose_pack(int pat, int ebytes) {
+  return ebytes == 2 ? pat != 7 : (pat / 2 + 1) % (16 / ebytes) != 0;
+}
+
+// Tiles of tx x 16 columns.
+static void wf_tile(const Grid& g, int pat, WfTiling* t, int shape, int tx) {
   // Default: tiles are sheared (y + x offset) when a lower neighbour column
   // lies at (x-1, y+1) (19- and 27-point patterns), so that every dependence
   // points to an earlier tile in x and y; otherwise, and when a single tile
@@ -166,11 +180,19 @@ void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape) {
   // (retile_level refuses that case).  shape 1 / 2 forces sheared /
   // rectangular tiles.
   t->sh = shape == 1 ? 1 : (shape == 2 ? 0 : ((pat == 7 || g.ny <= WF_TY) ? 0 : 1));
-  t->ntx = (g.nx + WF_TX - 1) / WF_TX;
-  t->nty = (g.ny + t->sh * (WF_TX - 1) + WF_TY - 1) / WF_TY;
+  t->ntx = (g.nx + tx - 1) / tx;
+  t->nty = (g.ny + t->sh * (tx - 1) + WF_TY - 1) / WF_TY;
   const int kb = wf_kb(pat);
-  t->ns = g.nz + (hp_wx(pat) - t->sh * hp_wy(pat)) * (WF_TX - 1) + hp_wy(pat) * (WF_TY - 1) + 2 * kb;
-  t->nsk = (long)t->ntx * t->nty * t->ns * WF_NL;
+  t->ns = g.nz + (hp_wx(pat) - t->sh * hp_wy(pat)) * (tx - 1) + hp_wy(pat) * (WF_TY - 1) + 2 * kb;
+  t->nsk = (long)t->ntx * t->nty * t->ns * tx * WF_TY;
+}
+
+void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape) { wf_tile(g, pat, t, shape, WF_TX); }
+
+long wf_reserve(const Grid& g, int pat, int shape) {
+  WfTiling t;
+  wf_tile(g, pat, &t, shape, 16);
+  return t.nsk;
 }
 
 int wf_pack_count(int pat, int ebytes) { return wf_npk(pat, ebytes); }
@@ -188,24 +210,24 @@ bool wf_ranges_ok(const Grid& g, const WfTiling& t, int pat, int vbytes, int eby
 // (x-1, y+1)).
 __host__ __device__ constexpr int wf_halo_slot(int dir, int qx, int qy) {
   const int fx = dir > 0 ? qx : WF_TX - 1 - qx, fy = dir > 0 ? qy : WF_TY - 1 - qy;
-  return fx < 0 ? fy + 2 : (fy == -1 ? 20 + fx : 36 + fx);
+  return fx < 0 ? fy + 2 : (fy == -1 ? 20 + fx : 20 + WF_TX + fx);
 }
 // Forward-frame position of slot t.
 __device__ inline void wf_halo_pos(int sh, int t, int* fx, int* fy) {
-  *fx = t < 20 ? -1 : (t < 36 ? t - 20 : t - 36);
-  *fy = t < 20 ? t - 2 : (t < 36 ? -1 : (sh ? -2 : WF_TY));
+  *fx = t < 20 ? -1 : (t < 20 + WF_TX ? t - 20 : t - 20 - WF_TX);
+  *fy = t < 20 ? t - 2 : (t < 20 + WF_TX ? -1 : (sh ? -2 : WF_TY));
 }
 
 // Export strips.  Per step a tile publishes the values of the columns that
-// other tiles read as one contiguous line group of wf_es entries: entries
-// 0..15 the columns lx = TX-1, 16..31 the columns ly = TY-1, 32..47 (19/27
-// points) the second row (ly = TY-2 of sheared tiles, ly = 0 of rectangles),
-// all in the forward frame.  Entry e of step s of a tile is at
+// other tiles read as one contiguous run of wf_es entries: the 16 columns
+// lx = TX-1, then the TX columns ly = TY-1, then (19/27 points) the TX columns
+// of the second row (ly = TY-2 of sheared tiles, ly = 0 of rectangles), all in
+// the forward frame.  Entry e of step s of a tile is at
 // ((tile*NS + s)*wf_es + e).
-__host__ __device__ constexpr int wf_es(int pat) { return pat == 7 ? 32 : 48; }
+__host__ __device__ constexpr int wf_es(int pat) { return WF_TY + (pat == 7 ? WF_TX : 2 * WF_TX); }
 __device__ inline int wf_export_lane(int dir, int sh, int e) {
-  int lx = e < 16 ? WF_TX - 1 : (e < 32 ? e - 16 : e - 32);
-  int ly = e < 16 ? e : (e < 32 ? WF_TY - 1 : (sh ? WF_TY - 2 : 0));
+  int lx = e < WF_TY ? WF_TX - 1 : (e - WF_TY) % WF_TX;
+  int ly = e < WF_TY ? e : (e < WF_TY + WF_TX ? WF_TY - 1 : (sh ? WF_TY - 2 : 0));
   if (dir < 0) {
     lx = WF_TX - 1 - lx;
     ly = WF_TY - 1 - ly;
@@ -325,7 +347,7 @@ __device__ inline int wf_step(int NS, int k) {
   return DIR > 0 ? k : NS - 1 - k;
 }
 
-// ---- compute role (waves 0-3) ----------------------------------------------
+// ---- compute role (the first two waves) ---------------------------------------
 template <int PAT, int DIR, int P, class E, bool UNITD>
 __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a, const WfGeo& q, unsigned tile,
                                            typename WfVal<E>::V* ring, typename WfVal<E>::V* hbuf) {
@@ -447,6 +469,10 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
       }
       const V dv = T::HALF ? __uint_as_float(SDP ? cf[jp][NPK - 1][3] : sdv[jp].y) : T::get(cf[jp], NT);
       const V xv = UNITD ? t : t * dv;
+      // words of the last pack without an entry stay live until here: reused
+      // as temporaries they would make their writer wait for every load in
+      // flight (27-point FP32: 0.246 instead of 0.15 us per step)
+      if constexpr (wf_loose_pack(PAT, sizeof(E))) asm volatile("" : : "v"(cf[jp][NPK - 1]));
       own_prev = xv;
       ring[j * WF_RW + tid] = xv;
       hb[j * WF_HRW] = xv;
@@ -478,7 +504,7 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
   __syncthreads();
 }
 
-// ---- halo role (wave 4) ------------------------------------------------------
+// ---- halo role ----------------------------------------------------------------
 template <int PAT, int DIR, class V>
 __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, const V* strip, V* ring, unsigned* err) {
   using B = VBits<V>;
@@ -486,7 +512,7 @@ __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, cons
   constexpr int PH = WF_PH;
   constexpr int AHEAD = PH + WF_LAG_EXTRA;  // steps a stalled tile falls back behind its producer
   static_assert(WF_HIST % PH == 0 && PH >= 2, "halo prefetch distance");
-  const int t = threadIdx.x - 4 * 64;
+  const int t = threadIdx.x - WF_NL;
   const int NS = q.NS;
 
   // Halo slot t: the producing tile, its export entry and the distance dk
@@ -499,12 +525,12 @@ __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, cons
     role = wf_halo_used(PAT, DIR, q.sh, DIR > 0 ? fx : WF_TX - 1 - fx, DIR > 0 ? fy : WF_TY - 1 - fy);
   }
   const int ax = fx < 0 ? 1 : 0;
-  const int fyt = fy + (ax ? WF_TY * q.sh : 0) + 2 * WF_TY;  // >= 0
+  const int fyt = fy + (ax ? WF_TX * q.sh : 0) + 2 * WF_TY;  // >= 0
   const int dyf = fyt / WF_TY - 2, lyf = fyt % WF_TY, lxf = ax ? WF_TX - 1 : fx;
   const int PX = q.X - DIR * ax, PY = q.Y + DIR * dyf;
   const bool have = role && PX >= 0 && PX < a.t.ntx && PY >= 0 && PY < a.t.nty;
   const int dk = DIR * (WX * WF_TX * ax - WY * WF_TY * dyf);
-  const int e = lxf == WF_TX - 1 ? lyf : (lyf == WF_TY - 1 ? 16 + lxf : 32 + lxf);
+  const int e = lxf == WF_TX - 1 ? lyf : (lyf == WF_TY - 1 ? WF_TY + lxf : WF_TY + WF_TX + lxf);
   const V* hp = have ? strip + (((long)PX * a.t.nty + PY) * NS) * ES + e : strip;
   const int es = have ? ES : 0;
 
@@ -549,12 +575,11 @@ __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, cons
   for (int j = 0; j < PH; ++j) hb[j] = fetch(j);
   __syncthreads();  // prologue
 
-  for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
+  for (int k0 = 0; k0 < q.nsteps; k0 += PH) {
 #pragma unroll
-    for (int j = 0; j < WF_HIST; ++j) {
-      const int k = k0 + j;
-      put(k, j % PH);
-      hb[j % PH] = fetch(k + PH);
+    for (int j = 0; j < PH; ++j) {
+      put(k0 + j, j);
+      hb[j] = fetch(k0 + j + PH);
       __syncthreads();
     }
   }
@@ -563,7 +588,7 @@ __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, cons
 }
 
 // ---- column runs (load and store roles) --------------------------------------
-// Group r of a chunk moves columns 4r + cq (cq = lane / 16), steps m = lane %
+// Group r (r = 4 lx + g) of a chunk moves columns 4r + cq (cq = lane / 16), steps m = lane %
 // 16 of the chunk: each column's 16 consecutive z values are one coalesced run.
 // Per chunk a lane forms its base offsets once, per step the step's bases; a
 // group then adds a uniform term.  The bases pass through wf_keep, which the
@@ -616,35 +641,36 @@ struct WfRuns {
     const int s = wf_step<DIR>(q.NS, c * WF_CH + m), lo = wf_step<DIR>(q.NS, c * WF_CH + (DIR > 0 ? 0 : WF_CH - 1));
     return Base{wf_keep(a0 + s), wf_keep(s - skq), u0 + lo, wf_keep_s(gx), wf_keep_s(gy), wf_keep_s(sx)};
   }
-  // Per-step bases: the four groups 4j .. 4j+3 moved at step j of a chunk
-  // share the column row lx = j.
+  // Per-step bases: the groups moved at one step of a chunk share a column
+  // row lx.
   struct Step {
     int e, z, y, lx;
   };
-  __device__ Step step(const Base& b, const WfGeo& q, int j) const {
+  __device__ Step step(const Base& b, const WfGeo& q, int lx) const {
     // a column row beyond the grid in x takes y = -1 - 16 (outside for every group)
-    const int y = q.X * WF_TX + j < nx ? y0 - q.sh * j : -WF_TY - 1;
-    return Step{wf_keep(b.e + j * b.gx), wf_keep(b.z - j * b.sx), wf_keep(y), j};
+    const int y = q.X * WF_TX + lx < nx ? y0 - q.sh * lx : -WF_TY - 1;
+    return Step{wf_keep(b.e + lx * b.gx), wf_keep(b.z - lx * b.sx), wf_keep(y), lx};
   }
-  // Offsets of the groups 4j .. 4j+3 of a chunk (in: the chunk is inner),
-  // vector and scalar parts.
+  // Offsets of the groups moved at step j of a chunk (GPS*j ..; in: the chunk
+  // is inner), vector and scalar parts.
   struct Offs {
     unsigned v[WF_GPS], s[WF_GPS];
   };
   __device__ Offs offs(const WfArgs<V>& a, const WfGeo& q, const Base& b, int j, bool in) const {
     Offs o;
+    const int lx = j * WF_GPS / 4, g0 = j * WF_GPS % 4;
     if (in) {
-      const int us = wf_keep_s((b.u + j * b.gx) * (int)sizeof(V));
+      const int us = wf_keep_s((b.u + lx * b.gx) * (int)sizeof(V));
 #pragma unroll
       for (int g = 0; g < WF_GPS; ++g) {
         o.v[g] = vin;
-        o.s[g] = (unsigned)(us + g * b.gy * (int)sizeof(V));
+        o.s[g] = (unsigned)(us + (g0 + g) * b.gy * (int)sizeof(V));
       }
     } else {
-      const Step t = step(b, q, j);
+      const Step t = step(b, q, lx);
 #pragma unroll
       for (int g = 0; g < WF_GPS; ++g) {
-        o.v[g] = off_any(a, q, b, t, g);
+        o.v[g] = off_any(a, q, b, t, g0 + g);
         o.s[g] = 0u;
       }
     }
@@ -672,16 +698,16 @@ struct WfRuns {
   }
 };
 
-// ---- load role (wave 5): right-hand side, two chunks ahead --------------------
+// ---- load role: right-hand side, two chunks ahead --------------------
 template <int PAT, int DIR, class V>
 __device__ __forceinline__ void wf_load(const WfArgs<V>& a, const WfGeo& q, V* hbuf) {
   using RU = WfRuns<PAT, DIR, V>;
-  const int lane = threadIdx.x - 5 * 64;
+  const int lane = threadIdx.x - WF_NL - 64;
   RU R;
   R.init(a, q, lane);
   const auto rh = wf_rsrc(a.h + q.vb, q.vbytes);
   V reg[WF_GRP];
-  // Per step j of a chunk: the registers of groups 4j .. 4j+3 (a chunk's
+  // Per step j of a chunk: the registers of the step's groups (a chunk's
   // runs) go to the chunk buffer hb, then take the runs of chunk c.
   auto advance = [&](V* hb, int c, bool sync) {
     const typename RU::Base b = R.base(q, c);
@@ -727,11 +753,11 @@ __device__ __forceinline__ void wf_load(const WfArgs<V>& a, const WfGeo& q, V* h
   __syncthreads();
 }
 
-// ---- store role (wave 6): results, one chunk behind ---------------------------
+// ---- store role: results, one chunk behind ---------------------------
 template <int PAT, int DIR, class V>
 __device__ __forceinline__ void wf_store(const WfArgs<V>& a, const WfGeo& q, V* hbuf) {
   using RU = WfRuns<PAT, DIR, V>;
-  const int lane = threadIdx.x - 6 * 64;
+  const int lane = threadIdx.x - WF_NL - 128;
   RU R;
   R.init(a, q, lane);
   const auto rx = wf_rsrc(a.x + q.vb, q.vbytes);
@@ -756,7 +782,7 @@ __device__ __forceinline__ void wf_store(const WfArgs<V>& a, const WfGeo& q, V* 
   __syncthreads();
 }
 
-// ---- export role (wave 7): the columns other tiles read -----------------------
+// ---- export role: the columns other tiles read -----------------------
 // One step after a value is computed it goes to this sweep's strip buffer
 // (device-coherently); the other buffer's entry gets the sentinel for the next
 // sweep on the level.
@@ -765,27 +791,24 @@ __device__ __forceinline__ void wf_export(const WfArgs<V>& a, const WfGeo& q, un
                                           const V* ring) {
   using B = VBits<V>;
   constexpr int ES = wf_es(PAT);
-  const int e = threadIdx.x - 7 * 64;
+  const int e = threadIdx.x - WF_NL - 192;
   const bool role = e < ES;
   const int el = role ? wf_export_lane(DIR, q.sh, e) : 0;
   const long base = (long)tile * q.NS * ES + e;
-  auto step = [&](int k, int j) {
+  auto step = [&](int k) {
     if (role && k >= 0 && k < q.NS) {
       const long o = base + (long)wf_step<DIR>(q.NS, k) * ES;
-      wf_coherent_store(strip + o, ring[((j + WF_HIST) % WF_HIST) * WF_RW + el]);
+      wf_coherent_store(strip + o, ring[(k % WF_HIST) * WF_RW + el]);
       other[o] = B::val(B::sent);
     }
   };
   __syncthreads();  // prologue
-  for (int k0 = 0; k0 < q.nsteps; k0 += WF_HIST) {
-#pragma unroll
-    for (int j = 0; j < WF_HIST; ++j) {
-      step(k0 + j - 1, j - 1);
-      __syncthreads();
-    }
+  for (int k = 0; k < q.nsteps; ++k) {
+    step(k - 1);
+    __syncthreads();
   }
   __syncthreads();
-  step(q.nsteps - 1, WF_HIST - 1);
+  step(q.nsteps - 1);
   __syncthreads();
 }
 
@@ -804,22 +827,15 @@ __device__ inline void wf_zero_lds(WfLds<V>* L) {
   __syncthreads();
 }
 
-// The last workgroup to finish resets the ticket counters for the next launch
-// and switches the strip buffers of the grids swept (flip(), every thread).
-template <class Flip>
-__device__ inline void wf_retire(unsigned* ctr, Flip flip) {
-  __shared__ unsigned s_last;
-  if (threadIdx.x == 0) {
-    s_last = atomicAdd(&ctr[1], 1u) == gridDim.x - 1 ? 1u : 0u;
-    if (s_last) {
-      __hip_atomic_store(&ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&ctr[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-  __syncthreads();
-  if (s_last) flip();
-}
+// What a workgroup sweeps next: a tile of a grid and the grid's strip buffer
+// (0 or 1) of this sweep.
+template <class V>
+struct WfJob {
+  WfArgs<V> a;
+  unsigned tile, par;
+};
 
+// The next ticket, the same for every thread.
 __device__ inline unsigned wf_take_ticket(unsigned* ctr) {
   __shared__ unsigned s_ticket;
   if (threadIdx.x == 0) s_ticket = atomicAdd(&ctr[0], 1u);
@@ -831,80 +847,112 @@ __device__ inline unsigned wf_take_ticket(unsigned* ctr) {
 
 // Every role of a sweep workgroup runs its own loop over the workgroup's
 // tiles (values a role keeps across tiles then stay out of the other roles'
-// code); next(&a, &tile) takes the next ticket, the same for all waves.
+// code); next(&job) takes the next ticket, the same for all waves.
 template <int PAT, int DIR, int P, class E, bool UNITD, class Next>
 __device__ __forceinline__ void wf_roles(Next next, unsigned* err, WfLds<typename WfVal<E>::V>* L) {
   using V = typename WfVal<E>::V;
-  WfArgs<V> a;
-  unsigned tile;
+  WfJob<V> w;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
-  // this sweep's strip buffer and the one of the level's next sweep
+  // this sweep's strip buffer and the one of the grid's next sweep
   auto strip = [&](unsigned other) {
-    const unsigned par = __builtin_amdgcn_readfirstlane(*a.par) ^ other;
-    return a.strip + (par & 1u ? (long)a.t.ntx * a.t.nty * a.t.ns * wf_es(PAT) : 0l);
+    return w.a.strip + ((w.par ^ other) & 1u ? (long)w.a.t.ntx * w.a.t.nty * w.a.t.ns * wf_es(PAT) : 0l);
   };
-  if (wave < 4) {
-    while (next(&a, &tile)) wf_compute<PAT, DIR, P, E, UNITD>(a, wf_geo(a, tile), tile, L->ring, L->hbuf);
-  } else if (wave == 4) {
-    while (next(&a, &tile)) wf_halo<PAT, DIR, V>(a, wf_geo(a, tile), strip(0u), L->ring, err);
-  } else if (wave == 5) {
-    while (next(&a, &tile)) wf_load<PAT, DIR, V>(a, wf_geo(a, tile), L->hbuf);
-  } else if (wave == 6) {
-    while (next(&a, &tile)) wf_store<PAT, DIR, V>(a, wf_geo(a, tile), L->hbuf);
+  constexpr int CW = WF_NCW;
+  if (wave < CW) {
+    while (next(&w)) wf_compute<PAT, DIR, P, E, UNITD>(w.a, wf_geo(w.a, w.tile), w.tile, L->ring, L->hbuf);
+  } else if (wave == CW) {
+    while (next(&w)) wf_halo<PAT, DIR, V>(w.a, wf_geo(w.a, w.tile), strip(0u), L->ring, err);
+  } else if (wave == CW + 1) {
+    while (next(&w)) wf_load<PAT, DIR, V>(w.a, wf_geo(w.a, w.tile), L->hbuf);
+  } else if (wave == CW + 2) {
+    while (next(&w)) wf_store<PAT, DIR, V>(w.a, wf_geo(w.a, w.tile), L->hbuf);
   } else {
-    while (next(&a, &tile)) wf_export<PAT, DIR, V>(a, wf_geo(a, tile), tile, strip(0u), strip(1u), L->ring);
+    while (next(&w))
+      wf_export<PAT, DIR, V>(w.a, wf_geo(w.a, w.tile), w.tile, strip(0u), strip(1u), L->ring);
   }
 }
 
-// One sweep over one grid: persistent workgroups take tiles by ticket.
+// One sweep over one grid: persistent workgroups take tiles by ticket.  A
+// workgroup reads the buffer word before it takes its first ticket (the
+// ticket's operand depends on the word), so whoever holds the last ticket --
+// the last tile's if every workgroup has one tile, else the last one beyond
+// the tiles -- knows that all others have read it and have taken theirs, and
+// readies counter and buffer word for the next launch.
 template <int PAT, int DIR, int P, class E, bool UNITD>
 __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<E>::V> a) {
   using V = typename WfVal<E>::V;
   __shared__ WfLds<V> L;
-  wf_zero_lds(&L);
+  __shared__ unsigned s_first, s_par;
   const unsigned ntiles = (unsigned)(a.t.ntx * a.t.nty);
-  auto next = [&](WfArgs<V>* pa, unsigned* tile) {
-    const unsigned ticket = wf_take_ticket(a.ctr);
-    if (ticket >= ntiles) return false;
-    *pa = a;
-    *tile = DIR > 0 ? ticket : ntiles - 1u - ticket;
+  const bool single = ntiles <= gridDim.x;
+  auto reset = [&](unsigned par) {
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(&a.ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.par, par ^ 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  if (threadIdx.x == 0) {
+    const unsigned p = __hip_atomic_load(a.par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_par = p;
+    s_first = atomicAdd(&a.ctr[0], 1u + (p >> 31));
+  }
+  wf_zero_lds(&L);  // (ends with a barrier)
+  const unsigned first = __builtin_amdgcn_readfirstlane(s_first), par = __builtin_amdgcn_readfirstlane(s_par);
+  if (single && first == ntiles - 1u) reset(par);
+  bool started = false;
+  auto next = [&](WfJob<V>* w) {
+    if (started && single) return false;
+    const unsigned ticket = started ? wf_take_ticket(a.ctr) : first;
+    if (ticket >= ntiles) {  // (also a first ticket: of a workgroup that started after the others were done)
+      if (ticket == ntiles + gridDim.x - 1u) reset(par);
+      return false;
+    }
+    started = true;
+    w->a = a;
+    w->tile = DIR > 0 ? ticket : ntiles - 1u - ticket;
+    w->par = par;
     return true;
   };
   wf_roles<PAT, DIR, P, E, UNITD>(next, a.err, &L);
-  wf_retire(a.ctr, [&] {
-    if (threadIdx.x == 0) *a.par ^= 1u;
-  });
 }
 
 // One sweep over many independent grids of the same pattern and precision in
 // one launch.  Ticket k names entry tmap[k] = (segment << 20) | r: the r-th
 // tile of segment seg in that segment's own dependence order, so every
 // tile's producers hold smaller tickets whatever the merge of the segments.
+// The workgroup with the last ticket beyond the tiles (all others are done)
+// readies the counter and the swept grids' buffer words for the next launch.
+// (27-point FP64 keeps its deeper registers and one workgroup per CU.)
 template <int PAT, int DIR, int P, class E>
-__global__ __launch_bounds__(WF_THREADS) void k_wavefront_group(const WfArgs<typename WfVal<E>::V>* __restrict__ segs,
-                                                                int nseg, const unsigned* __restrict__ tmap,
-                                                                unsigned total, const int* __restrict__ live,
-                                                                unsigned* ctr, unsigned* err) {
+__global__ __launch_bounds__(WF_THREADS, PAT == 27 && sizeof(E) == 8 ? 2 : 3) void k_wavefront_group(
+    const WfArgs<typename WfVal<E>::V>* __restrict__ segs, int nseg, const unsigned* __restrict__ tmap, unsigned total,
+    const int* __restrict__ live, unsigned* ctr, unsigned* err) {
   using V = typename WfVal<E>::V;
   __shared__ WfLds<V> L;
   wf_zero_lds(&L);
-  auto next = [&](WfArgs<V>* pa, unsigned* tile) {
+  bool last = false;
+  auto next = [&](WfJob<V>* w) {
     for (;;) {
       const unsigned ticket = wf_take_ticket(ctr);
-      if (ticket >= total) return false;
+      if (ticket >= total) {
+        last = ticket == total + gridDim.x - 1u;
+        return false;
+      }
       const unsigned e = __builtin_amdgcn_readfirstlane(tmap[ticket]);
-      *pa = segs[e >> 20];
-      if (live != nullptr && live[pa->sys] == 0) continue;
-      const unsigned r = e & 0xFFFFFu, nt = (unsigned)(pa->t.ntx * pa->t.nty);
-      *tile = DIR > 0 ? r : nt - 1u - r;
+      w->a = segs[e >> 20];
+      if (live != nullptr && live[w->a.sys] == 0) continue;
+      const unsigned r = e & 0xFFFFFu, nt = (unsigned)(w->a.t.ntx * w->a.t.nty);
+      w->tile = DIR > 0 ? r : nt - 1u - r;
+      w->par = __builtin_amdgcn_readfirstlane(*w->a.par);
       return true;
     }
   };
   wf_roles<PAT, DIR, P, E, false>(next, err, &L);
-  wf_retire(ctr, [&] {
+  if (last) {
+    if (threadIdx.x == 0) __hip_atomic_store(&ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int k = threadIdx.x; k < nseg; k += WF_THREADS)
       if (live == nullptr || live[segs[k].sys] != 0) *segs[k].par ^= 1u;
-  });
+  }
 }
 
 // addout = addv + x (the correction step after an ILU(0) upper sweep)
@@ -1075,10 +1123,13 @@ static hipError_t launch_wfg_t(const WfArgs<typename WfVal<E>::V>* segs, int nse
 }
 
 // Coefficient prefetch distance (steps) per pattern and storage type: as deep
-// as the compute waves' registers allow (NPK 16-byte packs per step).
+// as regs registers hold (NPK 16-byte packs per step).  A launch of one grid
+// has one workgroup per CU (256 registers a lane); grouped launches have two
+// (168), which hide each other's waits: 256 systems of 16..96 points per axis
+// solve in 156 instead of 168 ms (FP32).
 template <int PAT, class E>
-constexpr int wf_prefetch() {
-  return wf_npk(PAT, sizeof(E)) * 4 * 16 <= 160 ? 16 : (wf_npk(PAT, sizeof(E)) * 4 * 8 <= 160 ? 8 : 4);
+constexpr int wf_prefetch(int regs = 160) {
+  return wf_npk(PAT, sizeof(E)) * 4 * 16 <= regs ? 16 : (wf_npk(PAT, sizeof(E)) * 4 * 8 <= regs ? 8 : 4);
 }
 
 template <class E>
@@ -1086,13 +1137,13 @@ hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<
                                   const unsigned* tmap, unsigned total, unsigned grid, const int* live, unsigned* ctr,
                                   unsigned* err, hipStream_t st) {
   if (total == 0) return hipSuccess;
-  if (grid == 0 || grid > total) grid = total;
-  if (grid > (unsigned)WF_MAX_GRID) grid = WF_MAX_GRID;
+  if (grid == 0 || grid > (unsigned)WF_MAX_GRID) grid = WF_MAX_GRID;
+  grid = 2 * grid < total ? 2 * grid : total;
 #define SMG_WFG_CASE(PATV)                                                                                       \
   if (pat == PATV && dir > 0)                                                                                    \
-    return launch_wfg_t<PATV, 1, wf_prefetch<PATV, E>(), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);         \
+    return launch_wfg_t<PATV, 1, wf_prefetch<PATV, E>(112), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);         \
   if (pat == PATV && dir < 0)                                                                                    \
-    return launch_wfg_t<PATV, -1, wf_prefetch<PATV, E>(), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);
+    return launch_wfg_t<PATV, -1, wf_prefetch<PATV, E>(112), E>(segs, nseg, tmap, total, grid, live, ctr, err, st);
   SMG_WFG_CASE(7)
   SMG_WFG_CASE(19)
   SMG_WFG_CASE(27)

@@ -1,0 +1,52 @@
+"""The tiled sweep at the sizes where its tiling can go wrong: grids that end
+inside, at and just past a tile (8 x 16 columns) and a chunk (16 steps), more
+tiles than the persistent grid has workgroups, every pattern, precision and
+direction, against the CPU oracle; bit-exact (the order of operations of every
+value is fixed).  Sweeps alternate in direction and repeat, so both strip
+buffers of the level are used."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2506_21932_amd as smg  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+SHAPES = [(8, 16, 64), (9, 17, 33), (7, 15, 40), (17, 33, 16), (16, 31, 15), (24, 48, 130), (25, 8, 161), (1, 70, 40),
+          (64, 1, 80), (130, 370, 9)]
+
+
+def _np(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("pat", [7, 19, 27])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_sweeps_bitexact(shape, pat, prec):
+    A = workloads.random_sgdia(shape, pat, seed=31)
+    H = oracle.Hierarchy(shape, pat, A, prec=prec)
+    mg = smg.StructMG(torch.from_numpy(A).to(DEV), shape, pattern=pat, prec=prec, device=DEV)
+    assert H.nlev >= 2
+    off = workloads.offsets(pat)
+    what, npt, dt = (0, np.float64, torch.float64) if prec == "fp64" else (5, np.float32, torch.float32)
+    Al, rd = H.level_data(0, what), H.level_data(0, what + 1).ravel()
+    g = workloads.rng(37)
+    for rep in range(3):
+        f = g.uniform(-1, 1, size=shape).astype(npt)
+        u = g.uniform(-1, 1, size=shape).astype(npt)
+        ft, ut = (torch.from_numpy(v).to(DEV) for v in (f, u))
+        got = _np(mg.op_presmooth(0, ft, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.gs_sweep(off, Al, rd, f, np.zeros(shape, npt), 1, 1).ravel()), rep
+        for _ in range(rep + 1):
+            got = _np(mg.op_postsmooth(0, ft, ut, None, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.gs_sweep(off, Al, rd, f, u, -1, 0).ravel()), rep
