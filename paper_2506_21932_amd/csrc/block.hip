@@ -9,20 +9,27 @@
 // block, over columns c in order, with fma.
 //
 // The block sweep follows the scalar wavefront design (csrc/wavefront.hip):
-// z-columns as lanes, sheared tiles in dependence order taken by atomic
-// ticket, per-lane skew with the 3d27 hyperplane weights (4, 2, 1), an LDS
-// ring for neighbour values plus a halo of other tiles' columns fetched
-// device-coherently and checked against a signalling-NaN sentinel.  A node
-// carries 3 values and needs 13 coefficient blocks and the inverse diagonal
-// block per step (126 numbers, ~1 KB in FP64): more memory operations than a
-// single wavefront may have in flight (63).  So a tile of 8 x 8 columns has
-// three wavefronts, wavefront r computing scalar row r of every node: it
-// loads only that row of the blocks (42 numbers), accumulates the row's sum
-// in the oracle's order, the three sums meet in LDS, and each wavefront
-// applies its row of the inverse diagonal block.
+// z-columns in sheared tiles taken by ticket in dependence order, per-column
+// skew with the 3d27 hyperplane weights (4, 2, 1), one barrier per step, an
+// LDS ring for neighbour values, strips of exported values between tiles, and
+// waves by role (compute, halo, load, store, export).  A node has 3 values and
+// needs 13 coefficient blocks and the inverse diagonal block per step (126
+// numbers, 1 KB in FP64).  So a tile is 4 x 8 columns, and a compute wave holds
+// 16 columns, four lanes each: lane r < 3 accumulates scalar row r (42
+// numbers, in the oracle's order), the three sums meet through quad
+// broadcasts, and each lane applies its row of the inverse.  A step is bound
+// by the chain of 39 dependent fmas (forward: 24 of them are two or more steps
+// old and summed one step early) and by the CU's own load rate (17 KB a step in
+// FP32, 32 KB in FP64); the values a step needs are read from LDS in batches
+// ahead of the chain.  Forward sweep before (8 x 8 tiles, a wave per scalar
+// row that also did the halo loads and all stores, two barriers per step) /
+// after, MI355X: 128^3 FP32 2300 / 600 us (its 1.06 GB of coefficients take
+// 226 us at the 4.7 TB/s of a large copy), 64^3 1010 / 271 us; 45x52x39 FP64
+// 820 / 343 us.
 #include "smg_common.h"
 #include "smg_group.h"
 #include "smg_kernels.h"
+#include "smg_sweep.h"
 
 namespace smg {
 
@@ -123,112 +130,106 @@ SMG_BINST(BMatH)
 #undef SMG_BINST
 
 // ------------------------------------------------------------ block sweep
-constexpr int BW_TX = 8, BW_TY = 8, BW_NL = 64;
-constexpr int BW_NH = 56;    // halo slots around an 8 x 8 tile
-constexpr int BW_HIST = 16;  // LDS ring rows (steps)
-constexpr int BW_PH = 4;     // prefetch distance (steps) of right-hand side and halo values
-constexpr int BW_UNROLL = 4;
+constexpr int BW_TX = 4, BW_TY = 8, BW_NL = BW_TX * BW_TY;  // columns per tile
+constexpr int BW_HIST = 16;                  // LDS ring rows (steps)
+constexpr int BW_CH = 16;                    // steps per chunk of right-hand side / results
+constexpr int BW_NB = 3;                     // chunk buffers: filled, computed, drained
+constexpr int BW_NH = 12 + 2 * BW_TX;        // halo slots (nodes) around a tile
+constexpr int BW_NCW = BW_NL / 16;           // compute waves, 16 columns each
+constexpr int BW_THREADS = 64 * (BW_NCW + 4);  // ... and a halo, a load, a store and an export wave
+constexpr int BW_RW = (BW_NL + BW_NH) * 4;   // ring row length (a node takes 4 entries)
+constexpr int BW_HRW = BW_NL * 4 + 1;        // chunk buffer row length (padded)
+constexpr int BW_GRP = BW_NL / 4;            // groups of 4 columns; a group's run of 16 steps is 3 x 64 values
+constexpr int BW_LPS = 2;                    // runs moved per step (the last are done before step 14)
+constexpr int BW_ES = 3 * (BW_TY + 2 * BW_TX);  // strip entries per step
+constexpr int BW_PH = 4;                     // halo prefetch distance (steps)
+constexpr int BW_AHEAD = BW_PH + 2;          // steps a stalled tile falls back behind its producer
 constexpr int BW_WX = 4, BW_WY = 2, BW_KB = 7;  // 3d27 hyperplane weights, largest lower step distance
-constexpr unsigned BW_SPIN_LIMIT = 1u << 21;
-constexpr unsigned BW_OOB = 0x80000000u;
-constexpr int BW_SC1 = 16;
+static_assert(3 * BW_NH <= 64 && BW_ES <= 64 && 3 * BW_GRP <= BW_LPS * (BW_CH - 2), "one wave per role");
 
-typedef unsigned bu32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned bu32x4 __attribute__((ext_vector_type(4)));
-
-void bwf_tiling(const Grid& g, WfTiling* t) {
+static void bw_tile(const Grid& g, WfTiling* t, int tx) {
   t->sh = g.ny <= BW_TY ? 0 : 1;
-  t->ntx = (g.nx + BW_TX - 1) / BW_TX;
-  t->nty = (g.ny + t->sh * (BW_TX - 1) + BW_TY - 1) / BW_TY;
-  t->ns = g.nz + (BW_WX - t->sh * BW_WY) * (BW_TX - 1) + BW_WY * (BW_TY - 1) + 2 * BW_KB;
-  t->nsk = (long)t->ntx * t->nty * t->ns * BW_NL;
+  t->ntx = (g.nx + tx - 1) / tx;
+  t->nty = (g.ny + t->sh * (tx - 1) + BW_TY - 1) / BW_TY;
+  t->ns = g.nz + (BW_WX - t->sh * BW_WY) * (tx - 1) + BW_WY * (BW_TY - 1) + 2 * BW_KB;
+  t->nsk = (long)t->ntx * t->nty * t->ns * tx * BW_TY;
 }
+void bwf_tiling(const Grid& g, WfTiling* t) { bw_tile(g, t, BW_TX); }
+long bwf_reserve(const Grid& g) {
+  WfTiling t;
+  bw_tile(g, &t, 8);
+  return t.nsk;
+}
+long bwf_strip_elems(const WfTiling& t) { return (long)t.ntx * t.nty * t.ns * BW_ES; }
 
-// Sweep data per node position and scalar row r (each of the tile's three
-// waves handles one row of every node): the row's 13 triangle blocks (3
+// Sweep data per node and scalar row r: the row's 13 triangle blocks (3
 // entries each, canonical order) then row r of the inverse diagonal block.
 // FP64: 42 doubles = 21 packs; FP32: 42 floats in 11 packs; FP16: 39 halves
 // (bytes 0..77), the FP32 row scale (byte 80) and the FP32 inverse row
-// (bytes 84..95) = 6 packs.  Layout [tile][step][row][pack][lane].
+// (bytes 84..95) = 6 packs.  Layout [tile][step][pack][column * 3 + r].
 __host__ __device__ constexpr int bwf_npr(int ebytes) { return ebytes == 8 ? 21 : (ebytes == 4 ? 11 : 6); }
-__host__ __device__ constexpr int bwf_npk(int ebytes) { return 3 * bwf_npr(ebytes); }
-int bwf_pack_count(int ebytes) { return bwf_npk(ebytes); }
+int bwf_pack_count(int ebytes) { return 3 * bwf_npr(ebytes); }
 
-__host__ __device__ constexpr int bw_col_dx(int c) { return c == 3 ? 0 : -1; }
-__host__ __device__ constexpr int bw_col_dy(int c) { return c == 3 ? -1 : c - 1; }
-__host__ __device__ constexpr int bw_col_of(int dx, int dy) { return dx == -1 ? dy + 1 : (dy == -1 ? 3 : -1); }
+// Term m of the triangle (canonical order): neighbour column (forward frame)
+// and step distance.
+__host__ __device__ constexpr int bw_off(int dir, int m, int axis) { return pat_off(27, dir > 0 ? m : 14 + m, axis); }
+__host__ __device__ constexpr int bw_back(int dir, int m) {
+  return dir * (BW_WX * bw_off(dir, m, 0) + BW_WY * bw_off(dir, m, 1) + bw_off(dir, m, 2));
+}
+// leading terms whose values are at least two steps old
+__host__ __device__ constexpr int bw_prefix(int dir) {
+  int n = 0;
+  while (n < 13 && bw_back(dir, n) <= -2) ++n;
+  return n;
+}
 
-__host__ __device__ constexpr int bwf_halo_slot(int qx, int qy) {
-  return qx == -1 ? qy + 2
-                  : (qx == BW_TX ? 14 + qy
-                                 : (qy < 0 ? 24 + 2 * qx + (qy + 2) : 40 + 2 * qx + (qy - BW_TY)));
+// Halo nodes, export entries: as in the scalar sweep (forward frame: the
+// column x-1 with y in [-2, TY+2), the row y = -1, a second row; the TY
+// columns lx = TX-1, the TX columns ly = TY-1, the TX columns of the second
+// row), three values each.
+__host__ __device__ constexpr int bw_halo_slot(int dir, int qx, int qy) {
+  const int fx = dir > 0 ? qx : BW_TX - 1 - qx, fy = dir > 0 ? qy : BW_TY - 1 - qy;
+  return fx < 0 ? fy + 2 : (fy == -1 ? 12 + fx : 12 + BW_TX + fx);
 }
-__device__ inline void bwf_halo_pos(int hs, int* qx, int* qy) {
-  if (hs < 12) {
-    *qx = -1;
-    *qy = hs - 2;
-  } else if (hs < 24) {
-    *qx = BW_TX;
-    *qy = hs - 14;
-  } else if (hs < 40) {
-    *qx = (hs - 24) / 2;
-    *qy = (hs - 24) % 2 - 2;
-  } else {
-    *qx = (hs - 40) / 2;
-    *qy = BW_TY + (hs - 40) % 2;
-  }
+__device__ inline void bw_halo_pos(int sh, int n, int* fx, int* fy) {
+  *fx = n < 12 ? -1 : (n < 12 + BW_TX ? n - 12 : n - 12 - BW_TX);
+  *fy = n < 12 ? n - 2 : (n < 12 + BW_TX ? -1 : (sh ? -2 : BW_TY));
 }
-__device__ inline bool bwf_halo_used(int dir, int sh, int qx, int qy) {
+// Is forward-frame node (fx, fy) a lower neighbour column of some lane?
+__device__ inline bool bw_halo_used(int sh, int fx, int fy) {
   for (int c = 0; c < 4; ++c) {
-    const int cx = dir * bw_col_dx(c), cy = dir * bw_col_dy(c);
-    const int lx = qx - cx, ly = qy - cy - sh * cx;
+    const int cx = c == 3 ? 0 : -1, cy = c == 3 ? -1 : c - 1;
+    const int lx = fx - cx, ly = fy - cy - sh * cx;
     if (lx >= 0 && lx < BW_TX && ly >= 0 && ly < BW_TY) return true;
   }
   return false;
 }
-__device__ inline bool bwf_exported(int dir, int lx, int ly, int sh) {
-  for (int c = 0; c < 4; ++c) {
-    const int cx = dir * bw_col_dx(c), cy = dir * bw_col_dy(c);
-    const int qx = lx - cx, qy = ly - cy - sh * cx;
-    if (qx < 0 || qx >= BW_TX || qy < 0 || qy >= BW_TY) return true;
+__device__ inline int bw_export_lane(int dir, int sh, int e) {
+  int lx = e < BW_TY ? BW_TX - 1 : (e - BW_TY) % BW_TX;
+  int ly = e < BW_TY ? e : (e < BW_TY + BW_TX ? BW_TY - 1 : (sh ? BW_TY - 2 : 0));
+  if (dir < 0) {
+    lx = BW_TX - 1 - lx;
+    ly = BW_TY - 1 - ly;
   }
-  return false;
-}
-
-__device__ inline __amdgpu_buffer_rsrc_t bw_rsrc(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <class V, int CP>
-__device__ inline V bw_ld(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  if constexpr (sizeof(V) == 8)
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, CP));
-  else
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, CP));
-}
-template <int CP, class V>
-__device__ inline void bw_st(V v, __amdgpu_buffer_rsrc_t r, unsigned off) {
-  if constexpr (sizeof(V) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(bu32x2, v), r, off, 0, CP);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, CP);
+  return lx * BW_TY + ly;
 }
 
 // entry e (0..41) of a row's sweep data held in packs p[]: e < 39 are the
 // triangle coefficients (block e / 3, column e % 3), e = 39 + c the inverse
 // row's column c
 template <class E>
-__device__ inline typename WfVal<E>::V bw_row(const bu32x4* p, int e);
+__device__ inline typename WfVal<E>::V bw_row(const u32x4* p, int e);
 template <>
-__device__ inline double bw_row<double>(const bu32x4* p, int e) {
-  const bu32x4 w = p[e / 2];
-  return e % 2 == 0 ? __builtin_bit_cast(double, bu32x2{w.x, w.y}) : __builtin_bit_cast(double, bu32x2{w.z, w.w});
+__device__ inline double bw_row<double>(const u32x4* p, int e) {
+  const u32x4 w = p[e / 2];
+  return e % 2 == 0 ? __builtin_bit_cast(double, u32x2{w.x, w.y}) : __builtin_bit_cast(double, u32x2{w.z, w.w});
 }
 template <>
-__device__ inline float bw_row<float>(const bu32x4* p, int e) {
+__device__ inline float bw_row<float>(const u32x4* p, int e) {
   return __uint_as_float(p[e / 4][e % 4]);
 }
 template <>
-__device__ inline float bw_row<__half>(const bu32x4* p, int e) {
+__device__ inline float bw_row<__half>(const u32x4* p, int e) {
   if (e >= 39) return __uint_as_float(p[(84 + 4 * (e - 39)) / 16][((84 + 4 * (e - 39)) % 16) / 4]);
   // row scale (byte 80) times the half, rounded once
   const unsigned w = p[e / 8][(e % 8) / 2];
@@ -236,189 +237,435 @@ __device__ inline float bw_row<__half>(const bu32x4* p, int e) {
   return e % 2 == 0 ? half_times<0>(w, sc) : half_times<1>(w, sc);
 }
 
-constexpr int BW_NT = 3 * BW_NL;  // threads: one wave per scalar row
+// v of lane 4 * (lane / 4) + R (quad broadcast)
+template <int R>
+__device__ inline float bw_quad(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
+}
+template <int R>
+__device__ inline double bw_quad(double v) {
+  const u32x2 w = __builtin_bit_cast(u32x2, v);
+  return __builtin_bit_cast(
+      double, u32x2{(unsigned)__builtin_amdgcn_mov_dpp((int)w.x, R * 0x55, 0xf, 0xf, true),
+                    (unsigned)__builtin_amdgcn_mov_dpp((int)w.y, R * 0x55, 0xf, 0xf, true)});
+}
 
-template <int DIR, class E>
-__global__ __launch_bounds__(BW_NT) void k_bwavefront(WfArgs<typename WfVal<E>::V> a) {
+struct BwGeo {
+  int X, Y, sh, NS, nsteps, p0;
+  unsigned vbytes;  // bytes of the vector buffers (planes p0 .. p1-1)
+  long vb;          // element offset of plane p0
+  bool full;        // every column of the tile lies in the grid
+};
+template <class V>
+__device__ inline BwGeo bw_geo(const WfArgs<V>& a, unsigned tile) {
+  BwGeo q;
+  q.X = (int)(tile / (unsigned)a.t.nty);
+  q.Y = (int)(tile % (unsigned)a.t.nty);
+  q.sh = a.t.sh;
+  q.NS = a.t.ns;
+  q.nsteps = (q.NS + BW_CH - 1) / BW_CH * BW_CH;
+  q.p0 = q.X * BW_TX > 0 ? q.X * BW_TX - 1 : 0;
+  const int p1 = q.X * BW_TX + BW_TX + 1 < a.g.nx ? q.X * BW_TX + BW_TX + 1 : a.g.nx;
+  const long pl = 3l * a.g.ny * a.g.nz;
+  q.vbytes = (unsigned)((p1 - q.p0) * pl * (long)sizeof(V));
+  q.vb = q.p0 * pl;
+  const int y0 = q.Y * BW_TY;
+  q.full = q.X * BW_TX + BW_TX <= a.g.nx && y0 - q.sh * (BW_TX - 1) >= 0 && y0 + BW_TY <= a.g.ny;
+  return q;
+}
+template <int DIR>
+__device__ inline int bw_step(int NS, int k) {
+  return DIR > 0 ? k : NS - 1 - k;
+}
+
+// ---- compute role (the first two waves): lane 4 * column + r computes scalar
+// row r of its column's node (r = 3 idles); a node's three row sums meet
+// through quad broadcasts
+template <int DIR, int P, class E>
+__device__ __forceinline__ void bw_compute(const WfArgs<typename WfVal<E>::V>& a, const BwGeo& q, unsigned tile,
+                                           typename WfVal<E>::V* ring, typename WfVal<E>::V* hbuf) {
   using V = typename WfVal<E>::V;
-  using B = VBits<V>;
-  constexpr int NPR = bwf_npr(sizeof(E)), NPK = bwf_npk(sizeof(E));
-  constexpr int P = sizeof(E) == 2 ? 4 : 2;  // steps of row data fetched ahead
-  static_assert(BW_UNROLL % P == 0 && BW_UNROLL % BW_PH == 0, "unroll");
-  constexpr int RW = (BW_NL + BW_NH) * 3 + 1;
-  constexpr unsigned PACKB = BW_NL * 16u;
-  constexpr int VS = (int)sizeof(V);
-  __shared__ V ring[BW_HIST * RW];
-  __shared__ V tx[3 * BW_NL];  // the three rows' sums of the current step
-  __shared__ unsigned s_ticket;
-
-  const int tid = threadIdx.x;
-  const int r = tid / BW_NL;    // scalar row of this wave
-  const int lane = tid % BW_NL;  // column of the tile
-  const int lx = lane / BW_TY, ly = lane % BW_TY;
-  const int sh = a.t.sh;
-  const int skew = (BW_WX - sh * BW_WY) * lx + BW_WY * ly + BW_KB;
-  const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
-  const int NS = a.t.ns;
-  const unsigned ntiles = (unsigned)(a.t.ntx * a.t.nty);
-  const bool exported = bwf_exported(DIR, lx, ly, sh);
-  const bool exp_next = a.next != nullptr && bwf_exported(a.next_dir, lx, ly, sh);
-  int nidx[4];
+  constexpr int NPR = bwf_npr(sizeof(E)), K = 16 / (int)sizeof(E);
+  constexpr int NPRE = bw_prefix(DIR), PPRE = 3 * NPRE / K;  // prefix terms, and the packs they fill
+  constexpr int BATCH = sizeof(V) == 8 ? 4 : 13;  // nodes whose values are read ahead
+  constexpr unsigned PACKB = 3 * BW_NL * 16u;
+  static_assert(BW_HIST % P == 0 && BW_HIST > BW_KB + 1 && 3 * NPRE % K == 0, "prefetch");
+  const int col = threadIdx.x / 4, r = threadIdx.x % 4;
+  const int lx = col / BW_TY, ly = col % BW_TY;
+  const int NS = q.NS;
+  int nidx[4];  // ring index of each neighbour column's node
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int cx = DIR * bw_col_dx(c), cy = DIR * bw_col_dy(c);
-    const int qx = lx + cx, qy = ly + cy + sh * cx;
+    const int cx = c == 3 ? 0 : -DIR, cy = c == 3 ? -DIR : DIR * (c - 1);
+    const int qx = lx + cx, qy = ly + cy + q.sh * cx;
     const bool in = qx >= 0 && qx < BW_TX && qy >= 0 && qy < BW_TY;
-    nidx[c] = in ? qx * BW_TY + qy : BW_NL + bwf_halo_slot(qx, qy);
+    nidx[c] = 4 * (in ? qx * BW_TY + qy : BW_NL + bw_halo_slot(DIR, qx, qy));
   }
-  // halo loading: lane hs of wave r loads component r of halo slot hs
-  const int hs = lane;
-  int hqx = 0, hqy = 0;
-  bool hrole = false;
-  if (hs < BW_NH) {
-    bwf_halo_pos(hs, &hqx, &hqy);
-    hrole = bwf_halo_used(DIR, sh, hqx, hqy);
+  const unsigned tbytes = (unsigned)NS * NPR * PACKB;
+  const auto rp = wf_rsrc((const char*)a.pk + (size_t)tile * tbytes, tbytes);
+  const int skew = (BW_WX - q.sh * BW_WY) * lx + BW_WY * ly + BW_KB;
+  const int xt = q.X * BW_TX + lx, yt = q.Y * BW_TY + ly - q.sh * lx;
+  const unsigned zlim = xt < a.g.nx && yt >= 0 && yt < a.g.ny ? (unsigned)a.g.nz : 0u;
+  const unsigned lo = r < 3 ? (unsigned)(col * 3 + r) * 16u : WF_OOB;
+  auto is_point = [&](int k) { return (unsigned)(bw_step<DIR>(NS, k) - skew) < zlim; };
+  // packs of step k into slot j (positions without a point read as zero
+  // without a memory access)
+  u32x4 cf[P][NPR];
+  struct Po {
+    unsigned so, vo;
+  };
+  auto pack_off = [&](int k) {
+    const int s = bw_step<DIR>(NS, k);
+    return Po{s >= 0 && s < NS ? (unsigned)s * (NPR * PACKB) : WF_OOB, is_point(k) ? lo : WF_OOB};
+  };
+  auto pack_load = [&](const Po& o, int j, int p) {
+    cf[j][p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, o.vo, o.so + p * PACKB, 0));
+  };
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    // (step 0 has no points: its prefix is skipped, so slot 0 starts with the
+    // prefix packs of step P)
+    const Po o = pack_off(j), on = pack_off(j + P);
+#pragma unroll
+    for (int p = 0; p < NPR; ++p) pack_load(j == 0 && p < PPRE ? on : o, j, p);
   }
-  const int hskew = (BW_WX - sh * BW_WY) * hqx + BW_WY * hqy + BW_KB;
+  const int me = col * 4 + r;
+  V own = V(0), tp;
+  __syncthreads();  // prologue: the first chunk is in LDS
+  tp = hbuf[me];
 
-  for (;;) {
-    if (tid == 0) s_ticket = atomicAdd(&a.ctr[0], 1u);
-    __syncthreads();
-    const unsigned ticket = s_ticket;
-    __syncthreads();
-    if (ticket >= ntiles) break;
-    const unsigned tile = DIR > 0 ? ticket : ntiles - 1u - ticket;
-    const int X = (int)(tile / (unsigned)a.t.nty), Y = (int)(tile % (unsigned)a.t.nty);
-    const int xt = X * BW_TX + lx, yt = Y * BW_TY + ly - sh * lx;
-    const bool colv = xt < nx && yt >= 0 && yt < ny;
-    const int p0 = X * BW_TX > 0 ? X * BW_TX - 1 : 0;
-    const int p1 = X * BW_TX + BW_TX + 1 < nx ? X * BW_TX + BW_TX + 1 : nx;
-    const long pl = (long)ny * nz;
-    const unsigned vbytes = (unsigned)((p1 - p0) * pl * 3 * (long)VS);
-    const long vb = p0 * pl * 3;
-    const auto rh = bw_rsrc(a.h + vb, vbytes);
-    const auto rx = bw_rsrc(a.x + vb, vbytes);
-    const auto rn = bw_rsrc((a.next != nullptr ? a.next : a.x) + vb, a.next != nullptr ? vbytes : 0u);
-    const unsigned vo = colv ? (unsigned)(((xt - p0) * (long)ny + yt) * nz) : 0u;
-    const int gx = X * BW_TX + hqx, gy = Y * BW_TY + hqy - sh * hqx;
-    const bool hcolv = hrole && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    const unsigned hvo = hcolv ? (unsigned)(((gx - p0) * (long)ny + gy) * nz) : 0u;
-    const unsigned tbytes = (unsigned)NS * NPK * PACKB;
-    const auto rp = bw_rsrc((const char*)a.pk + (size_t)tile * tbytes, tbytes);
-    const int nsteps = (NS + BW_UNROLL - 1) / BW_UNROLL * BW_UNROLL;
-
-    auto step_of = [&](int k) { return DIR > 0 ? k : NS - 1 - k; };
-    // byte offset of component r of the node of this lane at iteration k
-    auto node_off = [&](int k) {
-      const int z = step_of(k) - skew;
-      return colv && z >= 0 && z < nz ? ((vo + (unsigned)z) * 3u + (unsigned)r) * (unsigned)VS : BW_OOB;
-    };
-    auto halo_off = [&](int k) {
-      const int s = step_of(k);
-      const int hz = s - hskew;
-      return s >= 0 && s < NS && hcolv && hz >= 0 && hz < nz ? ((hvo + (unsigned)hz) * 3u + (unsigned)r) * (unsigned)VS
-                                                             : BW_OOB;
-    };
-    // this row's sweep data of iteration k
-    bu32x4 cf[P][NPR];
-    auto row_fetch = [&](int k, int j) {
-      const int s = step_of(k);
-      const unsigned so = s >= 0 && s < NS ? ((unsigned)s * 3u + (unsigned)r) * (NPR * PACKB) : BW_OOB;
+  for (int k0 = 0; k0 < q.nsteps; k0 += BW_HIST) {
+    V* hb = hbuf + ((k0 / BW_CH) % BW_NB) * (BW_CH * BW_HRW) + me;
+    const V* hbn = hbuf + ((k0 / BW_CH + 1) % BW_NB) * (BW_CH * BW_HRW) + me;
 #pragma unroll
-      for (int p = 0; p < NPR; ++p)
-        cf[j][p] =
-            __builtin_bit_cast(bu32x4, __builtin_amdgcn_raw_buffer_load_b128(rp, lane * 16u, so + p * PACKB, 0));
-    };
-    V hv[BW_PH], hb[BW_PH];
-    auto h_fetch = [&](int k, int j) { hv[j] = bw_ld<V, 0>(rh, node_off(k)); };
-    auto halo_fetch = [&](int k, int j) { hb[j] = bw_ld<V, BW_SC1>(rx, halo_off(k)); };
-    auto halo_put = [&](int k, int j) {
-      const unsigned off = halo_off(k);
-      V v = hb[j];
-      if (off != BW_OOB && B::bits(v) == B::sent) {
-        unsigned spins = 0;
-        do {
-          __builtin_amdgcn_s_sleep(1);
-          v = bw_ld<V, BW_SC1>(rx, off);
-          // once any wait has timed out, stop waiting anywhere
-          if ((spins & 1023u) == 1023u && (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-            spins = BW_SPIN_LIMIT;
-        } while (B::bits(v) == B::sent && ++spins < BW_SPIN_LIMIT);
-        if (spins >= BW_SPIN_LIMIT) atomicOr(a.err, 1u);
-      }
-      if (hrole) ring[(k % BW_HIST) * RW + (BW_NL + hs) * 3 + r] = off != BW_OOB ? v : V(0);
-    };
-
+    for (int j = 0; j < BW_HIST; ++j) {
+      const int jp = j % P, jn = (j + 1) % P, k = k0 + j;
+      V u[13][3];
+      // the values of terms m0 .. m0 + BATCH - 1 of a step; all reads are
+      // issued before the first use
+      auto values = [&](int m0, int m1, int step) {
 #pragma unroll
-    for (int j = 0; j < P; ++j) row_fetch(j, j);
-#pragma unroll
-    for (int j = 0; j < BW_PH; ++j) {
-      h_fetch(j, j);
-      halo_fetch(j, j);
-    }
-    halo_put(0, 0);
-    __syncthreads();
-
-    for (int k0 = 0; k0 < nsteps; k0 += BW_UNROLL) {
-#pragma unroll
-      for (int j = 0; j < BW_UNROLL; ++j) {
-        const int k = k0 + j;
-        const int jh = j % BW_PH, jc = j % P;
-        // this row's sum over the 13 triangle blocks, canonical order,
-        // columns in order: t = h_r - sum A[m][r][c] u_m[c]
-        V t = hv[jh];
-#pragma unroll
-        for (int m = 0; m < 13; ++m) {
-          const int so = DIR > 0 ? m : 14 + m;
-          const int dx = pat_off(27, so, 0), dy = pat_off(27, so, 1), dz = pat_off(27, so, 2);
-          const V* rr;
-          if (dx == 0 && dy == 0) {
-            rr = ring + ((k - 1 + BW_HIST) % BW_HIST) * RW + lane * 3;  // this column, previous step
+        for (int m = m0; m < m0 + BATCH && m < m1; ++m) {
+          if (bw_off(DIR, m, 0) == 0 && bw_off(DIR, m, 1) == 0) {
+            u[m][0] = bw_quad<0>(own);
+            u[m][1] = bw_quad<1>(own);
+            u[m][2] = bw_quad<2>(own);
           } else {
-            const int c = bw_col_of(DIR * dx, DIR * dy);
-            const int back = DIR * (BW_WX * dx + BW_WY * dy + dz);  // in [-KB, -1]
-            rr = ring + ((k + back + BW_HIST) % BW_HIST) * RW + nidx[c] * 3;
+            const int c = bw_off(DIR, m, 0) != 0 ? DIR * bw_off(DIR, m, 1) + 1 : 3;
+            const V* n = ring + ((step + bw_back(DIR, m) + BW_HIST) % BW_HIST) * BW_RW + nidx[c];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) u[m][i] = n[i];
           }
-          const V u0 = rr[0], u1 = rr[1], u2 = rr[2];
-          t = fma(-bw_row<E>(cf[jc], 3 * m + 0), u0, t);
-          t = fma(-bw_row<E>(cf[jc], 3 * m + 1), u1, t);
-          t = fma(-bw_row<E>(cf[jc], 3 * m + 2), u2, t);
         }
-        tx[r * BW_NL + lane] = t;
-        __syncthreads();
-        const V t0 = tx[lane], t1 = tx[BW_NL + lane], t2 = tx[2 * BW_NL + lane];
-        const V xv = fma(bw_row<E>(cf[jc], 41), t2, fma(bw_row<E>(cf[jc], 40), t1, bw_row<E>(cf[jc], 39) * t0));
-        const unsigned off = node_off(k);
-        const bool act = off != BW_OOB;
-        ring[(k % BW_HIST) * RW + lane * 3 + r] = act ? xv : V(0);
-        bw_st<BW_SC1>(xv, rx, exported ? off : BW_OOB);
-        bw_st<0>(xv, rx, exported ? BW_OOB : off);
-        if (exp_next) bw_st<0>(B::val(B::sent), rn, off);
-        halo_put(k + 1, (j + 1) % BW_PH);
-        halo_fetch(k + BW_PH, jh);
-        h_fetch(k + BW_PH, jh);
-        row_fetch(k + P, jc);
-        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // t -= A_m u_m with the packs of slot
+      auto term = [&](V t, int m, int slot) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) t = fma(-bw_row<E>(cf[slot], 3 * m + i), u[m][i], t);
+        return t;
+      };
+      V t = tp;
+      values(NPRE, 13, j);
+#pragma unroll
+      for (int m = NPRE; m < 13; ++m) {
+        if ((m - NPRE) % BATCH == 0 && m + BATCH < 13) values(m + BATCH, 13, j);
+        t = term(t, m, jp);
       }
+      // row r of the inverse diagonal block times the node's three sums
+      const V t0 = bw_quad<0>(t), t1 = bw_quad<1>(t), t2 = bw_quad<2>(t);
+      const V xv = fma(bw_row<E>(cf[jp], 41), t2, fma(bw_row<E>(cf[jp], 40), t1, bw_row<E>(cf[jp], 39) * t0));
+      own = is_point(k) ? xv : V(0);
+      // (the last FP32 pack's unused words stay live until here, so that no
+      // temporary waits for a load in flight)
+      if constexpr (sizeof(E) == 4) asm volatile("" : : "v"(cf[jp][NPR - 1]));
+      ring[j * BW_RW + me] = own;
+      hb[j * BW_HRW] = own;
+      __builtin_amdgcn_sched_barrier(0);
+      // refill the packs used for the last time, then sum the next step's
+      // prefix (its values are in the ring already)
+      const Po po = pack_off(k + P), pn = pack_off(k + 1 + P);
+#pragma unroll
+      for (int p = PPRE; p < NPR; ++p) pack_load(po, jp, p);
+      tp = j + 1 < BW_HIST ? hb[(j + 1) * BW_HRW] : hbn[0];
+      if (NPRE > 0) values(0, NPRE, j + 1);
+#pragma unroll
+      for (int m = 0; m < NPRE; ++m) {
+        if (m % BATCH == 0 && m + BATCH < NPRE) values(m + BATCH, NPRE, j + 1);
+        tp = term(tp, m, jn);
+#pragma unroll
+        for (int p = 3 * m / K; p < 3 * (m + 1) / K; ++p) {
+          __builtin_amdgcn_sched_barrier(0);
+          pack_load(pn, jn, p);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
     }
   }
-  if (tid == 0) {
-    unsigned o = atomicAdd(&a.ctr[1], 1u);
-    if (o == gridDim.x - 1) {
-      __hip_atomic_store(&a.ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&a.ctr[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();  // tail: the last chunk is drained and the last step exported
+  __syncthreads();
+}
+
+// ---- halo role: lane 3 n + c brings component c of halo node n from the
+// producing tile's strip into the ring (see the scalar sweep)
+template <int DIR, class V>
+__device__ __forceinline__ void bw_halo(const WfArgs<V>& a, const BwGeo& q, const V* strip, V* ring, unsigned* err) {
+  using B = VBits<V>;
+  constexpr int PH = BW_PH;
+  static_assert(BW_CH % PH == 0, "halo prefetch distance");
+  const int t = threadIdx.x - 64 * BW_NCW;
+  const int NS = q.NS;
+  int fx = 0, fy = 0;
+  bool role = false;
+  if (t < 3 * BW_NH) {
+    bw_halo_pos(q.sh, t / 3, &fx, &fy);
+    role = bw_halo_used(q.sh, fx, fy);
+  }
+  const int ax = fx < 0 ? 1 : 0;
+  const int fyt = fy + (ax ? BW_TX * q.sh : 0) + 2 * BW_TY;  // >= 0
+  const int dyf = fyt / BW_TY - 2, lyf = fyt % BW_TY, lxf = ax ? BW_TX - 1 : fx;
+  const int PX = q.X - DIR * ax, PY = q.Y + DIR * dyf;
+  const bool have = role && PX >= 0 && PX < a.t.ntx && PY >= 0 && PY < a.t.nty;
+  const int dk = DIR * (BW_WX * BW_TX * ax - BW_WY * BW_TY * dyf);
+  const int e = lxf == BW_TX - 1 ? lyf : (lyf == BW_TY - 1 ? BW_TY + lxf : BW_TY + BW_TX + lxf);
+  const V* hp = have ? strip + (((long)PX * a.t.nty + PY) * NS) * BW_ES + 3 * e + t % 3 : strip;
+  const int es = have ? BW_ES : 0;
+  const int slot = 4 * (BW_NL + t / 3) + t % 3;
+  auto valid = [&](int k) {
+    const int s = bw_step<DIR>(NS, k), sp = s + dk;
+    return have && s >= 0 && s < NS && sp >= 0 && sp < NS;
+  };
+  auto fetch = [&](int k) {
+    int sp = bw_step<DIR>(NS, k) + dk;
+    sp = sp < 0 ? 0 : (sp >= NS ? NS - 1 : sp);
+    return wf_coherent_load(hp + (long)sp * es);
+  };
+  V hb[PH];
+  auto put = [&](int k, int j) {
+    const bool ok = valid(k);
+    if (__builtin_amdgcn_ballot_w64(ok && B::bits(hb[j]) == B::sent) != 0) {
+      unsigned spins = 0;
+      for (;;) {
+        const V far = fetch(k + BW_AHEAD);
+#pragma unroll
+        for (int d = 0; d < PH; ++d) hb[(j + d) % PH] = fetch(k + d);
+        const bool miss = (ok && B::bits(hb[j]) == B::sent) || (have && B::bits(far) == B::sent);
+        if (__builtin_amdgcn_ballot_w64(miss) == 0) break;
+        if (++spins >= WF_SPIN_LIMIT) {
+          atomicOr(err, 1u);
+          break;
+        }
+        // once any wait has timed out, stop waiting anywhere
+        if ((spins & 1023u) == 1023u && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u)) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
     }
+    if (role) ring[(k % BW_HIST) * BW_RW + slot] = ok ? hb[j] : V(0);
+  };
+#pragma unroll
+  for (int j = 0; j < PH; ++j) hb[j] = fetch(j);
+  __syncthreads();  // prologue
+  for (int k0 = 0; k0 < q.nsteps; k0 += PH) {
+#pragma unroll
+    for (int j = 0; j < PH; ++j) {
+      put(k0 + j, j);
+      hb[j] = fetch(k0 + j + PH);
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  __syncthreads();
+}
+
+// ---- column runs (load and store roles).  A chunk's 16 steps of a column are
+// 48 consecutive values; run 3 g + i moves values 64 i .. 64 i + 63 of the
+// four columns of group g (lx = g / 2, ly = 4 (g % 2) ..).
+template <int DIR, class V>
+struct BwRuns {
+  int cq[3], zo[3], lds[3];  // column in the group, point in the column's run, LDS index
+  unsigned vin[3];           // inner chunks: lane part of the byte offset
+  int off[3];                // value in the column's run
+  __device__ void init(const WfArgs<V>& a, int lane) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int e = 64 * i + lane;
+      cq[i] = e / 48;
+      off[i] = e % 48;
+      zo[i] = off[i] / 3;
+      lds[i] = (DIR > 0 ? zo[i] : BW_CH - 1 - zo[i]) * BW_HRW + 4 * cq[i] + off[i] % 3;
+      vin[i] = (unsigned)(cq[i] * (a.g.nz - BW_WY) * 3 + off[i]) * (unsigned)sizeof(V);
+    }
+  }
+  // lowest step of chunk c
+  __device__ static int low(const BwGeo& q, int c) {
+    return DIR > 0 ? c * BW_CH : q.NS - BW_CH - c * BW_CH;
+  }
+  // is every position of chunk c a point?
+  __device__ static bool inner(const WfArgs<V>& a, const BwGeo& q, int c) {
+    const int lo = low(q, c), sx = BW_WX - q.sh * BW_WY;
+    return q.full && lo >= BW_KB + sx * (BW_TX - 1) + BW_WY * (BW_TY - 1) && lo + BW_CH - 1 - BW_KB < a.g.nz;
+  }
+  // offsets (vector and scalar part) of run 3 g + i of chunk c
+  __device__ void offset(const WfArgs<V>& a, const BwGeo& q, int c, bool in, int g, int i, unsigned* vo,
+                         unsigned* so) const {
+    const int lx = g / 2, y0 = 4 * (g % 2), sx = BW_WX - q.sh * BW_WY;
+    const int lo = wf_keep_s(low(q, c)) - BW_KB - sx * lx - BW_WY * y0;  // z of the group's first column
+    const int row = (q.X * BW_TX - q.p0 + lx) * a.g.ny + q.Y * BW_TY + y0 - q.sh * lx;
+    if (in) {
+      *vo = vin[i];
+      *so = (unsigned)((row * a.g.nz + lo) * 3) * (unsigned)sizeof(V);
+    } else {
+      const int y = q.Y * BW_TY + y0 + cq[i] - q.sh * lx, z = lo - BW_WY * cq[i] + zo[i];
+      const bool ok = q.X * BW_TX + lx < a.g.nx && (unsigned)y < (unsigned)a.g.ny && (unsigned)z < (unsigned)a.g.nz;
+      const int e = ((row + cq[i]) * a.g.nz + lo - BW_WY * cq[i]) * 3 + off[i];
+      *vo = ok ? (unsigned)e * (unsigned)sizeof(V) : WF_OOB;
+      *so = 0u;
+    }
+  }
+};
+
+// ---- load role: right-hand side, two chunks ahead
+template <int DIR, class V>
+__device__ __forceinline__ void bw_load(const WfArgs<V>& a, const BwGeo& q, V* hbuf) {
+  constexpr int NR = 3 * BW_GRP;
+  BwRuns<DIR, V> R;
+  R.init(a, threadIdx.x - 64 * (BW_NCW + 1));
+  const auto rh = wf_rsrc(a.h + q.vb, q.vbytes);
+  V reg[NR];
+  // per step two runs: registers to the chunk buffer hb, then the runs of chunk c
+  auto advance = [&](V* hb, int c, bool put, bool sync) {
+    const bool in = R.inner(a, q, c);
+#pragma unroll
+    for (int j = 0; j < BW_CH; ++j) {
+#pragma unroll
+      for (int i = BW_LPS * j; i < BW_LPS * (j + 1); ++i) {
+        if (i >= NR) break;
+        if (put) hb[R.lds[i % 3] + 16 * (i / 3)] = reg[i];
+        unsigned vo, so;
+        R.offset(a, q, c, in, i / 3, i % 3, &vo, &so);
+        reg[i] = bld<V, 0>(rh, vo, so);
+      }
+      if (sync)
+        __syncthreads();
+      else
+        __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // prologue: chunk 0 into buffer 0, chunk 1 into the registers
+  advance(hbuf, 0, false, false);
+  advance(hbuf, 1, true, false);
+  __syncthreads();
+  for (int c = 0; c < q.nsteps / BW_CH; ++c) advance(hbuf + ((c + 1) % BW_NB) * (BW_CH * BW_HRW), c + 2, true, true);
+  __syncthreads();
+  __syncthreads();
+}
+
+// ---- store role: results, one chunk behind
+template <int DIR, class V>
+__device__ __forceinline__ void bw_store(const WfArgs<V>& a, const BwGeo& q, const V* hbuf) {
+  constexpr int NR = 3 * BW_GRP;
+  BwRuns<DIR, V> R;
+  R.init(a, threadIdx.x - 64 * (BW_NCW + 2));
+  const auto rx = wf_rsrc(a.x + q.vb, q.vbytes);
+  auto chunk = [&](int c, bool sync) {
+    const V* hb = hbuf + (c % BW_NB) * (BW_CH * BW_HRW);
+    const bool in = R.inner(a, q, c);
+#pragma unroll
+    for (int j = 0; j < BW_CH; ++j) {
+#pragma unroll
+      for (int i = BW_LPS * j; i < BW_LPS * (j + 1); ++i) {
+        if (i >= NR) break;
+        unsigned vo, so;
+        R.offset(a, q, c, in, i / 3, i % 3, &vo, &so);
+        bst<0>(hb[R.lds[i % 3] + 16 * (i / 3)], rx, vo, so);
+      }
+      if (sync) __syncthreads();
+    }
+  };
+  __syncthreads();  // prologue
+#pragma unroll 1
+  for (int j = 0; j < BW_CH; ++j) __syncthreads();
+  for (int c = 1; c < q.nsteps / BW_CH; ++c) chunk(c - 1, true);
+  __syncthreads();
+  chunk(q.nsteps / BW_CH - 1, false);
+  __syncthreads();
+}
+
+// ---- export role: one step after a node is computed its values go to this
+// sweep's strip buffer, and the other buffer's entries get the sentinel
+template <int DIR, class V>
+__device__ __forceinline__ void bw_export(const WfArgs<V>& a, const BwGeo& q, unsigned tile, V* strip, V* other,
+                                          const V* ring) {
+  using B = VBits<V>;
+  const int e = threadIdx.x - 64 * (BW_NCW + 3);
+  const bool role = e < BW_ES;
+  const int el = role ? 4 * bw_export_lane(DIR, q.sh, e / 3) + e % 3 : 0;
+  const long base = (long)tile * q.NS * BW_ES + e;
+  auto step = [&](int k) {
+    if (role && k >= 0 && k < q.NS) {
+      const long o = base + (long)bw_step<DIR>(q.NS, k) * BW_ES;
+      wf_coherent_store(strip + o, ring[(k % BW_HIST) * BW_RW + el]);
+      other[o] = B::val(B::sent);
+    }
+  };
+  __syncthreads();  // prologue
+  for (int k = 0; k < q.nsteps; ++k) {
+    step(k - 1);
+    __syncthreads();
+  }
+  __syncthreads();
+  step(q.nsteps - 1);
+  __syncthreads();
+}
+
+template <class V>
+struct alignas(16) BwLds {
+  V ring[BW_HIST * BW_RW];
+  V hbuf[BW_NB * BW_CH * BW_HRW];
+};
+
+template <int DIR, int P, class E>
+__global__ __launch_bounds__(BW_THREADS) void k_bwavefront(WfArgs<typename WfVal<E>::V> a) {
+  using V = typename WfVal<E>::V;
+  __shared__ BwLds<V> L;
+  SweepTickets tk(a.ctr, a.par, (unsigned)(a.t.ntx * a.t.nty));
+  // values of positions without a point stay finite
+  for (int i = threadIdx.x; i < (int)(sizeof(L) / 16); i += BW_THREADS)
+    reinterpret_cast<u32x4*>(&L)[i] = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  tk.start();
+  const long half = (long)a.t.ntx * a.t.nty * a.t.ns * BW_ES;
+  V* const strip = a.strip + (tk.par & 1u ? half : 0l);
+  V* const other = a.strip + (tk.par & 1u ? 0l : half);
+  unsigned ticket;
+  auto tile = [&] { return DIR > 0 ? ticket : tk.ntiles - 1u - ticket; };
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  if (wave < BW_NCW) {
+    while (tk.take(&ticket)) bw_compute<DIR, P, E>(a, bw_geo(a, tile()), tile(), L.ring, L.hbuf);
+  } else if (wave == BW_NCW) {
+    while (tk.take(&ticket)) bw_halo<DIR, V>(a, bw_geo(a, tile()), strip, L.ring, a.err);
+  } else if (wave == BW_NCW + 1) {
+    while (tk.take(&ticket)) bw_load<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
+  } else if (wave == BW_NCW + 2) {
+    while (tk.take(&ticket)) bw_store<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
+  } else {
+    while (tk.take(&ticket)) bw_export<DIR, V>(a, bw_geo(a, tile()), tile(), strip, other, L.ring);
   }
 }
 
 template <class E>
 hipError_t launch_bwavefront(int dir, const WfArgs<typename WfVal<E>::V>& a, hipStream_t st) {
   const unsigned ntiles = (unsigned)(a.t.ntx * a.t.nty);
-  const unsigned grid = ntiles < 2048u ? ntiles : 2048u;
+  const unsigned grid = ntiles < (unsigned)WF_MAX_GRID ? ntiles : (unsigned)WF_MAX_GRID;
+  // steps of row data fetched ahead, as the registers allow (the forward
+  // sweep's prefix holds 24 more values)
+  constexpr int PF = sizeof(E) == 2 ? 4 : 2, PB = sizeof(E) == 8 ? 2 : 4;
   if (dir > 0)
-    hipLaunchKernelGGL((k_bwavefront<1, E>), dim3(grid), dim3(BW_NT), 0, st, a);
+    hipLaunchKernelGGL((k_bwavefront<1, PF, E>), dim3(grid), dim3(BW_THREADS), 0, st, a);
   else
-    hipLaunchKernelGGL((k_bwavefront<-1, E>), dim3(grid), dim3(BW_NT), 0, st, a);
+    hipLaunchKernelGGL((k_bwavefront<-1, PB, E>), dim3(grid), dim3(BW_THREADS), 0, st, a);
   return hipGetLastError();
 }
 template hipError_t launch_bwavefront<double>(int, const WfArgs<double>&, hipStream_t);
@@ -456,7 +703,7 @@ __global__ __launch_bounds__(256) void k_bwf_pack(Grid g, WfTiling tl, int dir, 
   const int lane = (int)(q % BW_NL);
   for (int r = 0; r < 3; ++r)
     for (int p = 0; p < NPR; ++p) {
-      E* o = out + (((pos * 3 + r) * NPR + p) * BW_NL + lane) * K;
+      E* o = out + ((pos * NPR + p) * (3 * BW_NL) + 3 * lane + r) * K;
       for (int e = 0; e < K; ++e) {
         const int v = p * K + e;
         double x = 0.0;
@@ -501,7 +748,7 @@ __global__ __launch_bounds__(256) void k_bwf_pack_h(Grid g, WfTiling tl, int dir
       for (int b = 0; b < 4; ++b) bytes[84 + 4 * c + b] = (unsigned char)(u >> (8 * b));
     }
     for (int p = 0; p < NPR; ++p) {
-      unsigned char* o = out + (((pos * 3 + r) * NPR + p) * BW_NL + lane) * 16;
+      unsigned char* o = out + ((pos * NPR + p) * (3 * BW_NL) + 3 * lane + r) * 16;
       for (int b = 0; b < 16; ++b) o[b] = bytes[16 * p + b];
     }
   }

@@ -27,11 +27,10 @@ struct WfArgs {
   const void* pk;            // packed sweep data of this direction (launch_wf_pack)
   const float* sd;           // FP16 storage: {row scale, diagonal scaling} per position
   const V* h;                // right-hand side of the triangular system
-  V* x;                      // output (block sweep: positions read by other tiles hold the sentinel)
-  V* next;                   // block sweep: output buffer of the level's next sweep (sentinel prefill), or null
-  int next_dir;              // direction of that next sweep
-  V* strip;                  // scalar sweep: two buffers of wf_strip_elems entries, through which tiles exchange values
-  unsigned* par;             // scalar sweep: bit 0 names the buffer of the level's next sweep (it holds sentinels)
+  V* x;                      // output
+  V* strip;                  // two buffers of wf_strip_elems (blocks: bwf_strip_elems) entries, through which tiles
+                             // exchange values
+  unsigned* par;             // bit 0 names the buffer of the level's next sweep (it holds sentinels)
   const V* addv;             // optional: addout = addv + x
   V* addout;
   unsigned* ctr;             // [0] ticket counter, [1] exit counter; zero between launches
@@ -238,8 +237,10 @@ hipError_t launch_blower(const Grid& g, const M& m, const typename M::V* f, cons
 template <class M>
 hipError_t launch_bupper(const Grid& g, const M& m, const typename M::V* f, const typename M::V* u,
                          typename M::V* h, hipStream_t st);
-// point-block Gauss-Seidel sweep on 8 x 8-column tiles (WfArgs.pk: launch_bwf_pack data of this direction)
+// point-block Gauss-Seidel sweep on 4 x 8-column tiles (WfArgs.pk: launch_bwf_pack data of this direction)
 void bwf_tiling(const Grid& g, WfTiling* t);
+long bwf_reserve(const Grid& g);  // as wf_reserve, of 8 x 8-column tiles
+long bwf_strip_elems(const WfTiling& t);
 int bwf_pack_count(int ebytes);
 template <class E>
 hipError_t launch_bwavefront(int dir, const WfArgs<typename WfVal<E>::V>& a, hipStream_t st);

@@ -229,7 +229,8 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       }
     } else {
       bwf_tiling(v.g, &v.tl);
-      const size_t pbytes = (size_t)bwf_pack_count(eb) * 16 * v.tl.nsk;
+      v.strip_cap = 2 * bwf_strip_elems(v.tl);
+      const size_t pbytes = (size_t)bwf_pack_count(eb) * 16 * bwf_reserve(v.g);
       v.pk[0] = ar.take<char>(pbytes);
       v.pk[1] = ar.take<char>(pbytes);
     }
@@ -311,16 +312,15 @@ hipError_t sweep(smg_handle_s* H, const Level& L, int dir, bool unitd, const V* 
 }
 
 template <class E, class V>
-hipError_t bsweep(smg_handle_s* H, const Level& L, int dir, const V* hin, V* x, V* next, int next_dir,
-                  hipStream_t st) {
+hipError_t bsweep(smg_handle_s* H, const Level& L, int dir, const V* hin, V* x, hipStream_t st) {
   WfArgs<V> a{};
   a.g = L.g;
   a.t = L.tl;
   a.pk = L.pk[dir > 0 ? 0 : 1];
   a.h = hin;
   a.x = x;
-  a.next = next;
-  a.next_dir = next_dir;
+  a.strip = (V*)L.strip;
+  a.par = L.par;
   a.ctr = H->ctr;
   a.err = H->err;
   return launch_bwavefront<E>(dir, a, st);
@@ -340,7 +340,7 @@ hipError_t bvcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* 
     const Level& v = H->lev[l];
     {
       Timed t(H, l, 0, st);
-      e = bsweep<E, V>(H, v, +1, F(l), (V*)v.ua, UB(l), -1, st);
+      e = bsweep<E, V>(H, v, +1, F(l), (V*)v.ua, st);
     }
     if (e != hipSuccess) return e;
     Timed t(H, l, 2, st);
@@ -362,7 +362,7 @@ hipError_t bvcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* 
     }
     if (e != hipSuccess) return e;
     Timed t(H, l, 5, st);
-    e = bsweep<E, V>(H, v, -1, (const V*)v.h, UB(l), (V*)v.ua, +1, st);
+    e = bsweep<E, V>(H, v, -1, (const V*)v.h, UB(l), st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -459,8 +459,8 @@ hipError_t old_terms(smg_handle_s* H, const Level& v, int dir, const typename PT
 // operations to each value.
 //
 // GS step k of a level (0 <= k < T = pre + post) runs in direction D(k) and
-// writes X(k).  Line GS and 3x3 blocks exchange values through the output:
-// the step before left the sentinels of direction D(k) in X(k) (the last step
+// writes X(k).  Line GS exchanges values through the output: the step before
+// left the sentinels of direction D(k) in X(k) (the last step
 // of a cycle prepares X(0) of the next cycle, setup prepares every buffer
 // once).  X alternates between u_a and the level's
 // output, so X(k + 1) = X(k - 1): that buffer's old values were consumed by
@@ -505,7 +505,7 @@ hipError_t vcycle_gen_t(smg_handle_s* H, const typename PT::V* f0, typename PT::
       if (e != hipSuccess) return e;
       hin = (const V*)v.h;
     }
-    if (bs == 3) return bsweep<E, V>(H, v, D(k), hin, x, nx, D(kn), st);
+    if (bs == 3) return bsweep<E, V>(H, v, D(k), hin, x, st);
     return sweep<E, V>(H, v, D(k), false, hin, x, nullptr, nullptr, st);
   };
   // ILU(0) step k: out = u + U^-1 L^-1 (f - A u) (u null: the ZeroGuess
@@ -588,8 +588,8 @@ hipError_t vcycle_gen_t(smg_handle_s* H, const typename PT::V* f0, typename PT::
 }
 
 // One V-cycle on internal or caller vectors: f0 = level-0 right-hand side,
-// z0 = level-0 output (line GS and 3x3 blocks: its positions read across
-// tiles are given sentinels by the pre-smoothing sweep).
+// z0 = level-0 output (line GS: its positions are given sentinels by the
+// pre-smoothing sweep).
 template <class PT>
 hipError_t vcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* z0, hipStream_t st) {
   using V = typename PT::V;
@@ -855,9 +855,9 @@ hipError_t pack_sweep_data(smg_handle_s* H, Level& v, hipStream_t st) {
 
 // The state the first sweep of a level expects whatever the tiling (each
 // sweep then leaves it for the next one): sentinels in the buffers through
-// which workgroups exchange values -- the strip buffers of the tiled scalar
-// sweeps (whose buffer word is zero: the counter block is cleared first), the
-// sweep outputs of line GS and 3x3 blocks.
+// which workgroups exchange values -- the strip buffers of the tiled sweeps
+// (whose buffer word is zero: the counter block is cleared first), the sweep
+// outputs of line GS.
 hipError_t fill_sentinels(smg_handle_s* H, Level& v, hipStream_t st) {
   const bool strips = v.strip_cap > 0;
   const long nv = strips ? v.strip_cap : v.N * H->bs;
@@ -1591,11 +1591,7 @@ static hipError_t op_presmooth_t(smg_handle_s* H, const Level& v, const void* f,
   }
   const long nv = v.N * H->bs;
   hipError_t e;
-  if (H->bs == 3) {
-    e = launch_fill_bits<V>((V*)u, nv, sent, st);
-    if (e == hipSuccess) e = bsweep<typename PT::E, V>(H, v, +1, (const V*)f, (V*)u, nullptr, 0, st);
-    return e;
-  }
+  if (H->bs == 3) return bsweep<typename PT::E, V>(H, v, +1, (const V*)f, (V*)u, st);
   if (H->cfg.smoother == SMG_SMOOTH_GS)
     return sweep<typename PT::E, V>(H, v, +1, false, (const V*)f, (V*)u, nullptr, nullptr, st);
   if (H->cfg.smoother == SMG_SMOOTH_LGS) {
@@ -1625,13 +1621,11 @@ static hipError_t op_postsmooth_t(smg_handle_s* H, const Level& v, const void* f
   const auto A = PT::A(v);
   hipError_t e;
   if (H->bs == 3) {
-    // u_old = u_in + P ec in the level's u_a buffer (its sentinels restored after)
+    // u_old = u_in + P ec in the level's u_a buffer
     e = hipMemcpyAsync(v.ua, uin, sizeof(V) * nv, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && ec != nullptr) e = launch_prolong_add<V>(v.g, v.cmask, 3, (const V*)ec, (V*)v.ua, st);
     if (e == hipSuccess) e = launch_blower(v.g, PT::BA(v), (const V*)f, (const V*)v.ua, (V*)v.h, st);
-    if (e == hipSuccess) e = launch_fill_bits<V>((V*)uout, nv, sent, st);
-    if (e == hipSuccess) e = bsweep<typename PT::E, V>(H, v, -1, (const V*)v.h, (V*)uout, nullptr, 0, st);
-    if (e == hipSuccess) e = launch_fill_bits<V>((V*)v.ua, nv, sent, st);
+    if (e == hipSuccess) e = bsweep<typename PT::E, V>(H, v, -1, (const V*)v.h, (V*)uout, st);
     return e;
   }
   if (H->cfg.smoother == SMG_SMOOTH_LGS) {

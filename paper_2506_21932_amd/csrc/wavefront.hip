@@ -86,6 +86,7 @@
 #include "smg_common.h"
 #include "smg_group.h"
 #include "smg_kernels.h"
+#include "smg_sweep.h"
 
 namespace smg {
 
@@ -100,18 +101,12 @@ constexpr int WF_GRP = WF_NL * WF_CH / 64;   // column-run groups per chunk (4 c
 constexpr int WF_GPS = WF_GRP / WF_CH;       // groups moved per step
 constexpr int WF_RW = WF_NL + WF_NH + 1;     // ring row length (padded)
 constexpr int WF_HRW = WF_NL + 1;            // chunk buffer row length (padded)
-constexpr unsigned WF_SPIN_LIMIT = 1u << 21;
 #ifndef WF_LAG_EXTRA
 #define WF_LAG_EXTRA 2
 #endif
 #ifndef WF_PH
 #define WF_PH 4
 #endif
-constexpr unsigned WF_OOB = 0x80000000u;     // buffer offset outside every range
-constexpr int WF_SC1 = 16;                   // cache policy of device-coherent accesses
-
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Neighbour columns holding lower neighbours (forward-frame offsets); a
 // backward sweep uses the negated offsets.
@@ -246,36 +241,6 @@ __device__ inline bool wf_halo_used(int pat, int dir, int sh, int qx, int qy) {
     if (lx >= 0 && lx < WF_TX && ly >= 0 && ly < WF_TY) return true;
   }
   return false;
-}
-
-// ---- buffer access helpers -------------------------------------------------
-__device__ inline __amdgpu_buffer_rsrc_t wf_rsrc(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <class V, int CP>
-__device__ inline V bld(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0u) {
-  if constexpr (sizeof(V) == 8)
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, CP));
-  else
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, CP));
-}
-template <int CP, class V>
-__device__ inline void bst(V v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0u) {
-  if constexpr (sizeof(V) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, soff, CP);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, soff, CP);
-}
-
-template <class V>
-__device__ inline V wf_coherent_load(const V* p) {
-  using U = typename VBits<V>::U;
-  return VBits<V>::val(__hip_atomic_load(reinterpret_cast<const U*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-template <class V>
-__device__ inline void wf_coherent_store(V* p, V v) {
-  using U = typename VBits<V>::U;
-  __hip_atomic_store(reinterpret_cast<U*>(p), VBits<V>::bits(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Storage element traits: arithmetic type V, elements per 16-byte pack K,
@@ -595,15 +560,6 @@ __device__ __forceinline__ void wf_halo(const WfArgs<V>& a, const WfGeo& q, cons
 // compiler may not move across the step's memory operations, so that it does
 // not compute every step's offsets ahead (they would hold dozens of
 // registers for the whole chunk or sweep).
-__device__ inline int wf_keep(int v) {
-  asm volatile("" : "+v"(v) : : "memory");
-  return v;
-}
-__device__ inline int wf_keep_s(int v) {
-  asm volatile("" : "+s"(v) : : "memory");
-  return v;
-}
-
 template <int PAT, int DIR, class V>
 struct WfRuns {
   static constexpr int WX = hp_wx(PAT), WY = hp_wy(PAT), KB = wf_kb(PAT);
@@ -835,16 +791,6 @@ struct WfJob {
   unsigned tile, par;
 };
 
-// The next ticket, the same for every thread.
-__device__ inline unsigned wf_take_ticket(unsigned* ctr) {
-  __shared__ unsigned s_ticket;
-  if (threadIdx.x == 0) s_ticket = atomicAdd(&ctr[0], 1u);
-  __syncthreads();
-  const unsigned t = s_ticket;
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(t);
-}
-
 // Every role of a sweep workgroup runs its own loop over the workgroup's
 // tiles (values a role keeps across tiles then stay out of the other roles'
 // code); next(&job) takes the next ticket, the same for all waves.
@@ -872,45 +818,20 @@ __device__ __forceinline__ void wf_roles(Next next, unsigned* err, WfLds<typenam
   }
 }
 
-// One sweep over one grid: persistent workgroups take tiles by ticket.  A
-// workgroup reads the buffer word before it takes its first ticket (the
-// ticket's operand depends on the word), so whoever holds the last ticket --
-// the last tile's if every workgroup has one tile, else the last one beyond
-// the tiles -- knows that all others have read it and have taken theirs, and
-// readies counter and buffer word for the next launch.
+// One sweep over one grid: persistent workgroups take tiles by ticket.
 template <int PAT, int DIR, int P, class E, bool UNITD>
 __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<E>::V> a) {
   using V = typename WfVal<E>::V;
   __shared__ WfLds<V> L;
-  __shared__ unsigned s_first, s_par;
-  const unsigned ntiles = (unsigned)(a.t.ntx * a.t.nty);
-  const bool single = ntiles <= gridDim.x;
-  auto reset = [&](unsigned par) {
-    if (threadIdx.x == 0) {
-      __hip_atomic_store(&a.ctr[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.par, par ^ 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  };
-  if (threadIdx.x == 0) {
-    const unsigned p = __hip_atomic_load(a.par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_par = p;
-    s_first = atomicAdd(&a.ctr[0], 1u + (p >> 31));
-  }
+  SweepTickets tk(a.ctr, a.par, (unsigned)(a.t.ntx * a.t.nty));
   wf_zero_lds(&L);  // (ends with a barrier)
-  const unsigned first = __builtin_amdgcn_readfirstlane(s_first), par = __builtin_amdgcn_readfirstlane(s_par);
-  if (single && first == ntiles - 1u) reset(par);
-  bool started = false;
+  tk.start();
   auto next = [&](WfJob<V>* w) {
-    if (started && single) return false;
-    const unsigned ticket = started ? wf_take_ticket(a.ctr) : first;
-    if (ticket >= ntiles) {  // (also a first ticket: of a workgroup that started after the others were done)
-      if (ticket == ntiles + gridDim.x - 1u) reset(par);
-      return false;
-    }
-    started = true;
+    unsigned ticket;
+    if (!tk.take(&ticket)) return false;
     w->a = a;
-    w->tile = DIR > 0 ? ticket : ntiles - 1u - ticket;
-    w->par = par;
+    w->tile = DIR > 0 ? ticket : tk.ntiles - 1u - ticket;
+    w->par = tk.par;
     return true;
   };
   wf_roles<PAT, DIR, P, E, UNITD>(next, a.err, &L);

@@ -50,3 +50,29 @@ def test_sweeps_bitexact(shape, pat, prec):
         for _ in range(rep + 1):
             got = _np(mg.op_postsmooth(0, ft, ut, None, torch.empty(f.size, dtype=dt, device=DEV)))
         assert np.array_equal(got, oracle.gs_sweep(off, Al, rd, f, u, -1, 0).ravel()), rep
+
+
+# 3x3 blocks: tiles of 4 x 8 columns
+BLOCK_SHAPES = [(8, 8, 33), (4, 9, 16), (5, 17, 15), (9, 7, 64), (13, 24, 41), (1, 20, 18), (72, 170, 5)]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("shape", BLOCK_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_block_sweeps_bitexact(shape, prec):
+    A = workloads.random_sgdia(shape, 27, seed=41, block=3)
+    H = oracle.Hierarchy(shape, 27, A, block=3, prec=prec)
+    mg = smg.StructMG(torch.from_numpy(A).to(DEV), shape, pattern=27, block=3, prec=prec, device=DEV)
+    assert H.nlev >= 2
+    off = workloads.offsets(27)
+    what, npt, dt = (0, np.float64, torch.float64) if prec == "fp64" else (5, np.float32, torch.float32)
+    Al, D = H.level_data(0, what), H.level_data(0, what + 1)
+    g = workloads.rng(43)
+    for rep in range(2):
+        f = g.uniform(-1, 1, size=shape + (3,)).astype(npt)
+        u = g.uniform(-1, 1, size=shape + (3,)).astype(npt)
+        ft, ut = (torch.from_numpy(v.ravel()).to(DEV) for v in (f, u))
+        got = _np(mg.op_presmooth(0, ft, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.bgs_sweep(off, Al, D, f, np.zeros_like(f), 1, 1).ravel()), rep
+        for _ in range(rep + 1):
+            got = _np(mg.op_postsmooth(0, ft, ut, None, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.bgs_sweep(off, Al, D, f, u, -1, 0).ravel()), rep
