@@ -54,6 +54,7 @@ namespace {
 constexpr int LGS_NT = 256;                 // threads per workgroup
 constexpr int LGS_PTS = LGS_NT;             // points per chunk (K * nz), unless nz is larger
 constexpr unsigned LGS_SPIN_LIMIT = 1u << 21;
+constexpr int LT_MAX_GRID = 256;            // k_lgs_tile: one workgroup per CU
 
 __host__ __device__ constexpr int lgs_cwx(int pat) { return pat == 7 ? 1 : 2; }
 
@@ -269,6 +270,403 @@ __global__ __launch_bounds__(LGS_NT) void k_lgs(LgsArgs<V> a) {
   lgs_retire(a.ctr);
 }
 
+// ---- columns of at most LT_MAX_NZ points -------------------------------------
+// The chain of the sweep is one column hyperplane after another (1534 of them
+// at 512 x 512), each a right-hand side and a Thomas recurrence of 2 nz
+// dependent operations, so everything else is kept out of it.  A workgroup
+// holds a tile of K x K columns (K nz points a hyperplane) and steps through
+// its 2K - 1 hyperplanes with two barriers each; its waves have roles:
+//   point waves, a thread per (lx, z): after the first barrier of a step the
+//     terms of this sweep's columns, from LDS, onto a sum of f and the old
+//     values that was formed a step earlier; behind the Thomas solve they load
+//     the data of the step after next and prepare the next one; they store the
+//     columns of the step before, device-coherently, and their sentinels;
+//   a Thomas wave, a lane per column: LDS to LDS, the next eight points' reads
+//     issued before the current eight are used;
+//   a halo wave: the neighbouring tiles' columns the next step needs (one at
+//     lx = -1, one each in the rows ly' = -1 and -2), read device-coherently
+//     one step ahead and awaited while they hold the sentinel;
+// Finished columns stay in an LDS ring of four hyperplanes (the neighbours of
+// a column lie one to three hyperplanes back).  The backward sweep mirrors the
+// tile.  A hyperplane takes 2.4 us, of which the Thomas solve about half (its
+// chain, and LDS reads and writes of 16 bytes).  Forward / backward sweep of a
+// 512 x 512 x 64 level, 19-point FP32, with the kernel above and with this one
+// (MI355X): 10.43 / 11.55 and 3.74 / 3.72 ms; 128 x 128 x 64, 27-point: 1.29 /
+// 1.55 and 0.49 / 0.45 ms (kernel above: longer columns, whose hyperplanes of
+// one or two columns leave nothing to overlap).
+constexpr int LT_MAX_NZ = 128;
+template <class V>
+constexpr int lt_pts() {
+  return sizeof(V) == 4 ? 512 : 256;  // points per hyperplane (registers per point: two steps' data)
+}
+__host__ __device__ constexpr int lt_ldp(int nz) { return (nz + 7) / 8 * 8 + 4; }  // column stride of the LDS arrays
+__host__ __device__ constexpr int lt_rz(int nz) { return lt_ldp(nz) + 8; }         // ... of the ring (z at z + 4)
+
+// Eight consecutive values (16-byte aligned) of an LDS column.
+template <class V>
+__device__ __forceinline__ void lt_read8(V (&o)[8], const V* p) {
+  typedef V VV __attribute__((ext_vector_type(16 / sizeof(V))));
+#pragma unroll
+  for (int q = 0; q < 8; q += 16 / (int)sizeof(V)) {
+    const VV w = *reinterpret_cast<const VV*>(p + q);
+#pragma unroll
+    for (int r = 0; r < 16 / (int)sizeof(V); ++r) o[q + r] = w[r];
+  }
+}
+template <class V>
+__device__ __forceinline__ void lt_write8(V* p, const V (&o)[8]) {
+  typedef V VV __attribute__((ext_vector_type(16 / sizeof(V))));
+#pragma unroll
+  for (int q = 0; q < 8; q += 16 / (int)sizeof(V)) {
+    VV w;
+#pragma unroll
+    for (int r = 0; r < 16 / (int)sizeof(V); ++r) w[r] = o[q + r];
+    *reinterpret_cast<VV*>(p + q) = w;
+  }
+}
+
+template <int PAT, class V>
+struct LtPoint {
+  V a[PAT], uo[PAT], t, la, lr, lc;
+  bool act, yl, yh;  // is there a point; neighbours at y - 1, y + 1
+};
+
+template <int PAT, int DIR, class V, bool ZG>
+__global__ __launch_bounds__(lt_pts<V>() + 128) void k_lgs_tile(LgsArgs<V> a) {
+  constexpr int SH = lgs_cwx(PAT) - 1, SLO = pat_slot(PAT, 0, 0, -1);
+  extern __shared__ __align__(16) unsigned char lgs_smem[];
+  using B = VBits<V>;
+  const Grid g = a.g;
+  const long N = g.N();
+  const int nz = g.nz, K = a.K, LDP = lt_ldp(nz), RZ = lt_rz(nz);
+  V* const ld = reinterpret_cast<V*>(lgs_smem);  // right-hand side, then d'
+  V* const fac = ld + K * LDP;                    // [2][3][K]: coupling to z-1, 1 / pivot, c / pivot
+  V* const ring = fac + 6 * K * LDP;              // [4][K + 1]: finished columns, position lx + 1
+  const int nsteps = 2 * K - 1;
+  const int npw = (K * nz + 63) / 64;  // point waves
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = threadIdx.x % 64;
+  // point waves: a thread per (lx, z); the last wave's rest idles
+  const bool rest = (int)threadIdx.x >= K * nz;
+  const int lx = rest ? K - 1 : (int)threadIdx.x / nz, z = rest ? 0 : (int)threadIdx.x % nz;
+  auto ringp = [&](int h, int pos) { return ring + ((h & 3) * (K + 1) + pos) * RZ + 4; };
+
+  for (;;) {
+    const unsigned ticket = lgs_take_ticket(a.ctr);
+    if (ticket >= (unsigned)a.ntile) break;
+    const int e = a.tmap[DIR > 0 ? (int)ticket : a.ntile - 1 - (int)ticket];
+    const int bx = e >> 16, by = e & 0xffff;
+    // grid column of (lx, ly) in the forward frame; does it exist?
+    auto column = [&](int cx, int cy, int& X, int& Y) {
+      X = bx * K + (DIR > 0 ? cx : K - 1 - cx);
+      Y = by * K + (DIR > 0 ? cy : K - 1 - cy) - SH * X;
+      return X >= 0 && X < g.nx && Y >= 0 && Y < g.ny;
+    };
+    // --- point role (32-bit byte offsets from the plane before the tile's first)
+    const int X0 = bx * K > 0 ? bx * K - 1 : 0;
+    const long tb = (long)X0 * g.ny * nz;
+    const int Xp = bx * K + (DIR > 0 ? lx : K - 1 - lx);
+    const int Y0 = by * K + (DIR > 0 ? 0 : K - 1) - SH * Xp;  // y of ly = 0; then DIR steps
+    const bool prole = !rest && Xp < g.nx;
+    // y of this thread's column at step k; is there one?
+    auto at_step = [&](int k, int& Y) {
+      const int ly = k - lx;
+      Y = Y0 + DIR * ly;
+      return prole && (unsigned)ly < (unsigned)K && (unsigned)Y < (unsigned)g.ny;
+    };
+    const bool xl = Xp > 0, xh = Xp < g.nx - 1, zl = z > 0, zh = z < nz - 1;
+    auto inside = [&](const LtPoint<PAT, V>& p, int s) {
+      const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1), dz = pat_off(PAT, s, 2);
+      bool in = p.act;
+      if (dx < 0) in = in & xl;
+      if (dx > 0) in = in & xh;
+      if (dy < 0) in = in & p.yl;
+      if (dy > 0) in = in & p.yh;
+      if (dz < 0) in = in & zl;
+      if (dz > 0) in = in & zh;
+      return in;
+    };
+    // data of step k (every load before the first use; a missing neighbour's
+    // value is the point's own and goes unused)
+    auto load = [&](LtPoint<PAT, V>& p, int k) {
+      int Y;
+      p.act = at_step(k, Y);
+      p.yl = Y > 0;
+      p.yh = Y < g.ny - 1;
+      const unsigned o = p.act ? (unsigned)(((Xp - X0) * g.ny + Y) * nz + z) * (unsigned)sizeof(V) : 0u;
+      auto at = [&](const V* v, unsigned off) { return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(v + tb) + off); };
+#pragma unroll
+      for (int s = 0; s < PAT; ++s) {
+        const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1), dz = pat_off(PAT, s, 2);
+        if (dx == 0 && dy == 0) continue;
+        const bool later = lgs_later(DIR, dx, dy);
+        if (ZG && later) continue;
+        p.a[s] = at(a.A + (long)s * N, o);
+        if (later)
+          p.uo[s] = at(a.uold, inside(p, s) ? o + (unsigned)(((dx * g.ny + dy) * nz + dz) * (int)sizeof(V)) : o);
+      }
+      p.t = at(a.f, o);
+      p.la = at(a.A + (long)SLO * N, o);
+      p.lr = at(a.rden, o);
+      p.lc = at(a.cp, o);
+    };
+    // the terms of old values, and the Thomas factors into LDS
+    auto stage = [&](LtPoint<PAT, V>& p, int k) {
+      if constexpr (!ZG) {
+#pragma unroll
+        for (int s = 0; s < PAT; ++s) {
+          const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1);
+          if ((dx == 0 && dy == 0) || !lgs_later(DIR, dx, dy)) continue;
+          p.t = inside(p, s) ? fma(-p.a[s], p.uo[s], p.t) : p.t;
+        }
+      }
+      if (p.act) {
+        V* o = fac + (k & 1) * 3 * K * LDP + lx * LDP + z;
+        o[0] = zl ? p.la : V(0);
+        o[K * LDP] = p.lr;
+        o[2 * K * LDP] = p.lc;
+      }
+    };
+    // the terms of this sweep's columns
+    auto rhs = [&](LtPoint<PAT, V>& p, int k) {
+      V v[PAT];
+#pragma unroll
+      for (int s = 0; s < PAT; ++s) {
+        const int dx = DIR * pat_off(PAT, s, 0), dy = DIR * pat_off(PAT, s, 1), dz = pat_off(PAT, s, 2);
+        if ((dx == 0 && dy == 0) || lgs_later(1, dx, dy)) continue;
+        v[s] = ringp(k + dx + dy + SH * dx, lx + 1 + dx)[z + dz];  // forward-frame offset (dx, dy + SH dx)
+      }
+      V t = p.t;
+#pragma unroll
+      for (int s = 0; s < PAT; ++s) {
+        const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1);
+        if ((dx == 0 && dy == 0) || lgs_later(DIR, dx, dy)) continue;
+        t = inside(p, s) ? fma(-p.a[s], v[s], t) : t;
+      }
+      if (p.act) ld[lx * LDP + z] = t;
+    };
+    // --- Thomas role
+    const int Xt = bx * K + (DIR > 0 ? lane : K - 1 - lane), Yt = by * K + (DIR > 0 ? 0 : K - 1) - SH * Xt;
+    auto solve = [&](int k) {
+      const int ly = k - lane;
+      if (lane >= K || Xt >= g.nx || (unsigned)ly >= (unsigned)K || (unsigned)(Yt + DIR * ly) >= (unsigned)g.ny) return;
+      V* const d = ld + lane * LDP;
+      const V* const fa = fac + (k & 1) * 3 * K * LDP + lane * LDP;
+      const V *const fr = fa + K * LDP, *const fc = fr + K * LDP;
+      V* const out = ringp(k, lane + 1);
+      // blocks of 8 points; the next block's reads are issued before this
+      // one's chain (a read past the column's end stays inside its stride)
+      struct Blk {
+        V a[8], r[8], d[8];
+      };
+      const int nb = nz / 8;  // full blocks
+      V dp = V(0);
+      auto read3 = [&](Blk& b, int z0) {
+        lt_read8(b.a, fa + z0);
+        lt_read8(b.r, fr + z0);
+        lt_read8(b.d, d + z0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // d'_0 = t_0 / pivot_0 comes out of the same formula (coupling and d' are +0)
+      auto forward = [&](const Blk& b, int z0, int n) {
+        // (a ragged block's last places are written too: they lie past the column)
+        V o[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const V v = fma(-b.a[q], dp, b.d[q]) * b.r[q];
+          dp = q < n ? v : dp;
+          o[q] = dp;
+        }
+        lt_write8(d + z0, o);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      Blk b0, b1;
+      read3(b0, 0);
+      int ib = 0;
+      for (; ib + 2 <= nb; ib += 2) {
+        read3(b1, 8 * ib + 8);
+        forward(b0, 8 * ib, 8);
+        read3(b0, ib + 2 <= nb ? 8 * ib + 16 : 0);
+        forward(b1, 8 * ib + 8, 8);
+      }
+      if (ib < nb) {
+        read3(b1, 8 * ib + 8);
+        forward(b0, 8 * ib, 8);
+        if (nz > 8 * nb) forward(b1, 8 * nb, nz - 8 * nb);
+      } else if (nz > 8 * nb) {
+        forward(b0, 8 * nb, nz - 8 * nb);
+      }
+      V xv = dp;  // the last point's value (the ragged block writes it in its place)
+      auto read2 = [&](Blk& b, int z0) {
+        lt_read8(b.a, fc + z0);
+        lt_read8(b.d, d + z0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      auto back = [&](const Blk& b, int z0, int n) {
+        V o[8];
+#pragma unroll
+        for (int q = 7; q >= 0; --q) {
+          const V v = fma(-b.a[q], xv, b.d[q]);
+          xv = q < n ? v : xv;
+          o[q] = xv;
+        }
+        lt_write8(out + z0, o);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // points nz - 2 .. 0: the ragged top block, then full blocks
+      const int mb = (nz - 1) / 8;
+      read2(b0, 8 * mb);
+      if (mb > 0) read2(b1, 8 * mb - 8);
+      back(b0, 8 * mb, nz - 1 - 8 * mb);
+      for (ib = mb - 1; ib >= 1; ib -= 2) {
+        read2(b0, 8 * ib - 8);
+        back(b1, 8 * ib, 8);
+        if (ib >= 2) read2(b1, 8 * ib - 16);
+        back(b0, 8 * ib - 8, 8);
+      }
+      if (ib == 0) back(b1, 0, 8);
+    };
+    // --- halo role: the neighbouring tiles' columns that step k is the first
+    // to need
+    constexpr int NC = SH ? 3 : 2;
+    V hv[NC][2];
+    // column c of step k: (-1, k), (k, -1), (k - 1, -2); k counts along a line
+    // of columns, whose first index, step and existing members are kept
+    long hbase[NC];
+    int hstep[NC];
+    unsigned hmask[NC];
+    auto halo_plan = [&] {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int cx = c == 0 ? -1 : (c == 1 ? 0 : -1), cy = c == 0 ? 0 : -c;
+        int X, Y;
+        column(cx, cy, X, Y);
+        hbase[c] = ((long)X * g.ny + Y) * nz;
+        hstep[c] = DIR * (c == 0 ? 1 : g.ny - SH) * nz;
+        hmask[c] = 0;
+        for (int k = 0; k < K; ++k) hmask[c] |= column(c == 0 ? -1 : cx + k, c == 0 ? k : cy, X, Y) ? 1u << k : 0u;
+      }
+    };
+    auto halo_col = [&](int k, int c, int& h, int& pos, long& i) {  // h: hyperplane; false: no such column
+      h = k - (c == 2 ? 3 : 1);
+      pos = c == 0 ? 0 : (c == 1 ? k + 1 : k);
+      const bool ok = k < K && ((hmask[c] >> k) & 1u) != 0;
+      i = ok ? hbase[c] + (long)k * hstep[c] : 0;
+      return ok;
+    };
+    auto halo_load = [&](int k, V (&v)[NC][2]) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        int h, pos;
+        long i;
+        halo_col(k, c, h, pos, i);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v[c][q] = cload(a.x + i + (64 * q + lane < nz ? 64 * q + lane : 0));
+      }
+    };
+    auto missing = [&](int k, const V (&v)[NC][2]) {
+      bool miss = false;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        int h, pos;
+        long i;
+        if (halo_col(k, c, h, pos, i)) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) miss |= B::bits(v[c][q]) == B::sent;
+        }
+      }
+      return __builtin_amdgcn_ballot_w64(miss) != 0;
+    };
+    auto halo_put = [&](int k, V (&v)[NC][2]) {
+      if (missing(k, v)) {
+        // fall back behind the producers: wait for the next step's columns
+        // too, so that later steps find theirs when they are read ahead
+        unsigned spins = 0;
+        V w[NC][2];
+        do {
+          if (++spins >= LGS_SPIN_LIMIT) {
+            atomicOr(a.err, 1u);
+            break;
+          }
+          if ((spins & 1023u) == 1023u && (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
+            break;
+          __builtin_amdgcn_s_sleep(1);
+          halo_load(k, v);
+          halo_load(k + 1, w);
+        } while (missing(k, v) || missing(k + 1, w));
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        int h, pos;
+        long i;
+        if (halo_col(k, c, h, pos, i)) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            if (64 * q + lane < nz) ringp(h, pos)[64 * q + lane] = v[c][q];
+        }
+      }
+    };
+    // the finished column of step k, device-coherently, and its sentinel in `next`
+    auto store = [&](int k) {
+      int Y;
+      if (at_step(k, Y)) {
+        const long i = tb + ((Xp - X0) * g.ny + Y) * nz + z;
+        cstore(a.x + i, ringp(k, lx + 1)[z]);
+        if (a.next) a.next[i] = B::val(B::sent);
+      }
+    };
+
+    if (wave < npw) {
+      LtPoint<PAT, V> p0, p1;
+      load(p0, 0);
+      load(p1, 1);
+      stage(p0, 0);
+      __syncthreads();
+      auto step = [&](LtPoint<PAT, V>& p, LtPoint<PAT, V>& pn, int k) {
+        store(k - 1);
+        rhs(p, k);
+        __syncthreads();
+        load(p, k + 2);
+        stage(pn, k + 1);
+        __syncthreads();
+      };
+#pragma unroll 1
+      for (int k = 0; k < nsteps; k += 2) {
+        step(p0, p1, k);
+        if (k + 1 < nsteps) step(p1, p0, k + 1);
+      }
+      store(nsteps - 1);
+    } else if (wave == npw) {
+      __builtin_amdgcn_s_setprio(3);
+      __syncthreads();
+      for (int k = 0; k < nsteps; ++k) {
+        __syncthreads();
+        solve(k);
+        __syncthreads();
+      }
+    } else {
+      halo_plan();
+      if (SH) {  // step 0 also reads (-1, -1)
+        int X, Y;
+        if (column(-1, -1, X, Y)) {
+          const long i = ((long)X * g.ny + Y) * nz;
+          for (int q = lane; q < nz; q += 64) ringp(-2, 0)[q] = await_value(a.x + i + q, cload(a.x + i + q), a.err);
+        }
+      }
+      halo_load(0, hv);
+      halo_put(0, hv);
+      halo_load(1, hv);
+      __syncthreads();
+      for (int k = 0; k < nsteps; ++k) {
+        __syncthreads();
+        halo_put(k + 1, hv);
+        halo_load(k + 2, hv);
+        __syncthreads();
+      }
+    }
+  }
+  lgs_retire(a.ctr);
+}
+
 // Thomas pivots of every z-column (FP64, one thread per column).
 __global__ __launch_bounds__(256) void k_tri_factor(Grid g, int slo, int sc, int sup, const double* __restrict__ A,
                                                      double* __restrict__ rden, double* __restrict__ cp,
@@ -294,6 +692,13 @@ __global__ __launch_bounds__(256) void k_tri_factor(Grid g, int slo, int sc, int
 template <int PAT, int DIR, class V, bool ZG>
 hipError_t launch_lgs_t(const LgsArgs<V>& a, hipStream_t st) {
   const unsigned total = (unsigned)a.ntile;
+  if (a.g.nz <= LT_MAX_NZ) {
+    const unsigned tgrid = total < (unsigned)LT_MAX_GRID ? total : (unsigned)LT_MAX_GRID;
+    const unsigned threads = (unsigned)((a.K * a.g.nz + 63) / 64 + 2) * 64u;
+    const size_t smem = ((size_t)7 * a.K * lt_ldp(a.g.nz) + (size_t)4 * (a.K + 1) * lt_rz(a.g.nz)) * sizeof(V);
+    hipLaunchKernelGGL((k_lgs_tile<PAT, DIR, V, ZG>), dim3(tgrid), dim3(threads), smem, st, a);
+    return hipGetLastError();
+  }
   const unsigned grid = total < (unsigned)LGS_MAX_GRID ? total : (unsigned)LGS_MAX_GRID;
   const size_t lds = lgs_lds_bytes(a.g, a.K, (int)sizeof(V));
   hipLaunchKernelGGL((k_lgs<PAT, DIR, V, ZG>), dim3(grid), dim3(LGS_NT), lds, st, a);
@@ -309,11 +714,12 @@ hipError_t launch_lgs_p(int dir, bool zg, const LgsArgs<V>& a, hipStream_t st) {
 
 }  // namespace
 
-int lgs_plan(const Grid& g, int pat, int* K, std::vector<int>* tmap) {
-  const int k = g.nz >= LGS_PTS ? 1 : (LGS_PTS / g.nz < 8 ? LGS_PTS / g.nz : 8);
+// Tile side: a hyperplane of a tile is K columns, at most pts points.
+static int lgs_side(const Grid& g, int pts) { return g.nz >= pts ? 1 : (pts / g.nz < 8 ? pts / g.nz : 8); }
+
+static int lgs_tiles(const Grid& g, int pat, int k, std::vector<int>* tmap) {
   const int sh = lgs_cwx(pat) - 1;
   const int ntx = (g.nx + k - 1) / k, nty = (g.ny + sh * (g.nx - 1) + k - 1) / k;
-  *K = k;
   int n = 0;
   for (int d = 0; d < ntx + nty - 1; ++d)
     for (int bx = 0; bx < ntx; ++bx) {
@@ -331,6 +737,15 @@ int lgs_plan(const Grid& g, int pat, int* K, std::vector<int>* tmap) {
     }
   return n;
 }
+
+int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap) {
+  *K = lgs_side(g, g.nz > LT_MAX_NZ ? LGS_PTS : (vbytes == 4 ? lt_pts<float>() : lt_pts<double>()));
+  return lgs_tiles(g, pat, *K, tmap);
+}
+
+// (the smaller tiles of every precision, so that the workspace does not
+// depend on the kernel)
+int lgs_reserve(const Grid& g, int pat) { return lgs_tiles(g, pat, lgs_side(g, LGS_PTS), nullptr); }
 
 size_t lgs_lds_bytes(const Grid& g, int K, int vbytes) { return (size_t)4 * K * (g.nz + 1) * vbytes; }
 

@@ -297,7 +297,8 @@ struct LgsArgs {
 };
 // tile side K and the tiles holding columns in dependence order (tmap may
 // be null: count only); returns their number
-int lgs_plan(const Grid& g, int pat, int* K, std::vector<int>* tmap);
+int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap);
+int lgs_reserve(const Grid& g, int pat);  // room for tmap
 size_t lgs_lds_bytes(const Grid& g, int K, int vbytes);
 hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rden, double* cp, unsigned* err,
                              hipStream_t st);

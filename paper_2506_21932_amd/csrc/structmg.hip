@@ -197,8 +197,8 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     }
     const int eb = cfg.prec == SMG_FP16_ROWSCALE ? 2 : (int)vsz;
     if (cfg.smoother == SMG_SMOOTH_LGS) {
-      v.lg_nt = lgs_plan(v.g, v.S, &v.lg_K, nullptr);
-      v.lg_map = ar.take<int>((size_t)v.lg_nt);
+      v.lg_nt = lgs_plan(v.g, v.S, (int)vsz, &v.lg_K, nullptr);
+      v.lg_map = ar.take<int>((size_t)lgs_reserve(v.g, v.S));
       v.tr64 = ar.take<double>((size_t)N);
       v.tc64 = ar.take<double>((size_t)N);
       if (cfg.prec == SMG_FP32) {
@@ -960,7 +960,7 @@ smg_status build_hierarchy(smg_handle_s* H, const double* coeffs, hipStream_t st
     if (cfg->smoother == SMG_SMOOTH_LGS) {
       std::vector<int> tiles;
       int kside = 0;
-      lgs_plan(v.g, v.S, &kside, &tiles);
+      lgs_plan(v.g, v.S, cfg->prec == SMG_FP64 ? 8 : 4, &kside, &tiles);
       SCHK(hipMemcpy(v.lg_map, tiles.data(), sizeof(int) * tiles.size(), hipMemcpyHostToDevice));
       SCHK(launch_tri_factor(v.S, v.g, v.A64, v.tr64, v.tc64, H->err, st));
       if (cfg->prec == SMG_FP32) {

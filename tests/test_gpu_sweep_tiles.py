@@ -76,3 +76,32 @@ def test_block_sweeps_bitexact(shape, prec):
         for _ in range(rep + 1):
             got = _np(mg.op_postsmooth(0, ft, ut, None, torch.empty(f.size, dtype=dt, device=DEV)))
         assert np.array_equal(got, oracle.bgs_sweep(off, Al, D, f, u, -1, 0).ravel()), rep
+
+
+# line sweep: columns around the block of 8 points, the wave of 64 and the
+# longest column of the tiled kernel (128; 129 takes the other one)
+LINE_SHAPES = [(9, 17, 64), (8, 8, 128), (5, 30, 127), (17, 9, 129), (33, 40, 16), (20, 19, 8), (1, 9, 65),
+               (11, 1, 24), (130, 140, 7)]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("pat", [7, 19, 27])
+@pytest.mark.parametrize("shape", LINE_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_line_sweeps_bitexact(shape, pat, prec):
+    A = workloads.random_sgdia(shape, pat, seed=47, symmetric=False)
+    kw = dict(smoother="lgs")
+    H = oracle.Hierarchy(shape, pat, A, prec=prec, **kw)
+    mg = smg.StructMG(torch.from_numpy(A).to(DEV), shape, pattern=pat, prec=prec, **kw, device=DEV)
+    assert H.nlev >= 2
+    off = workloads.offsets(pat)
+    what, npt, dt = (0, np.float64, torch.float64) if prec == "fp64" else (5, np.float32, torch.float32)
+    Al, tr, tc = (H.level_data(0, w).astype(npt) for w in (what, 7, 8))
+    g = workloads.rng(53)
+    f = g.uniform(-1, 1, size=shape).astype(npt)
+    u = g.uniform(-1, 1, size=shape).astype(npt)
+    ft, ut = (torch.from_numpy(v).to(DEV) for v in (f, u))
+    for _ in range(2):
+        got = _np(mg.op_presmooth(0, ft, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.lgs_sweep(off, Al, tr, tc, f, np.zeros(shape, npt), 1, 1).ravel())
+        got = _np(mg.op_postsmooth(0, ft, ut, None, torch.empty(f.size, dtype=dt, device=DEV)))
+        assert np.array_equal(got, oracle.lgs_sweep(off, Al, tr, tc, f, u, -1, 0).ravel())
