@@ -437,7 +437,9 @@ __device__ __forceinline__ void wf_compute(const WfArgs<typename WfVal<E>::V>& a
       // words of the last pack without an entry stay live until here: reused
       // as temporaries they would make their writer wait for every load in
       // flight (27-point FP32: 0.246 instead of 0.15 us per step)
-      if constexpr (wf_loose_pack(PAT, sizeof(E))) asm volatile("" : : "v"(cf[jp][NPK - 1]));
+      // (a unit diagonal leaves the scaling's words unused: 512x512x64 19-point
+      // FP64 L solve 2952 -> 1685 us)
+      if constexpr (UNITD || wf_loose_pack(PAT, sizeof(E))) asm volatile("" : : "v"(cf[jp][NPK - 1]));
       own_prev = xv;
       ring[j * WF_RW + tid] = xv;
       hb[j * WF_HRW] = xv;
