@@ -159,6 +159,9 @@ __global__ __launch_bounds__(HP_NL) void k_hpsweep(Grid g, int nsteps, const int
         V t = hb[b];
 #pragma unroll
         for (int m = 0; m < NT; ++m) t = fma(-hp_get<V>(pc[j], m), xb[b + noff[m]], t);
+        // (words of the last pack without an entry stay live until here: reused
+        // as temporaries they would make their writer wait for every load)
+        if constexpr ((NT + 1) % hp_k<V>() != 0) asm volatile("" : : "v"(pc[j][NPK - 1]));
         xb[b] = t * hp_get<V>(pc[j], NT);
       }
       fetch(k0 + j + HP_P, j);
