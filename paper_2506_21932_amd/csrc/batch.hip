@@ -243,7 +243,7 @@ struct WfGrp {
 // One grouped stencil launch: segments, block map.
 struct Grp {
   int pat = 0;
-  bool small = false;  // small block shape (residual + restriction, prolongation)
+  bool small = false;  // small block shape (prolongation)
   unsigned stage = 0;  // prolongation: LDS-staged coarse values per block
   void* segs = nullptr;
   unsigned* bmap = nullptr;
@@ -251,7 +251,8 @@ struct Grp {
 };
 struct LevelPh {
   WfGrp pre, post;
-  Grp rr, pp;
+  bool split = false;  // residual (res) and restriction (rst) as two launches instead of rr
+  Grp rr, res, rst, pp;
   std::vector<int> sys;  // systems with a smoothing step on this level
 };
 
@@ -342,7 +343,7 @@ size_t layout(smg_batch_s* B, const std::vector<Shape>& sh, char* base) {
   B->lv.assign(std::max(B->maxlev - 1, 0), LevelPh{});
   for (int l = 0; l + 1 < B->maxlev; ++l) {
     LevelPh& L = B->lv[l];
-    long tiles = 0, rrb = 0, ppb = 0;
+    long tiles = 0, rrb = 0, ppb = 0, npts = 0, resb = 0, rstb = 0;
     for (int s = 0; s < ns; ++s) {
       if (l + 1 >= sh[s].nlev) continue;
       const Level& v = sh[s].lev[l];
@@ -352,18 +353,23 @@ size_t layout(smg_batch_s* B, const std::vector<Shape>& sh, char* base) {
       wf_tiling(v.g, v.Ssw, &t1, 1);
       wf_tiling(v.g, v.Ssw, &t2, 2);
       tiles += std::max((long)t1.ntx * t1.nty, (long)t2.ntx * t2.nty);
-      rrb += rr_blocks(v.g, v.cmask, false);
       ppb += pp_blocks(v.g, false);
-      L.pre.pat = L.post.pat = L.rr.pat = L.pp.pat = v.S;
+      npts += v.N;
+      L.pre.pat = L.post.pat = L.rr.pat = L.res.pat = L.pp.pat = v.S;
     }
     // the block shape of a level's grouped launches follows their total size
-    L.rr.small = rr_small((unsigned)rrb);
     L.pp.small = pp_small((unsigned)ppb);
-    rrb = ppb = 0;
+    L.split = npts >= SPLIT_MIN_POINTS;
+    ppb = 0;
     L.pp.stage = 0;
     for (int s : L.sys) {
       const Level& v = sh[s].lev[l];
-      rrb += rr_blocks(v.g, v.cmask, L.rr.small);
+      if (L.split) {
+        resb += spmv_blocks(v.g);
+        rstb += restrict_blocks(v.g, v.cmask, 1);
+      } else {
+        rrb += rr_blocks(v.g, v.cmask);
+      }
       ppb += pp_blocks(v.g, L.pp.small);
       L.pp.stage = std::max(L.pp.stage, pp_stage_elems(v.cmask, L.pp.small));
     }
@@ -372,9 +378,18 @@ size_t layout(smg_batch_s* B, const std::vector<Shape>& sh, char* base) {
     L.post.segs = ar.take<char>(k * SEGB);
     L.pre.tmap = ar.take<unsigned>(tiles);
     L.post.tmap = ar.take<unsigned>(tiles);
-    L.rr.segs = ar.take<char>(k * SEGB);
-    L.rr.bmap = ar.take<unsigned>(rrb);
-    L.rr.nblocks = (unsigned)rrb;
+    if (L.split) {
+      L.res.segs = ar.take<char>(k * SEGB);
+      L.res.bmap = ar.take<unsigned>(resb);
+      L.res.nblocks = (unsigned)resb;
+      L.rst.segs = ar.take<char>(k * SEGB);
+      L.rst.bmap = ar.take<unsigned>(rstb);
+      L.rst.nblocks = (unsigned)rstb;
+    } else {
+      L.rr.segs = ar.take<char>(k * SEGB);
+      L.rr.bmap = ar.take<unsigned>(rrb);
+      L.rr.nblocks = (unsigned)rrb;
+    }
     L.pp.segs = ar.take<char>(k * SEGB);
     L.pp.bmap = ar.take<unsigned>(ppb);
     L.pp.nblocks = (unsigned)ppb;
@@ -488,8 +503,10 @@ hipError_t fill_tables(smg_batch_s* B) {
     LevelPh& L = B->lv[l];
     std::vector<WfArgs<V>> pre, post;
     std::vector<RRArgs<M>> rr;
+    std::vector<SpmvArgs<M>> res;
+    std::vector<RestrictArgs<V>> rst;
     std::vector<PPArgs<M>> pp;
-    std::vector<unsigned> rrb, ppb;
+    std::vector<unsigned> rrb, resb, rstb, ppb;
     L.pre.nt.clear();
     for (int s : L.sys) {
       smg_handle_s* H = B->h[s];
@@ -511,10 +528,17 @@ hipError_t fill_tables(smg_batch_s* B) {
       c.x = UBp<PT>(B, s, l);
       post.push_back(c);
       L.pre.nt.push_back(v.tl.ntx * v.tl.nty);
-      rr.push_back(RRArgs<M>{v.g, v.cmask, PT::A(v), Fp<PT>(B, s, l), (const V*)v.ua, (V*)H->lev[l + 1].f, s});
+      if (L.split) {  // residual into the level's h (free until the upward leg)
+        res.push_back(SpmvArgs<M>{v.g, PT::A(v), (const V*)v.ua, Fp<PT>(B, s, l), (V*)v.h, s});
+        rst.push_back(RestrictArgs<V>{v.g, v.cmask, 1, (const V*)v.h, (V*)H->lev[l + 1].f, s});
+        resb.push_back(spmv_blocks(v.g));
+        rstb.push_back(restrict_blocks(v.g, v.cmask, 1));
+      } else {
+        rr.push_back(RRArgs<M>{v.g, v.cmask, PT::A(v), Fp<PT>(B, s, l), (const V*)v.ua, (V*)H->lev[l + 1].f, s});
+        rrb.push_back(rr_blocks(v.g, v.cmask));
+      }
       pp.push_back(PPArgs<M>{v.g, v.cmask, PT::A(v), Fp<PT>(B, s, l), (const V*)v.ua, (const V*)UBp<PT>(B, s, l + 1),
                              (V*)v.h, nullptr, s});
-      rrb.push_back(rr_blocks(v.g, v.cmask, L.rr.small));
       ppb.push_back(pp_blocks(v.g, L.pp.small));
     }
     L.post.nt = L.pre.nt;
@@ -524,8 +548,12 @@ hipError_t fill_tables(smg_batch_s* B) {
     if ((e = upload_typed(L.pre.segs, pre)) != hipSuccess) return e;
     if ((e = upload_typed(L.post.segs, post)) != hipSuccess) return e;
     if ((e = upload_typed(L.rr.segs, rr)) != hipSuccess) return e;
+    if ((e = upload_typed(L.res.segs, res)) != hipSuccess) return e;
+    if ((e = upload_typed(L.rst.segs, rst)) != hipSuccess) return e;
     if ((e = upload_typed(L.pp.segs, pp)) != hipSuccess) return e;
     if ((e = upload(L.rr.bmap, block_map(rrb))) != hipSuccess) return e;
+    if ((e = upload(L.res.bmap, block_map(resb))) != hipSuccess) return e;
+    if ((e = upload(L.rst.bmap, block_map(rstb))) != hipSuccess) return e;
     if ((e = upload(L.pp.bmap, block_map(ppb))) != hipSuccess) return e;
   }
   if ((e = upload_tile_maps(B)) != hipSuccess) return e;
@@ -578,7 +606,9 @@ hipError_t bvcycle(smg_batch_s* B, const int* gate, hipStream_t st) {
     const LevelPh& L = B->lv[l];
     e = launch_wavefront_group<E>(L.pre.pat, +1, (const WfArgs<V>*)L.pre.segs, (int)L.sys.size(), L.pre.tmap, L.pre.total, B->grid,
                                   gate, B->ctr, B->err, st);
-    if (e == hipSuccess) e = launch_rr_group<M>(L.rr.pat, L.rr.small, (const RRArgs<M>*)L.rr.segs, L.rr.bmap, L.rr.nblocks, gate, st);
+    if (e == hipSuccess) e = launch_rr_group<M>(L.rr.pat, (const RRArgs<M>*)L.rr.segs, L.rr.bmap, L.rr.nblocks, gate, st);
+    if (e == hipSuccess) e = launch_spmv_group<M>(L.res.pat, true, (const SpmvArgs<M>*)L.res.segs, L.res.bmap, L.res.nblocks, gate, st);
+    if (e == hipSuccess) e = launch_restrict_group<V>((const RestrictArgs<V>*)L.rst.segs, L.rst.bmap, L.rst.nblocks, gate, st);
     if (e != hipSuccess) return e;
   }
   e = launch_gemv_group<V>((const GemvArgs<V>*)B->gemv.segs, B->gemv.bmap, B->gemv.nblocks, gate, st);

@@ -124,6 +124,15 @@ struct RRArgs {
   typename M::V* rc;
   int sys;
 };
+template <class V>
+struct RestrictArgs {
+  Grid g;
+  int cmask;
+  int bs;
+  const V* rf;
+  V* rc;
+  int sys;
+};
 template <class M>
 struct PPArgs {
   Grid g;
@@ -146,21 +155,33 @@ struct GemvArgs {
   int sys;
 };
 unsigned spmv_blocks(const Grid& g);
-// residual + restriction and prolongation: large or small blocks (chosen by
-// rr_small / pp_small from the large-block count of one grid or a group)
-unsigned rr_blocks(const Grid& g, int cmask, bool small);
+// Scalar levels of at least this many points (a level's systems together in a
+// batch) run the residual + restriction as two plain passes (more workgroups,
+// no halo recomputation); smaller levels use the fused one-launch kernel,
+// whose single launch costs less there.  Single levels do the same with the
+// prolongation + lower-triangle terms.  Both forms give identical bits.
+// Measured in a batch of 256 systems, FP32, fused against two passes: 44M
+// 7-point rows 762 against 493 + 57 us, 10.8M 27-point rows 693 against 372 and
+// under 15, 0.74M 27-point rows 52 against 35 and under 15.
+constexpr long SPLIT_MIN_POINTS = 1L << 17;
+unsigned rr_blocks(const Grid& g, int cmask);
+// prolongation: large or small blocks (chosen by pp_small from the
+// large-block count of one grid or a group)
 unsigned pp_blocks(const Grid& g, bool small);
-bool rr_small(unsigned big_blocks);
 bool pp_small(unsigned big_blocks);
 // coarse values staged in LDS by one prolongation block (grid's mask)
 unsigned pp_stage_elems(int cmask, bool small);
+unsigned restrict_blocks(const Grid& g, int cmask, int bs);
 unsigned gemv_blocks(int n);
 template <class M>
 hipError_t launch_spmv_group(int pat, bool res, const SpmvArgs<M>* segs, const unsigned* bmap, unsigned nblocks,
                              const int* live, hipStream_t st);
 template <class M>
-hipError_t launch_rr_group(int pat, bool small, const RRArgs<M>* segs, const unsigned* bmap, unsigned nblocks,
+hipError_t launch_rr_group(int pat, const RRArgs<M>* segs, const unsigned* bmap, unsigned nblocks,
                            const int* live, hipStream_t st);
+template <class V>
+hipError_t launch_restrict_group(const RestrictArgs<V>* segs, const unsigned* bmap, unsigned nblocks, const int* live,
+                                 hipStream_t st);
 // stage_elems: the largest pp_stage_elems of the segments (0 when every ec is null)
 template <class M>
 hipError_t launch_pp_group(int pat, bool full, bool small, unsigned stage_elems, const PPArgs<M>* segs,

@@ -166,24 +166,19 @@ hipError_t launch_upper(int pat, const Grid& g, const M& m, const typename M::V*
 }
 
 // ------------------------------------------------ residual + restriction
-// One workgroup per coarse block of RB_X x RB_Y x RB_Z coarse points.
+// One workgroup per coarse block of RB_X x RB_Y x RB_Z coarse points, for
+// levels (and groups of levels) below SPLIT_MIN_POINTS.
 // Phase 1 computes the fine residuals of the block's footprint into LDS;
 // phase 2 restricts them.  A residual shared by two blocks is recomputed
-// (identically) by both.
-// Coarse block per workgroup: 4 x 4 x 16 on large levels; 2 x 2 x 4 where
-// the large blocks would leave most compute units idle (small levels), so
-// that each thread computes about one residual and the kernel's latency is
-// one round of loads.  Results do not depend on the block shape.
-template <bool SMALL>
-struct RBT {
-  static constexpr int X = SMALL ? 2 : 4, Y = SMALL ? 2 : 4, Z = SMALL ? 4 : 16;
-};
+// (identically) by both.  The small block spreads a small level over the
+// compute units, each thread computing about one residual, so that the
+// kernel's latency is one round of loads.
+constexpr int RB_X = 2, RB_Y = 2, RB_Z = 4;
 
 __host__ __device__ inline int rr_ext(int cm, int cb) { return cm ? 2 * cb + 1 : cb; }
 
-template <int PAT, class M, bool SMALL>
+template <int PAT, class M>
 struct RROp {
-  static constexpr int RB_X = RBT<SMALL>::X, RB_Y = RBT<SMALL>::Y, RB_Z = RBT<SMALL>::Z;
   using Args = RRArgs<M>;
   __device__ static void run(const Args& a, unsigned bid_) {
   const Grid gf = a.g;
@@ -237,30 +232,20 @@ struct RROp {
   }
 };
 
-template <bool SMALL>
-static unsigned rr_blocks_t(const Grid& g, int cmask) {
-  constexpr int BX = RBT<SMALL>::X, BY = RBT<SMALL>::Y, BZ = RBT<SMALL>::Z;
+unsigned rr_blocks(const Grid& g, int cmask) {
   const int cx = (cmask & 1) ? g.nx / 2 : g.nx, cy = (cmask & 2) ? g.ny / 2 : g.ny, cz = (cmask & 4) ? g.nz / 2 : g.nz;
-  return (unsigned)(((cx + BX - 1) / BX) * ((cy + BY - 1) / BY) * ((cz + BZ - 1) / BZ));
+  return (unsigned)(((cx + RB_X - 1) / RB_X) * ((cy + RB_Y - 1) / RB_Y) * ((cz + RB_Z - 1) / RB_Z));
 }
-unsigned rr_blocks(const Grid& g, int cmask, bool small) {
-  return small ? rr_blocks_t<true>(g, cmask) : rr_blocks_t<false>(g, cmask);
-}
-bool rr_small(unsigned big_blocks) { return big_blocks < 1024; }
 
 template <class M>
 hipError_t launch_resid_restrict(int pat, const Grid& g, int cmask, const M& m, const typename M::V* f,
                                  const typename M::V* u, typename M::V* rc, hipStream_t st) {
   const RRArgs<M> a{g, cmask, m, f, u, rc, 0};
-  const bool small = rr_small(rr_blocks(g, cmask, false));
-  const unsigned nb = rr_blocks(g, cmask, small);
-#define SMG_RR(P)                                                                          \
-  if (pat == P) {                                                                          \
-    if (small)                                                                             \
-      hipLaunchKernelGGL((k_one_xcd<RROp<P, M, true>>), dim3(nb), dim3(256), 0, st, a);       \
-    else                                                                                   \
-      hipLaunchKernelGGL((k_one_xcd<RROp<P, M, false>>), dim3(nb), dim3(256), 0, st, a);      \
-    return hipGetLastError();                                                              \
+  const unsigned nb = rr_blocks(g, cmask);
+#define SMG_RR(P)                                                                    \
+  if (pat == P) {                                                                    \
+    hipLaunchKernelGGL((k_one_xcd<RROp<P, M>>), dim3(nb), dim3(256), 0, st, a);      \
+    return hipGetLastError();                                                        \
   }
   SMG_RR(7)
   SMG_RR(19)
@@ -270,16 +255,13 @@ hipError_t launch_resid_restrict(int pat, const Grid& g, int cmask, const M& m, 
 }
 
 template <class M>
-hipError_t launch_rr_group(int pat, bool small, const RRArgs<M>* segs, const unsigned* bmap, unsigned nblocks,
-                           const int* live, hipStream_t st) {
+hipError_t launch_rr_group(int pat, const RRArgs<M>* segs, const unsigned* bmap, unsigned nblocks, const int* live,
+                           hipStream_t st) {
   if (nblocks == 0) return hipSuccess;
-#define SMG_RR(P)                                                                                              \
-  if (pat == P) {                                                                                              \
-    if (small)                                                                                                 \
-      hipLaunchKernelGGL((k_group<RROp<P, M, true>>), dim3(nblocks), dim3(256), 0, st, segs, bmap, live);     \
-    else                                                                                                       \
-      hipLaunchKernelGGL((k_group<RROp<P, M, false>>), dim3(nblocks), dim3(256), 0, st, segs, bmap, live);    \
-    return hipGetLastError();                                                                                  \
+#define SMG_RR(P)                                                                                      \
+  if (pat == P) {                                                                                      \
+    hipLaunchKernelGGL((k_group<RROp<P, M>>), dim3(nblocks), dim3(256), 0, st, segs, bmap, live);      \
+    return hipGetLastError();                                                                          \
   }
   SMG_RR(7)
   SMG_RR(19)
@@ -516,29 +498,62 @@ hipError_t launch_pp_group(int pat, bool full, bool small, unsigned stage_elems,
 }
 
 // -------------------------------------- plain restriction / prolongation
-template <class V>
-__global__ __launch_bounds__(256) void k_restrict(Grid gf, int cmask, int bs, const V* __restrict__ rf,
-                                                  V* __restrict__ rc) {
-  const int cmx = cmask & 1, cmy = (cmask >> 1) & 1, cmz = (cmask >> 2) & 1;
-  const Grid gc{cmx ? gf.nx / 2 : gf.nx, cmy ? gf.ny / 2 : gf.ny, cmz ? gf.nz / 2 : gf.nz};
-  const unsigned k = blockIdx.x * 256u + threadIdx.x;
-  if (k >= (unsigned)(gc.N() * bs)) return;
-  const unsigned ic = k / bs;
-  const int comp = k % bs;
-  int Xc, Yc, Z;
-  unflat(ic, gc.ny, gc.nz, Xc, Yc, Z);
-  const int fx0 = cmx ? 2 * Xc + 1 : Xc, fy0 = cmy ? 2 * Yc + 1 : Yc, fz0 = cmz ? 2 * Z + 1 : Z;
-  V acc = V(0);
+// Restriction of one value: the fine neighbours' values, loaded together
+// (row r of the 27 clamped to the fine point itself where it is off the grid:
+// only the upper neighbour of a coarsened axis can be), then the sum in
+// canonical order over those that exist.  Bound by the latency of its loads:
+// one load per step of a rolled loop took 289 us for 44M fine FP32 points
+// (256 systems), where the data alone take 50; loaded together 57.
+template <class V, int CM>
+__device__ inline V restrict_value(const Grid& gf, int bs, const V* __restrict__ rf, int Xc, int Yc, int Zc) {
+  constexpr int cmx = CM & 1, cmy = (CM >> 1) & 1, cmz = (CM >> 2) & 1;
+  const int fx = cmx ? 2 * Xc + 1 : Xc, fy = cmy ? 2 * Yc + 1 : Yc, fz = cmz ? 2 * Zc + 1 : Zc;
+  const bool ux = fx + 1 < gf.nx, uy = fy + 1 < gf.ny, uz = fz + 1 < gf.nz;
+  const long sy = (long)gf.nz * bs, sx = sy * gf.ny;
+  const V* __restrict__ c = rf + fx * sx + fy * sy + (long)fz * bs;
+  V v[27];
+#pragma unroll
   for (int r = 0; r < 27; ++r) {
     const int dx = r / 9 - 1, dy = (r / 3) % 3 - 1, dz = r % 3 - 1;
     if ((!cmx && dx) || (!cmy && dy) || (!cmz && dz)) continue;
-    const int ux = fx0 + dx, uy = fy0 + dy, uz = fz0 + dz;
-    if (!in_grid(gf, ux, uy, uz)) continue;
-    const V w = V((dx ? 0.5 : 1.0) * (dy ? 0.5 : 1.0) * (dz ? 0.5 : 1.0));
-    acc = fma(w, rf[(((long)ux * gf.ny + uy) * gf.nz + uz) * bs + comp], acc);
+    const bool ok = (dx < 1 || ux) && (dy < 1 || uy) && (dz < 1 || uz);
+    v[r] = c[ok ? dx * sx + dy * sy + dz * bs : 0];
   }
-  rc[k] = acc;
+  V acc = V(0);
+#pragma unroll
+  for (int r = 0; r < 27; ++r) {
+    const int dx = r / 9 - 1, dy = (r / 3) % 3 - 1, dz = r % 3 - 1;
+    if ((!cmx && dx) || (!cmy && dy) || (!cmz && dz)) continue;
+    const bool ok = (dx < 1 || ux) && (dy < 1 || uy) && (dz < 1 || uz);
+    const V w = V((dx ? 0.5 : 1.0) * (dy ? 0.5 : 1.0) * (dz ? 0.5 : 1.0));
+    acc = ok ? fma(w, v[r], acc) : acc;
+  }
+  return acc;
 }
+
+template <class V>
+struct RestrictOp {
+  using Args = RestrictArgs<V>;
+  __device__ static void run(const Args& a, unsigned bid) {
+    const Grid gf = a.g;
+    const int cmask = a.cmask, bs = a.bs;
+    const V* __restrict__ rf = a.rf;
+    const Grid gc{cmask & 1 ? gf.nx / 2 : gf.nx, cmask & 2 ? gf.ny / 2 : gf.ny, cmask & 4 ? gf.nz / 2 : gf.nz};
+    const unsigned k = bid * 256u + threadIdx.x;
+    if (k >= (unsigned)(gc.N() * bs)) return;
+    const unsigned ic = bs == 1 ? k : k / (unsigned)bs;
+    rf += k - ic * (unsigned)bs;  // component
+    int Xc, Yc, Z;
+    unflat(ic, gc.ny, gc.nz, Xc, Yc, Z);
+    V acc = V(0);
+    switch (cmask) {
+#define SMG_CM(m) case m: acc = restrict_value<V, m>(gf, bs, rf, Xc, Yc, Z); break;
+      SMG_CM(0) SMG_CM(1) SMG_CM(2) SMG_CM(3) SMG_CM(4) SMG_CM(5) SMG_CM(6) SMG_CM(7)
+#undef SMG_CM
+    }
+    a.rc[k] = acc;
+  }
+};
 
 template <class V>
 __global__ __launch_bounds__(256) void k_prolong_add(Grid gf, int cmask, int bs, const V* __restrict__ ec,
@@ -554,11 +569,22 @@ __global__ __launch_bounds__(256) void k_prolong_add(Grid gf, int cmask, int bs,
   uf[k] = uf[k] + interp_point(ec, gc, cmx, cmy, cmz, X, Y, Z, bs, comp);
 }
 
-template <class V>
-hipError_t launch_restrict(const Grid& g, int cmask, int bs, const V* rf, V* rc, hipStream_t st) {
+unsigned restrict_blocks(const Grid& g, int cmask, int bs) {
   const long nc = (long)((cmask & 1) ? g.nx / 2 : g.nx) * ((cmask & 2) ? g.ny / 2 : g.ny) *
                   ((cmask & 4) ? g.nz / 2 : g.nz) * bs;
-  hipLaunchKernelGGL((k_restrict<V>), dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, g, cmask, bs, rf, rc);
+  return (unsigned)((nc + 255) / 256);
+}
+template <class V>
+hipError_t launch_restrict(const Grid& g, int cmask, int bs, const V* rf, V* rc, hipStream_t st) {
+  const RestrictArgs<V> a{g, cmask, bs, rf, rc, 0};
+  hipLaunchKernelGGL((k_one<RestrictOp<V>>), dim3(restrict_blocks(g, cmask, bs)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+template <class V>
+hipError_t launch_restrict_group(const RestrictArgs<V>* segs, const unsigned* bmap, unsigned nblocks, const int* live,
+                                 hipStream_t st) {
+  if (nblocks == 0) return hipSuccess;
+  hipLaunchKernelGGL((k_group<RestrictOp<V>>), dim3(nblocks), dim3(256), 0, st, segs, bmap, live);
   return hipGetLastError();
 }
 template <class V>
@@ -582,8 +608,7 @@ SMG_INST(MatH)
 #define SMG_GINST(M)                                                                                           \
   template hipError_t launch_spmv_group<M>(int, bool, const SpmvArgs<M>*, const unsigned*, unsigned, const int*, \
                                            hipStream_t);                                                       \
-  template hipError_t launch_rr_group<M>(int, bool, const RRArgs<M>*, const unsigned*, unsigned, const int*,     \
-                                         hipStream_t);                                                         \
+  template hipError_t launch_rr_group<M>(int, const RRArgs<M>*, const unsigned*, unsigned, const int*, hipStream_t);  \
   template hipError_t launch_pp_group<M>(int, bool, bool, unsigned, const PPArgs<M>*, const unsigned*, unsigned, \
                                          const int*, hipStream_t);
 SMG_GINST(MatD)
@@ -600,6 +625,10 @@ template hipError_t launch_upper<MatF>(int, const Grid&, const MatF&, const floa
 template hipError_t launch_upper<MatH>(int, const Grid&, const MatH&, const float*, const float*, float*, hipStream_t);
 template hipError_t launch_restrict<double>(const Grid&, int, int, const double*, double*, hipStream_t);
 template hipError_t launch_restrict<float>(const Grid&, int, int, const float*, float*, hipStream_t);
+template hipError_t launch_restrict_group<double>(const RestrictArgs<double>*, const unsigned*, unsigned, const int*,
+                                                  hipStream_t);
+template hipError_t launch_restrict_group<float>(const RestrictArgs<float>*, const unsigned*, unsigned, const int*,
+                                                 hipStream_t);
 template hipError_t launch_prolong_add<double>(const Grid&, int, int, const double*, double*, hipStream_t);
 template hipError_t launch_prolong_add<float>(const Grid&, int, int, const float*, float*, hipStream_t);
 

@@ -369,12 +369,6 @@ hipError_t bvcycle_t(smg_handle_s* H, const typename PT::V* f0, typename PT::V* 
   return hipSuccess;
 }
 
-// Scalar levels of at least this many points run the residual + restriction
-// and the prolongation + lower-triangle terms as two plain passes each (more
-// workgroups, no halo recomputation); smaller levels use the fused one-launch
-// kernels, whose single launch costs less there.  Both forms give identical
-// bits.
-constexpr long SPLIT_MIN_POINTS = 1L << 17;
 static bool split_rp(const Level& v) { return v.N >= SPLIT_MIN_POINTS; }
 
 // One line GS sweep on level v: x = LGS(f) from the values uold (null: zero
