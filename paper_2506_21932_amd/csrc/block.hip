@@ -640,18 +640,23 @@ __global__ __launch_bounds__(BW_THREADS) void k_bwavefront(WfArgs<typename WfVal
   V* const strip = a.strip + (tk.par & 1u ? half : 0l);
   V* const other = a.strip + (tk.par & 1u ? 0l : half);
   unsigned ticket;
+  auto take = [&] {
+    if (!tk.take(&ticket)) return false;
+    if (!tk.single) ticket = sweep_tile(ticket, a.t.sh, a.t.ntx, a.t.nty);
+    return true;
+  };
   auto tile = [&] { return DIR > 0 ? ticket : tk.ntiles - 1u - ticket; };
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   if (wave < BW_NCW) {
-    while (tk.take(&ticket)) bw_compute<DIR, P, E>(a, bw_geo(a, tile()), tile(), L.ring, L.hbuf);
+    while (take()) bw_compute<DIR, P, E>(a, bw_geo(a, tile()), tile(), L.ring, L.hbuf);
   } else if (wave == BW_NCW) {
-    while (tk.take(&ticket)) bw_halo<DIR, V>(a, bw_geo(a, tile()), strip, L.ring, a.err);
+    while (take()) bw_halo<DIR, V>(a, bw_geo(a, tile()), strip, L.ring, a.err);
   } else if (wave == BW_NCW + 1) {
-    while (tk.take(&ticket)) bw_load<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
+    while (take()) bw_load<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
   } else if (wave == BW_NCW + 2) {
-    while (tk.take(&ticket)) bw_store<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
+    while (take()) bw_store<DIR, V>(a, bw_geo(a, tile()), L.hbuf);
   } else {
-    while (tk.take(&ticket)) bw_export<DIR, V>(a, bw_geo(a, tile()), tile(), strip, other, L.ring);
+    while (take()) bw_export<DIR, V>(a, bw_geo(a, tile()), tile(), strip, other, L.ring);
   }
 }
 

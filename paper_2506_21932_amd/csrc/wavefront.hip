@@ -832,7 +832,9 @@ __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<
     unsigned ticket;
     if (!tk.take(&ticket)) return false;
     w->a = a;
-    w->tile = DIR > 0 ? ticket : tk.ntiles - 1u - ticket;
+    // (one tile per workgroup: all are resident, any order will do)
+    const unsigned r = tk.single ? ticket : sweep_tile(ticket, a.t.sh, a.t.ntx, a.t.nty);
+    w->tile = DIR > 0 ? r : tk.ntiles - 1u - r;
     w->par = tk.par;
     return true;
   };
