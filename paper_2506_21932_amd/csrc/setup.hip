@@ -297,10 +297,22 @@ __device__ __forceinline__ void ilu_rows(double (&w)[PAT], const Grid& g, long i
 // Threads cover only the points that can meet the hyperplane: the x range
 // [x0, x0 + nxr) where it crosses the grid, and for each x the kb = nz / wy + 2
 // largest y with z = tau - wx*x - wy*y >= 0.  The rows of one hyperplane are
-// scattered in memory (every load of a wave touches 64 lines), so the launch
-// uses one-wave workgroups to spread them over all compute units.
+// scattered in memory (every lane of a load touches a line of its own), so
+// the launch uses workgroups of one wave, partly filled (ilu_lanes).
 __host__ __device__ constexpr int ilu_band(int nz, int wy) { return nz / wy + 2; }
 constexpr int ILU_WG = 64;
+
+// Threads per workgroup: as few as 8, so that a hyperplane spreads over the
+// chip.  A row makes about 230 accesses to lines of its own, which a compute
+// unit serves one line after another: 64 rows on one unit took 11.3 us per
+// hyperplane (27 points, 150x133x41 and its coarse levels) and 8.7 us (19
+// points), 8 rows take 7.0 and 5.4; 16 rows 7.1 and 5.4, 4 rows 7.2 and 6.0.
+// Beyond 512 workgroups the units are shared anyway and waves fill up.
+static int ilu_lanes(int slots) {
+  int wl = 8;
+  while (wl < ILU_WG && slots > wl * 512) wl *= 2;
+  return wl;
+}
 
 // x range [x0, x0 + nxr) of the points on hyperplane tau (nxr <= 0: none)
 __host__ __device__ inline void ilu_xrange(const Grid& g, int wx, int wy, int tau, int* x0, int* nxr) {
@@ -363,7 +375,7 @@ __global__ __launch_bounds__(ILU_WG) __attribute__((amdgpu_waves_per_eu(1, 1))) 
   const int kb = ilu_band(g.nz, WY);
   int X, Y, Z;
   // neighbouring band slots read overlapping U lines: keep them on one XCD
-  const unsigned slot = xcd_block(blockIdx.x, gridDim.x) * (unsigned)ILU_WG + threadIdx.x;
+  const unsigned slot = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   if (!ilu_point<WX, WY>(g, tau, x0, nxr, kb, (int)slot, X, Y, Z)) return;
   const long i = ((long)X * g.ny + Y) * g.nz + Z;
   const IluNb nb{X > 0, X < g.nx - 1, Y > 0, Y < g.ny - 1, Z > 0, Z < g.nz - 1};
@@ -437,7 +449,8 @@ static hipError_t launch_ilu0_t(const Grid& g, const double* A, double* L, doubl
     int x0, nxr;
     ilu_xrange(g, wx, wy, tau, &x0, &nxr);
     if (nxr <= 0) continue;
-    const dim3 grid((unsigned)((nxr * kb + ILU_WG - 1) / ILU_WG)), blk(ILU_WG);
+    const int wl = ilu_lanes(nxr * kb);
+    const dim3 grid((unsigned)((nxr * kb + wl - 1) / wl)), blk(wl);
     hipLaunchKernelGGL((k_ilu0_plane<PAT, PA>), grid, blk, 0, st, g, tau, x0, nxr, A, L, U, rU, err);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
