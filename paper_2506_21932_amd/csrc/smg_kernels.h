@@ -160,9 +160,10 @@ unsigned spmv_blocks(const Grid& g);
 // no halo recomputation); smaller levels use the fused one-launch kernel,
 // whose single launch costs less there.  Single levels do the same with the
 // prolongation + lower-triangle terms.  Both forms give identical bits.
-// Measured in a batch of 256 systems, FP32, fused against two passes: 44M
-// 7-point rows 762 against 493 + 57 us, 10.8M 27-point rows 693 against 372 and
-// under 15, 0.74M 27-point rows 52 against 35 and under 15.
+// Measured in a batch of 256 systems, FP32, fused (its loads then behind
+// branches) against two passes: 44M 7-point rows 762 against 344 + 57 us,
+// 10.8M 27-point rows 693 against 257 and under 15, 0.74M 27-point rows 52
+// against 19 and under 15.  Below, a fused launch takes 7 us, two take 7 + 4.
 constexpr long SPLIT_MIN_POINTS = 1L << 17;
 unsigned rr_blocks(const Grid& g, int cmask);
 // prolongation: large or small blocks (chosen by pp_small from the
