@@ -302,17 +302,16 @@ __device__ __forceinline__ void ilu_rows(double (&w)[PAT], const Grid& g, long i
 __host__ __device__ constexpr int ilu_band(int nz, int wy) { return nz / wy + 2; }
 constexpr int ILU_WG = 64;
 
-// Threads per workgroup: as few as 8, so that a hyperplane spreads over the
-// chip.  A row makes about 230 accesses to lines of its own, which a compute
-// unit serves one line after another: 64 rows on one unit took 11.3 us per
-// hyperplane (27 points, 150x133x41 and its coarse levels) and 8.7 us (19
-// points), 8 rows take 7.0 and 5.4; 16 rows 7.1 and 5.4, 4 rows 7.2 and 6.0.
-// Beyond 512 workgroups the units are shared anyway and waves fill up.
-static int ilu_lanes(int slots) {
-  int wl = 8;
-  while (wl < ILU_WG && slots > wl * 512) wl *= 2;
-  return wl;
-}
+// Threads per workgroup: 8, so that a hyperplane spreads over the chip, up to
+// 1024 workgroups, then full waves.  A row makes about 230 accesses to lines
+// of its own, which a compute unit serves one line after another: 64 rows on
+// one unit took 11.3 us per hyperplane (27 points, 150x133x41 and its coarse
+// levels) and 8.7 us (19 points), 8 rows take 7.0 and 5.4; 16 rows 7.1 and
+// 5.4, 4 rows 7.2 and 6.0.  Where the units are full anyway, rows of a wave
+// that share lines count more: 8 / 16 / 32 / 64 rows take 12.3 / 11.8 / - /
+// 13.4 us at 6-8 thousand points of the band (512x512x64, 19 points), - / 16.6
+// / 17.4 / 15.5 at 8-10 and - / 18.6 / 20.7 / 17.3 at 10-12 thousand.
+static int ilu_lanes(int slots) { return slots <= 8192 ? 8 : ILU_WG; }
 
 // x range [x0, x0 + nxr) of the points on hyperplane tau (nxr <= 0: none)
 __host__ __device__ inline void ilu_xrange(const Grid& g, int wx, int wy, int tau, int* x0, int* nxr) {
