@@ -68,7 +68,7 @@ def kernel_bytes(kind, S, N, Nc, w, smoother="gs", ncoarse=0, interp="vertex"):
 
 def wavefront_src_hash():
     h = hashlib.sha256()
-    for f in ("wavefront.hip", "stencil.hip", "smg_common.h", "smg_group.h", "smg_kernels.h"):
+    for f in ("wavefront.hip", "stencil.hip", "smg_common.h", "smg_group.h", "smg_kernels.h", "smg_sweep.h"):
         with open(os.path.join(ROOT, "paper_2506_21932_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
