@@ -46,8 +46,11 @@
 //    buffers (one filled, one computed, one drained).
 //  * Inactive positions (a column outside the grid, or z outside [0, nz) at
 //    that step) have zero coefficients, scaling and right-hand side, so
-//    their result is zero without a test: the LDS is zeroed once per launch
-//    and every value in it stays finite.
+//    their result is zero without a test as long as every value they read is
+//    finite: the LDS is zeroed once per launch.  In a grouped launch the tile
+//    before may be another system's, whose values overflowed (a zero
+//    coefficient does not stop those), so the ring rows that a tile reads
+//    before it writes them are zeroed ahead of it.
 //  * Tiles exchange values through strips: per step a tile writes the values
 //    of the columns that others read (23 of 128, 30 with 19/27 points) as one
 //    contiguous run, device-coherently.  A hyperplane has one step number per
@@ -785,6 +788,13 @@ __device__ inline void wf_zero_lds(WfLds<V>* L) {
   __syncthreads();
 }
 
+// The last KB rows of the ring stand for the steps before a tile's first: the
+// only values of the tile before that a tile reads.
+template <int PAT, class V>
+__device__ inline void wf_clear_history(V* ring) {
+  for (int i = threadIdx.x; i < wf_kb(PAT) * WF_RW; i += WF_THREADS) ring[(WF_HIST - wf_kb(PAT)) * WF_RW + i] = V(0);
+}
+
 // What a workgroup sweeps next: a tile of a grid and the grid's strip buffer
 // (0 or 1) of this sweep.
 template <class V>
@@ -869,6 +879,9 @@ __global__ __launch_bounds__(WF_THREADS, PAT == 27 && sizeof(E) == 8 ? 2 : 3) vo
       const unsigned r = e & 0xFFFFFu, nt = (unsigned)(w->a.t.ntx * w->a.t.nty);
       w->tile = DIR > 0 ? r : nt - 1u - r;
       w->par = __builtin_amdgcn_readfirstlane(*w->a.par);
+      // (behind the ticket's barriers no wave is in a tile, and the roles start
+      // with one)
+      wf_clear_history<PAT>(L.ring);
       return true;
     }
   };
