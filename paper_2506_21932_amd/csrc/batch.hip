@@ -737,6 +737,18 @@ smg_status smg_batch_workspace_size(int nsys, const smg_config* cfgs, size_t* by
     if (b == 0) return bfail(nullptr, SMG_EINVAL, "system %d: coarsest level too large", s);
     if ((sh[s].lev[0].N + BV - 1) / BV >= MAXMAP || spmv_blocks(sh[s].lev[0].g) >= MAXMAP)
       return bfail(nullptr, SMG_EINVAL, "system %d: grid too large for a batch", s);
+    // (flat grids: a prolongation block of 8 x 8 x 32 or a sweep tile of 8 x 16
+    // columns may hold few points)
+    for (int l = 0; l + 1 < sh[s].nlev; ++l) {
+      const Level& v = sh[s].lev[l];
+      long most = pp_blocks(v.g, false);
+      for (int shape = 1; shape <= 2; ++shape) {
+        WfTiling t;
+        wf_tiling(v.g, v.Ssw, &t, shape);
+        most = std::max(most, (long)t.ntx * t.nty);
+      }
+      if (most > MAXMAP) return bfail(nullptr, SMG_EINVAL, "system %d: grid too large for a batch", s);
+    }
     total += (b + 255) & ~(size_t)255;
   }
   smg_batch_s tmp;
