@@ -42,6 +42,7 @@
 //      reads are complete.
 // Waits are bounded: after LGS_SPIN_LIMIT polls, bit 0 of err is set and
 // every waiting lane gives up.
+#include <algorithm>
 #include <utility>
 #include <vector>
 
@@ -721,8 +722,10 @@ static int lgs_tiles(const Grid& g, int pat, int k, std::vector<int>* tmap) {
   const int sh = lgs_cwx(pat) - 1;
   const int ntx = (g.nx + k - 1) / k, nty = (g.ny + sh * (g.nx - 1) + k - 1) / k;
   int n = 0;
-  for (int d = 0; d < ntx + nty - 1; ++d)
-    for (int bx = 0; bx < ntx; ++bx) {
+  for (int d = 0; d < ntx + nty - 1; ++d) {
+    // (only these bx can hold a column: sh*bx <= by <= sh*(bx + 1) + (ny - 1) / k)
+    const int b0 = std::max((d - sh - (g.ny - 1) / k) / (1 + sh) - 1, 0), b1 = std::min(d / (1 + sh) + 1, ntx - 1);
+    for (int bx = b0; bx <= b1; ++bx) {
       const int by = d - bx;
       if (by < 0 || by >= nty) continue;
       // the tile holds a column if some x of it has y = y' - sh*x in [0, ny)
@@ -735,6 +738,7 @@ static int lgs_tiles(const Grid& g, int pat, int k, std::vector<int>* tmap) {
       if (tmap) tmap->push_back((bx << 16) | by);
       ++n;
     }
+  }
   return n;
 }
 
