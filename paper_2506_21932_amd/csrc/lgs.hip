@@ -742,9 +742,19 @@ static int lgs_tiles(const Grid& g, int pat, int k, std::vector<int>* tmap) {
   return n;
 }
 
+static int lgs_points(const Grid& g, int vbytes) {
+  return g.nz > LT_MAX_NZ ? LGS_PTS : (vbytes == 4 ? lt_pts<float>() : lt_pts<double>());
+}
+
 int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap) {
-  *K = lgs_side(g, g.nz > LT_MAX_NZ ? LGS_PTS : (vbytes == 4 ? lt_pts<float>() : lt_pts<double>()));
+  *K = lgs_side(g, lgs_points(g, vbytes));
   return lgs_tiles(g, pat, *K, tmap);
+}
+
+// A tile's entry in the table: bx above bit 16 of a signed word, by below.
+bool lgs_ranges_ok(const Grid& g, int pat, int vbytes) {
+  const int sh = lgs_cwx(pat) - 1, k = lgs_side(g, lgs_points(g, vbytes));
+  return (g.nx - 1) / k < 1 << 15 && ((long)g.ny - 1 + (long)sh * (g.nx - 1)) / k < 1 << 16;
 }
 
 // (the smaller tiles of every precision, so that the workspace does not

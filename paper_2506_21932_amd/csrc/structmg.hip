@@ -105,6 +105,9 @@ const char* check_cfg(const smg_config* c) {
   if (c->smoother == SMG_SMOOTH_LGS && c->block != 1) return "line GS is implemented for scalar systems";
   if (c->smoother == SMG_SMOOTH_LGS && c->prec == SMG_FP16_ROWSCALE) return "line GS supports FP64 and FP32";
   if (c->smoother == SMG_SMOOTH_LGS && c->nz > LGS_MAX_NZ) return "line GS: nz too large (limit 2047)";
+  // (coarser levels have fewer columns and no smaller tiles)
+  if (c->smoother == SMG_SMOOTH_LGS && !lgs_ranges_ok(Grid{c->nx, c->ny, c->nz}, c->pattern, c->prec == SMG_FP64 ? 8 : 4))
+    return "line GS: nx or ny too large";
   if (c->smoother == SMG_SMOOTH_ILU0 && c->block != 1) return "ILU(0) is implemented for scalar systems";
   if (c->smoother == SMG_SMOOTH_ILU0 && c->prec == SMG_FP16_ROWSCALE) return "ILU(0) supports FP64 and FP32";
   if (c->coarsen != SMG_COARSEN_FULL && c->coarsen != SMG_COARSEN_SEMI_XY && c->coarsen != SMG_COARSEN_AUTO)
