@@ -29,12 +29,21 @@ __device__ inline void unflat(unsigned i, int ny, int nz, int& x, int& y, int& z
 // memory round trip each, which bounds levels too small to hide it with other
 // waves.  Before / after: 27-point FP64 levels of a few thousand points 15 / 7
 // us, 10.8M 27-point FP32 rows of a batch 372 / 257 us, 44M 7-point FP32 rows
-// 493 / 344 us; 128^3 27-point FP64 98 / 108 us.
-template <int PAT, class M>
+// 493 / 344 us.  WALK keeps the branches, for the launches of spmv_walk.
+template <int PAT, bool WALK, class M>
 __device__ __forceinline__ typename M::V spmv_row(const Grid& g, const M& m, const typename M::V* __restrict__ x,
                                                   int X, int Y, int Z, long i) {
   using V = typename M::V;
   const long nyz = (long)g.ny * g.nz;
+  V acc = V(0);
+  if constexpr (WALK) {
+#pragma unroll
+    for (int s = 0; s < PAT; ++s) {
+      const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1), dz = pat_off(PAT, s, 2);
+      if (in_grid(g, X + dx, Y + dy, Z + dz)) acc = fma(m(s, i), x[i + dx * nyz + dy * g.nz + dz], acc);
+    }
+    return acc;
+  }
   V c[PAT], xv[PAT];
 #pragma unroll
   for (int s = 0; s < PAT; ++s) {
@@ -43,7 +52,6 @@ __device__ __forceinline__ typename M::V spmv_row(const Grid& g, const M& m, con
     c[s] = m(s, i);
     xv[s] = x[ok ? i + dx * nyz + dy * g.nz + dz : i];
   }
-  V acc = V(0);
 #pragma unroll
   for (int s = 0; s < PAT; ++s) {
     const int dx = pat_off(PAT, s, 0), dy = pat_off(PAT, s, 1), dz = pat_off(PAT, s, 2);
@@ -52,7 +60,7 @@ __device__ __forceinline__ typename M::V spmv_row(const Grid& g, const M& m, con
   return acc;
 }
 
-template <int PAT, class M, bool RES>
+template <int PAT, class M, bool RES, bool WALK = false>
 struct SpmvOp {
   using Args = SpmvArgs<M>;
   __device__ static void run(const Args& a, unsigned bid) {
@@ -65,12 +73,31 @@ struct SpmvOp {
     if (i >= N) return;
     int X, Y, Z;
     unflat(i, g.ny, g.nz, X, Y, Z);
-    const V acc = spmv_row<PAT>(g, m, x, X, Y, Z, (long)i);
+    const V acc = spmv_row<PAT, WALK>(g, m, x, X, Y, Z, (long)i);
     a.y[i] = RES ? a.b[i] - acc : acc;
   }
 };
 
 unsigned spmv_blocks(const Grid& g) { return (unsigned)((g.N() + 255) / 256); }
+
+// Does a product in FP64 walk its slots one after another?  Where all
+// workgroups of a launch are resident together (8 on each of 256 CUs) they
+// then read each coefficient array in step, as one stream; all loads at once
+// are 27 streams.  That holds for the few first fills of the chip and pays as
+// long as the last one is full as well: a part of a fill takes as long as a
+// whole one.  At once / walking, MI355X, us: one fill (64x64x128) 7 points
+// 8.2 / 7.0, 19 points 21.0 / 18.8, 27 points 29.6 / 25.3; two (128x128x64)
+// 16.9 / 16.2, 39.3 / 35.4, 56 / 48; three 23.7 / 23.0, 57 / 53, 79 / 71; four
+// (128^3) 31.4 / 30.0, 77 / 69, 106 / 94.  Not full: 64x64x144 (1.1 fills)
+// 9.8 / 10.4, 23 / 29, 31 / 40; 128x128x112 (3.5) 25 / 29, 60 / 63, 88 / 89;
+// 127x128x128 (3.97) 29 / 31, 74 / 71, 103 / 97; more fills: 256x256x64 (8)
+// 57 / 56, 137 / 139, 188 / 200.  FP32 rows load half as much at once and gain
+// from it at every size (128^3, 27 points: 41 / 50).
+static bool spmv_walk(int pat, const Grid& g) {
+  constexpr unsigned FILL = 8 * 256;
+  const unsigned n = spmv_blocks(g), fills = (n + FILL - 1) / FILL;
+  return fills <= (pat == 7 ? 1u : 4u) && fills * FILL - n <= FILL / 32;
+}
 
 template <class M>
 hipError_t launch_spmv(int pat, const Grid& g, const M& m, const typename M::V* x, const typename M::V* b,
@@ -79,6 +106,15 @@ hipError_t launch_spmv(int pat, const Grid& g, const M& m, const typename M::V* 
   const dim3 grid(spmv_blocks(g)), blk(256);
 #define SMG_SPMV(P)                                                                      \
   if (pat == P) {                                                                        \
+    if constexpr (sizeof(typename M::V) == 8) {                                          \
+      if (spmv_walk(P, g)) {                                                          \
+        if (res)                                                                         \
+          hipLaunchKernelGGL((k_one<SpmvOp<P, M, true, true>>), grid, blk, 0, st, a);   \
+        else                                                                             \
+          hipLaunchKernelGGL((k_one<SpmvOp<P, M, false, true>>), grid, blk, 0, st, a);  \
+        return hipGetLastError();                                                        \
+      }                                                                                  \
+    }                                                                                    \
     if (res)                                                                             \
       hipLaunchKernelGGL((k_one<SpmvOp<P, M, true>>), grid, blk, 0, st, a);             \
     else                                                                                 \
@@ -226,7 +262,7 @@ struct RROp {
     const int fz = loz + k % ez, fy = loy + (k / ez) % ey, fx = lox + k / (ez * ey);
     if (fx >= gf.nx || fy >= gf.ny || fz >= gf.nz) continue;
     const long i = ((long)fx * gf.ny + fy) * gf.nz + fz;
-    const V acc = spmv_row<PAT>(gf, m, u, fx, fy, fz, i);
+    const V acc = spmv_row<PAT, false>(gf, m, u, fx, fy, fz, i);
     rs[k] = f[i] - acc;
   }
   __syncthreads();
