@@ -61,6 +61,34 @@ int hp_plan(const Grid& g, int pat, int vbytes, std::vector<int>* pts) {
   return H;
 }
 
+// One workgroup pays per hyperplane (0.15 us with 7 points and few of them in
+// a hyperplane to 0.8 us where it fills the workgroup), tiles a launch's start
+// and hand-offs between them, then 0.1-0.15 us per hyperplane.  Both measured
+// in V-cycles of two levels, every precision; us a sweep that one workgroup
+// takes less (-) or more (+) than tiles:
+//  7 points, FP64 / FP32: 4x4x90 -10 / -10, 4x4x160 (2560 points) -2 / -9,
+//    4x4x200 (3200) +2 / -3, 6x6x100 (3600) 0 / -1, 8x8x60 (3840) -1 / -2, 8x8x70
+//    (4480) +0.8 / +0.8; of at most 72 hyperplanes 16x16x19 (4864) -1 / 0,
+//    10x10x50 0 / 0, 12x12x38 (5472) +2 / +2, 16x12x30 (5760) -1 / 0, 16x16x22
+//    (5632) +0.6 / +1.6, 16x16x30 (7680, FP32) +4.
+//  19 points: 12x12x20 (75 hyperplanes) -5 / -5, 14x14x14 (79) -2 / -2, 12x12x28
+//    (83) 0 / -0.6, 16x16x12 (87) +1 / -1, 12x12x35 (90) +4 / +4; one tile, which has
+//    no hand-offs: 8x8x36 (71) -1.6 / -4.7, 8x8x42 (77) +1 / -1, 8x8x50 (85) +3.5 /
+//    +2.4.
+//  27 points: 12x11x14 (78) -1.9 / -5, 10x10x26 (80) -3.4 / -5, 12x16x9 (83) 0 /
+//    -3.7, 14x14x8 (86) +3.4 / -1, 14x14x12 (90) +4 / 0, 16^3 (106) +22 / +13; one
+//    tile: 8x8x28 (70) +0.8 / -2.8, 8x8x32 (74) +7.7 / +2.7.  FP16 gains 2 to 3
+//    more than FP32 everywhere.
+//  Few points, 19 and 27: 4x4x80 (1280 points, 98) 0 / -3.5, 2x2x90 (96) -6 / -10,
+//    4x4x100 (118) +3.5 / +0.5.
+int hp_max_steps(const Grid& g, int pat, int vbytes) {
+  const long n = g.N();
+  if (pat == 7) return n <= (vbytes == 8 ? 3000 : 4400) ? (int)n : (vbytes == 8 || n <= 5400 ? 72 : 0);
+  if (n <= 1280) return 96;
+  if (g.nx <= WF_TX) return pat == 19 && vbytes == 4 ? 80 : 72;
+  return pat == 27 && vbytes == 4 ? 88 : 80;
+}
+
 // Coefficient copy of direction dir in step order (step k is hyperplane k
 // forward, nsteps-1-k backward), 16-byte packs per point: element e of pack
 // p of slot t of step k at ((k * NPK + p) * 256 + t) * K + e holds entry

@@ -84,16 +84,7 @@ hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<
 // FP64 data, 2: FP16 row-scaled storage); launch_hpsweep runs a forward
 // (dir > 0) or backward Gauss-Seidel sweep x = S(h) of the level.
 int hp_plan(const Grid& g, int pat, int vbytes, std::vector<int>* pts);
-// Most hyperplanes at which that sweep still runs instead of the tiled one.
-// It costs 0.35-0.4 us per hyperplane of a few points and up to 0.8 us where
-// a hyperplane fills the workgroup; the tiled sweep costs 20 us and then
-// 0.1-0.15 us per hyperplane.  Measured inside V-cycles, both sweeps of a
-// level averaged, one workgroup against tiles: 27-point 6x8x4 (38
-// hyperplanes, FP16) 12 against 21 us, 8^3 (50, FP64) 20 against 22, 12x10x8
-// (70, FP64) 26.5 against 30, 12x11x14 (78, FP32) 33 against 31, 12x16x9 (83,
-// FP16) 39 against 31.5, 16^3 (106, FP64) 88 against 33; 7-point 8^3 (22)
-// 28 against 35, 16^3 (46) 36 against 39, 4x4x64 (70) 35 against 44.
-constexpr int HP_MAX_STEPS = 72;
+int hp_max_steps(const Grid& g, int pat, int vbytes);  // most hyperplanes at which it runs instead of the tiled sweep
 hipError_t launch_hp_pack(int pat, int src, const Grid& g, int nsteps, int dir, const int* pts, const double* A,
                           const double* rd, const __half* a16, const float* sc, const float* rd32, void* out,
                           hipStream_t st);

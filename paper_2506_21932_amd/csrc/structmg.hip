@@ -224,7 +224,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       v.pk[1] = ar.take<char>(pbytes);
       if (cfg.prec == SMG_FP16_ROWSCALE) v.psd = ar.take<float>((size_t)2 * v.nsk_cap);
       const int hp = cfg.smoother == SMG_SMOOTH_GS ? hp_plan(v.g, v.S, (int)vsz, nullptr) : 0;
-      v.hp_steps = hp <= HP_MAX_STEPS ? hp : 0;
+      v.hp_steps = hp <= hp_max_steps(v.g, v.S, (int)vsz) ? hp : 0;
       if (hp > 0) {  // (room on every level that could run it: the workspace does not depend on the limit)
         v.hp_pts = ar.take<int>((size_t)hp * 256);
         const size_t kv = 16 / vsz, npk = (v.S / 2 + 1 + kv - 1) / kv;  // 16-byte packs per point
