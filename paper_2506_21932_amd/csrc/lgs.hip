@@ -10,7 +10,7 @@
 // thread per column): p_0 = b_0, p_z = fma(-a_z, cp_{z-1}, b_z),
 // rden_z = 1/p_z, cp_z = c_z * rden_z.
 //
-// Sweep (k_lgs): a column depends only on columns whose (x, y) come earlier
+// Sweep: a column depends only on columns whose (x, y) come earlier
 // in the visiting order and are stencil neighbours (the projected 2D pattern:
 // 2d5 for 3d7, 2d9 for 3d19 / 3d27).  In the sheared coordinates
 // (x, y' = y + sh*x), sh = 0 for 3d7 and 1 otherwise (the neighbour
@@ -20,20 +20,19 @@
 // (bx, by'-1), so tiles listed by diagonal bx + by' (setup-time table, empty
 // tiles left out) are in dependence order.  Persistent workgroups take tiles
 // by atomic ticket (every tile's producers hold smaller tickets and are
-// already running: the grid always makes progress) and walk a tile's local
-// hyperplanes lx + ly' = k, at most K columns each (K*nz <= 256 points, one
-// per thread, unless a column is longer); every column of this sweep is read
-// back device-coherently, a column of another tile after its sentinel has
-// gone.  The backward sweep takes the table and the local
-// hyperplanes in reverse.
-// For each local hyperplane a workgroup
-//   A. assembles the right-hand side of its columns, one point per thread:
+// already running: the grid always makes progress).  k_lgs_tile walks a
+// tile's local hyperplanes lx + ly' = k, K columns each; columns longer than
+// its LDS arrays take k_lgs, a column per tile (K = 1).  A column of another
+// tile is read back device-coherently, after its sentinel has gone.  The
+// backward sweep takes the table (and k_lgs_tile the local hyperplanes) in
+// reverse.
+// For each column (k_lgs_tile: for the columns of a hyperplane together) a
+// workgroup
+//   A. assembles the right-hand side, one point per thread:
 //      t = f_i; the terms of columns not yet visited (values from before the
-//      sweep, plain loads); then the terms of columns of this sweep, whose
-//      values are read device-coherently from the output and awaited while
-//      they still hold the sentinel; each group in canonical order with fma.
-//      Every load of a point is issued before its first wait.  The Thomas
-//      factors of the columns are staged in LDS with the sums;
+//      sweep, plain loads); then the terms of columns of this sweep; each
+//      group in canonical order with fma.  The Thomas factors are staged in
+//      LDS with the sums;
 //   B. solves each column in one lane (forward elimination, back
 //      substitution), in the oracle's order of operations;
 //   C. stores the column device-coherently and, if asked, writes the sentinel
@@ -52,8 +51,8 @@ namespace smg {
 
 namespace {
 
-constexpr int LGS_NT = 256;                 // threads per workgroup
-constexpr int LGS_PTS = LGS_NT;             // points per chunk (K * nz), unless nz is larger
+constexpr int LGS_NT = 256;                 // k_lgs: threads per workgroup
+constexpr int LGS_RESERVE_PTS = 256;        // points per hyperplane of the tiles that the table has room for
 constexpr unsigned LGS_SPIN_LIMIT = 1u << 21;
 constexpr int LT_MAX_GRID = 256;            // k_lgs_tile: one workgroup per CU
 
@@ -168,105 +167,91 @@ __device__ inline void lgs_retire(unsigned* ctr) {
   }
 }
 
+// Columns of more than LT_MAX_NZ points: one column at a time, bound by the
+// chain of right-hand side, solve (one lane) and hand-off.  64 x 64 x 129, 7-point
+// FP64 1.59 ms each way, 19-point FP32 2.10 / 2.38, 27-point FP64 2.51 / 2.99 (a
+// form for K x K tiles of shorter columns 1.64, 2.32 / 2.57, 2.51 / 3.03).
 template <int PAT, int DIR, class V, bool ZG>
 __global__ __launch_bounds__(LGS_NT) void k_lgs(LgsArgs<V> a) {
-  constexpr int CWX = lgs_cwx(PAT);
+  constexpr int SH = lgs_cwx(PAT) - 1;
   constexpr int SLO = pat_slot(PAT, 0, 0, -1);
   extern __shared__ __align__(16) unsigned char lgs_smem[];
   const Grid g = a.g;
   const long N = g.N();
-  const int nz = g.nz, K = a.K, LD = nz + 1;
+  const int nz = g.nz;
   V* ld = reinterpret_cast<V*>(lgs_smem);  // right-hand side, then d', then x
-  V* la = ld + K * LD;                      // coupling to z-1
-  V* lr = la + K * LD;                      // 1 / pivot
-  V* lc = lr + K * LD;                      // c / pivot
-  const int SH = CWX - 1;
-  const int nsteps = 2 * K - 1;
+  V* la = ld + nz;                          // coupling to z-1
+  V* lr = la + nz;                          // 1 / pivot
+  V* lc = lr + nz;                          // c / pivot
   for (;;) {
     const unsigned ticket = lgs_take_ticket(a.ctr);
     if (ticket >= (unsigned)a.ntile) break;
     const int e = a.tmap[DIR > 0 ? (int)ticket : a.ntile - 1 - (int)ticket];
-    const int bx = e >> 16, by = e & 0xffff;
-    for (int st = 0; st < nsteps; ++st) {
-      const int kh = DIR > 0 ? st : nsteps - 1 - st;  // local hyperplane lx + ly' = kh
-      const int lx0 = kh - (K - 1) > 0 ? kh - (K - 1) : 0;
-      const int ncol = (kh < K - 1 ? kh : K - 1) - lx0 + 1;  // columns of this hyperplane in the tile
-      // column c of the hyperplane: (lx, ly') = (lx0 + c, kh - lx0 - c); it
-      // exists if it falls inside the grid
-      auto column = [&](int c, int& X, int& Y) {
-        X = bx * K + lx0 + c;
-        Y = by * K + (kh - lx0 - c) - SH * X;
-        return X < g.nx && Y >= 0 && Y < g.ny;
-      };
-      // A. right-hand sides and staged factors (one point per thread unless
-      // the column is longer than a workgroup)
-      for (int q = threadIdx.x; q < ncol * nz; q += LGS_NT) {
-        const int c = q / nz, Z = q - c * nz;
-        int X, Y;
-        if (!column(c, X, Y)) continue;
-        const long i = ((long)X * g.ny + Y) * nz + Z;
-        const int o = c * LD + Z;
-        la[o] = Z > 0 ? a.A[(long)SLO * N + i] : V(0);
-        lr[o] = a.rden[i];
-        lc[o] = a.cp[i];
-        ld[o] = lgs_rhs<PAT, DIR, ZG, V>(a, N, i, X, Y, Z, std::make_integer_sequence<int, PAT>{});
-      }
-      __syncthreads();
-      // B. Thomas solve, one lane per column, in blocks of 8 points whose LDS
-      // reads are issued together.  d'_0 = t_0 * rden_0 comes out of the same
-      // formula: the stored coupling to z-1 at z = 0 is +0 and d' starts at +0,
-      // so fma(-0, +0, t_0) = t_0 exactly.
-      int cX, cY;
-      if ((int)threadIdx.x < ncol && column((int)threadIdx.x, cX, cY)) {
-        const int b = (int)threadIdx.x * LD;
-        V dp = V(0);
-        for (int z0 = 0; z0 < nz; z0 += 8) {
-          V a8[8], r8[8], d8[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int z = z0 + k < nz ? z0 + k : nz - 1;
-            a8[k] = la[b + z];
-            r8[k] = lr[b + z];
-            d8[k] = ld[b + z];
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            if (z0 + k < nz) {
-              dp = fma(-a8[k], dp, d8[k]) * r8[k];
-              ld[b + z0 + k] = dp;
-            }
-          }
-        }
-        V xv = dp;
-        for (int z1 = nz - 2; z1 >= 0; z1 -= 8) {
-          V c8[8], d8[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int z = z1 - k >= 0 ? z1 - k : 0;
-            c8[k] = lc[b + z];
-            d8[k] = ld[b + z];
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            if (z1 - k >= 0) {
-              xv = fma(-c8[k], xv, d8[k]);
-              ld[b + z1 - k] = xv;
-            }
-          }
-        }
-      }
-      __syncthreads();
-      // C. results out, sentinels for the next sweep
-      for (int q = threadIdx.x; q < ncol * nz; q += LGS_NT) {
-        const int c = q / nz, Z = q - c * nz;
-        int X, Y;
-        if (!column(c, X, Y)) continue;
-        const long i = ((long)X * g.ny + Y) * nz + Z;
-        cstore(a.x + i, ld[c * LD + Z]);
-        if (a.next) a.next[i] = VBits<V>::val(VBits<V>::sent);
-      }
-      __syncthreads();  // LDS is refilled by the next local hyperplane
+    int X = e >> 16, Y = (e & 0xffff) - SH * X;
+    // kept in vector registers, and b below: a scalar form holds every
+    // neighbour's test in spilled scalar registers (27 points, backward: 2% of
+    // the sweep) and forms the LDS addresses of the solve one by one (10%)
+    asm("" : "+v"(X), "+v"(Y));
+    const long i0 = ((long)X * g.ny + Y) * nz;
+    // A. right-hand sides and staged factors
+    for (int Z = threadIdx.x; Z < nz; Z += LGS_NT) {
+      const long i = i0 + Z;
+      la[Z] = Z > 0 ? a.A[(long)SLO * N + i] : V(0);
+      lr[Z] = a.rden[i];
+      lc[Z] = a.cp[i];
+      ld[Z] = lgs_rhs<PAT, DIR, ZG, V>(a, N, i, X, Y, Z, std::make_integer_sequence<int, PAT>{});
     }
+    __syncthreads();
+    // B. Thomas solve in one lane, in blocks of 8 points whose LDS reads are
+    // issued together.  d'_0 = t_0 * rden_0 comes out of the same formula: the
+    // stored coupling to z-1 at z = 0 is +0 and d' starts at +0, so fma(-0, +0,
+    // t_0) = t_0 exactly.
+    if (threadIdx.x == 0) {
+      int b = 0;
+      asm("" : "+v"(b));
+      V dp = V(0);
+      for (int z0 = 0; z0 < nz; z0 += 8) {
+        V a8[8], r8[8], d8[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int z = z0 + k < nz ? z0 + k : nz - 1;
+          a8[k] = la[b + z];
+          r8[k] = lr[b + z];
+          d8[k] = ld[b + z];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (z0 + k < nz) {
+            dp = fma(-a8[k], dp, d8[k]) * r8[k];
+            ld[b + z0 + k] = dp;
+          }
+        }
+      }
+      V xv = dp;
+      for (int z1 = nz - 2; z1 >= 0; z1 -= 8) {
+        V c8[8], d8[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int z = z1 - k >= 0 ? z1 - k : 0;
+          c8[k] = lc[b + z];
+          d8[k] = ld[b + z];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (z1 - k >= 0) {
+            xv = fma(-c8[k], xv, d8[k]);
+            ld[b + z1 - k] = xv;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // C. results out, sentinels for the next sweep
+    for (int Z = threadIdx.x; Z < nz; Z += LGS_NT) {
+      cstore(a.x + i0 + Z, ld[Z]);
+      if (a.next) a.next[i0 + Z] = VBits<V>::val(VBits<V>::sent);
+    }
+    __syncthreads();  // LDS is refilled by the next column
   }
   lgs_retire(a.ctr);
 }
@@ -291,10 +276,13 @@ __global__ __launch_bounds__(LGS_NT) void k_lgs(LgsArgs<V> a) {
 // a column lie one to three hyperplanes back).  The backward sweep mirrors the
 // tile.  A hyperplane takes 2.4 us, of which the Thomas solve about half (its
 // chain, and LDS reads and writes of 16 bytes).  Forward / backward sweep of a
-// 512 x 512 x 64 level, 19-point FP32, with the kernel above and with this one
-// (MI355X): 10.43 / 11.55 and 3.74 / 3.72 ms; 128 x 128 x 64, 27-point: 1.29 /
-// 1.55 and 0.49 / 0.45 ms (kernel above: longer columns, whose hyperplanes of
-// one or two columns leave nothing to overlap).
+// 512 x 512 x 64 level, 19-point FP32, before
+// (a kernel that did a hyperplane's loads, solves and stores in turn) and with
+// this one (MI355X): 10.43 / 11.55 and 3.74 / 3.72 ms; 128 x 128 x 64, 27-point:
+// 1.29 / 1.55 and 0.49 / 0.45 ms.  Longer columns gain as much, down to two
+// columns a hyperplane: 64 x 64 x 96, 19-point FP64 1.93 / 2.14 and 1.09 / 1.14
+// ms, 128^3, 27-point FP64 5.01 / 5.78 and 2.69 / 2.71, FP32 4.41 / 5.27 and
+// 1.71 / 1.67 ms; the limit is the halo wave's two values a lane and column.
 constexpr int LT_MAX_NZ = 128;
 template <class V>
 constexpr int lt_pts() {
@@ -455,7 +443,9 @@ __global__ __launch_bounds__(lt_pts<V>() + 128) void k_lgs_tile(LgsArgs<V> a) {
       const V *const fr = fa + K * LDP, *const fc = fr + K * LDP;
       V* const out = ringp(k, lane + 1);
       // blocks of 8 points; the next block's reads are issued before this
-      // one's chain (a read past the column's end stays inside its stride)
+      // one's chain (behind a last block that is full they bring four values of
+      // the LDS column or array after this one, which nothing uses: a clamped
+      // address costs 1-2% of the sweep)
       struct Blk {
         V a[8], r[8], d[8];
       };
@@ -486,7 +476,7 @@ __global__ __launch_bounds__(lt_pts<V>() + 128) void k_lgs_tile(LgsArgs<V> a) {
       for (; ib + 2 <= nb; ib += 2) {
         read3(b1, 8 * ib + 8);
         forward(b0, 8 * ib, 8);
-        read3(b0, ib + 2 <= nb ? 8 * ib + 16 : 0);
+        read3(b0, 8 * ib + 16);
         forward(b1, 8 * ib + 8, 8);
       }
       if (ib < nb) {
@@ -701,8 +691,8 @@ hipError_t launch_lgs_t(const LgsArgs<V>& a, hipStream_t st) {
     return hipGetLastError();
   }
   const unsigned grid = total < (unsigned)LGS_MAX_GRID ? total : (unsigned)LGS_MAX_GRID;
-  const size_t lds = lgs_lds_bytes(a.g, a.K, (int)sizeof(V));
-  hipLaunchKernelGGL((k_lgs<PAT, DIR, V, ZG>), dim3(grid), dim3(LGS_NT), lds, st, a);
+  if (a.K != 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_lgs<PAT, DIR, V, ZG>), dim3(grid), dim3(LGS_NT), 4 * sizeof(V) * a.g.nz, st, a);
   return hipGetLastError();
 }
 
@@ -743,7 +733,7 @@ static int lgs_tiles(const Grid& g, int pat, int k, std::vector<int>* tmap) {
 }
 
 static int lgs_points(const Grid& g, int vbytes) {
-  return g.nz > LT_MAX_NZ ? LGS_PTS : (vbytes == 4 ? lt_pts<float>() : lt_pts<double>());
+  return g.nz > LT_MAX_NZ ? 1 : (vbytes == 4 ? lt_pts<float>() : lt_pts<double>());
 }
 
 int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap) {
@@ -759,9 +749,7 @@ bool lgs_ranges_ok(const Grid& g, int pat, int vbytes) {
 
 // (the smaller tiles of every precision, so that the workspace does not
 // depend on the kernel)
-int lgs_reserve(const Grid& g, int pat) { return lgs_tiles(g, pat, lgs_side(g, LGS_PTS), nullptr); }
-
-size_t lgs_lds_bytes(const Grid& g, int K, int vbytes) { return (size_t)4 * K * (g.nz + 1) * vbytes; }
+int lgs_reserve(const Grid& g, int pat) { return lgs_tiles(g, pat, lgs_side(g, LGS_RESERVE_PTS), nullptr); }
 
 hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rden, double* cp, unsigned* err,
                              hipStream_t st) {
@@ -775,8 +763,7 @@ hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rd
 
 template <class V>
 hipError_t launch_lgs(int pat, int dir, bool zero_guess, const LgsArgs<V>& a, hipStream_t st) {
-  if (a.K < 1 || a.ntile < 1 || !a.tmap || a.g.nz > LGS_MAX_NZ || lgs_lds_bytes(a.g, a.K, (int)sizeof(V)) > 65536 ||
-      (!zero_guess && a.uold == nullptr))
+  if (a.K < 1 || a.ntile < 1 || !a.tmap || a.g.nz > LGS_MAX_NZ || (!zero_guess && a.uold == nullptr))
     return hipErrorInvalidValue;
   if (pat == 7) return launch_lgs_p<7, V>(dir, zero_guess, a, st);
   if (pat == 19) return launch_lgs_p<19, V>(dir, zero_guess, a, st);

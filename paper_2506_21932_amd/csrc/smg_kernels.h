@@ -323,7 +323,6 @@ struct LgsArgs {
 int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap);
 int lgs_reserve(const Grid& g, int pat);  // room for tmap
 bool lgs_ranges_ok(const Grid& g, int pat, int vbytes);  // do the tiles fit its entries?
-size_t lgs_lds_bytes(const Grid& g, int K, int vbytes);
 hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rden, double* cp, unsigned* err,
                              hipStream_t st);
 template <class V>
