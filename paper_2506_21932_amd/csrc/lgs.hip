@@ -52,7 +52,7 @@ namespace smg {
 namespace {
 
 constexpr int LGS_NT = 256;                 // k_lgs: threads per workgroup
-constexpr int LGS_RESERVE_PTS = 256;        // points per hyperplane of the tiles that the table has room for
+constexpr int LGS_RESERVE_PTS = 256;        // points per hyperplane of the tiles of lgs_reserve
 constexpr unsigned LGS_SPIN_LIMIT = 1u << 21;
 constexpr int LT_MAX_GRID = 256;            // k_lgs_tile: one workgroup per CU
 
@@ -747,8 +747,7 @@ bool lgs_ranges_ok(const Grid& g, int pat, int vbytes) {
   return (g.nx - 1) / k < 1 << 15 && ((long)g.ny - 1 + (long)sh * (g.nx - 1)) / k < 1 << 16;
 }
 
-// (the smaller tiles of every precision, so that the workspace does not
-// depend on the kernel)
+// (the smaller tiles of every precision)
 int lgs_reserve(const Grid& g, int pat) { return lgs_tiles(g, pat, lgs_side(g, LGS_RESERVE_PTS), nullptr); }
 
 hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rden, double* cp, unsigned* err,

@@ -41,9 +41,9 @@ struct WfArgs {
 // shape: 0 default (sheared for 19/27 points with more than one tile row),
 // 1 sheared, 2 rectangular
 void wf_tiling(const Grid& g, int pat, WfTiling* t, int shape = 0);
-// Schedule positions a level reserves for a shape: those of tiles 16 columns
-// wide, whose padding is larger.  (The hierarchies that smg_setup_noalloc's
-// array takes then do not depend on the tile width.)
+// Schedule positions of a shape that the limit of smg_setup_noalloc counts:
+// those of tiles 16 columns wide, whose padding is larger.  (What it takes then
+// does not depend on the tile width.)
 long wf_reserve(const Grid& g, int pat, int shape);
 // 16-byte packs per schedule position and direction for storage elements of
 // ebytes bytes; offsets within a tile must stay below 2^31 bytes.
@@ -321,7 +321,7 @@ struct LgsArgs {
 // tile side K and the tiles holding columns in dependence order (tmap may
 // be null: count only); returns their number
 int lgs_plan(const Grid& g, int pat, int vbytes, int* K, std::vector<int>* tmap);
-int lgs_reserve(const Grid& g, int pat);  // room for tmap
+int lgs_reserve(const Grid& g, int pat);  // entries that the limit of smg_setup_noalloc counts
 bool lgs_ranges_ok(const Grid& g, int pat, int vbytes);  // do the tiles fit its entries?
 hipError_t launch_tri_factor(int pat, const Grid& g, const double* A, double* rden, double* cp, unsigned* err,
                              hipStream_t st);

@@ -139,10 +139,12 @@ constexpr int CTR_WORDS = 64, CTR_PAR = 8;
 static_assert(CTR_PAR + MAXLEV <= CTR_WORDS, "counter block too small");
 
 // Lays out every device array of the handle in the workspace (base == null:
-// size only).  Returns the number of bytes; *core receives those without the
-// strip buffers, which come last.
+// size only).  Returns the number of bytes.  counted (size only): the bytes
+// that the limit of smg_setup_noalloc counts, which do not depend on the sweeps'
+// tiles: sweep data of wf_reserve / bwf_reserve positions, tables of every
+// level that could use them, no strip buffers.
 size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, int* nc_out, Level* Lext = nullptr,
-            size_t* core = nullptr) {
+            bool counted = false) {
   Arena ar{base};
   const int bs = cfg.block, be = bs * bs;
   const int maxc = cfg.max_coarse > 0 ? cfg.max_coarse : 4096;
@@ -201,7 +203,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     const int eb = cfg.prec == SMG_FP16_ROWSCALE ? 2 : (int)vsz;
     if (cfg.smoother == SMG_SMOOTH_LGS) {
       v.lg_nt = lgs_plan(v.g, v.S, (int)vsz, &v.lg_K, nullptr);
-      v.lg_map = ar.take<int>((size_t)lgs_reserve(v.g, v.S));
+      v.lg_map = ar.take<int>((size_t)(counted ? lgs_reserve(v.g, v.S) : v.lg_nt));
       v.tr64 = ar.take<double>((size_t)N);
       v.tc64 = ar.take<double>((size_t)N);
       if (cfg.prec == SMG_FP32) {
@@ -215,7 +217,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       for (int shape = 1; shape <= 2; ++shape) {
         WfTiling t;
         wf_tiling(v.g, v.Ssw, &t, shape);
-        v.nsk_cap = std::max(v.nsk_cap, wf_reserve(v.g, v.Ssw, shape));
+        v.nsk_cap = std::max(v.nsk_cap, counted ? wf_reserve(v.g, v.Ssw, shape) : t.nsk);
         v.strip_cap = std::max(v.strip_cap, 2 * wf_strip_elems(t, v.Ssw));
       }
       wf_tiling(v.g, v.Ssw, &v.tl);
@@ -225,7 +227,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       if (cfg.prec == SMG_FP16_ROWSCALE) v.psd = ar.take<float>((size_t)2 * v.nsk_cap);
       const int hp = cfg.smoother == SMG_SMOOTH_GS ? hp_plan(v.g, v.S, (int)vsz, nullptr) : 0;
       v.hp_steps = hp <= hp_max_steps(v.g, v.S, (int)vsz) ? hp : 0;
-      if (hp > 0) {  // (room on every level that could run it: the workspace does not depend on the limit)
+      if (counted ? hp > 0 : v.hp_steps > 0) {
         v.hp_pts = ar.take<int>((size_t)hp * 256);
         const size_t kv = 16 / vsz, npk = (v.S / 2 + 1 + kv - 1) / kv;  // 16-byte packs per point
         v.hp_cf[0] = ar.take<char>((size_t)hp * npk * 256 * 16);
@@ -234,7 +236,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     } else {
       bwf_tiling(v.g, &v.tl);
       v.strip_cap = 2 * bwf_strip_elems(v.tl);
-      const size_t pbytes = (size_t)bwf_pack_count(eb) * 16 * bwf_reserve(v.g);
+      const size_t pbytes = (size_t)bwf_pack_count(eb) * 16 * (counted ? bwf_reserve(v.g) : v.tl.nsk);
       v.pk[0] = ar.take<char>(pbytes);
       v.pk[1] = ar.take<char>(pbytes);
     }
@@ -284,8 +286,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
     H->kZ = kZ;
     H->kV_m = cfg.gmres_restart;
   }
-  if (core) *core = ar.off + 256;
-  for (int l = 0; l + 1 < nlev; ++l) {
+  for (int l = 0; !counted && l + 1 < nlev; ++l) {
     Level& v = L[l];
     if (v.strip_cap > 0) v.strip = ar.take<char>((size_t)v.strip_cap * vsz);
     v.par = ctr ? ctr + CTR_PAR + l : nullptr;
@@ -1082,18 +1083,15 @@ extern "C" {
 
 // Workspace bytes of cfg; with automatic coarsening the largest over the
 // possible numbers of leading x,y-only levels.
-size_t plan_bytes(const smg_config& cfg, int* nlev, int* nc, size_t* core = nullptr) {
-  if (cfg.coarsen != SMG_COARSEN_AUTO) return plan(cfg, nullptr, nullptr, nlev, nc, nullptr, core);
+size_t plan_bytes(const smg_config& cfg, int* nlev, int* nc, bool counted = false) {
+  if (cfg.coarsen != SMG_COARSEN_AUTO) return plan(cfg, nullptr, nullptr, nlev, nc, nullptr, counted);
   size_t best = 0;
-  if (core) *core = 0;
   for (int s = MAXLEV; s >= 0; --s) {
     smg_config e = cfg;
     e.coarsen = SMG_COARSEN_FULL;
     e.semi_levels = s;
     int nl = 0, ncc = 0;
-    size_t c = 0;
-    const size_t b = plan(e, nullptr, nullptr, &nl, &ncc, nullptr, &c);
-    if (core && b > 0) *core = std::max(*core, c);
+    const size_t b = plan(e, nullptr, nullptr, &nl, &ncc, nullptr, counted);
     if (b > best || s == MAXLEV) {
       *nlev = nl;
       *nc = ncc;
@@ -1202,10 +1200,11 @@ static smg_status setup_impl(const smg_config* cfg, const double* coeffs, void* 
 // ends).  Host code never passes the array's name to a kernel or copy: its
 // device address is taken once per device with hipGetSymbolAddress and kept
 // in g_scratch_ptr.
-// SMG_SCRATCH_BYTES bound the hierarchy without its strip buffers.  Those take
-// at most 3/64 of it: two buffers of 24 entries a tile and step (7 points)
-// beside two directions of 128 columns of one pack (FP32) or two (FP64), at
-// least four entries each; 32 entries beside three packs with 19 points.
+// SMG_SCRATCH_BYTES bound the bytes that plan counts for it; beyond those a
+// hierarchy takes at most its strip buffers, 3/64 of them: two buffers of 24
+// entries a tile and step (7 points) beside two directions of 128 columns of one
+// pack (FP32) or two (FP64), at least four entries each; 32 entries beside three
+// packs with 19 points.
 constexpr size_t SCRATCH_ALL = SMG_SCRATCH_BYTES + SMG_SCRATCH_BYTES / 16;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_ALL];
 constexpr int SMG_SCRATCH_DEVICES = 64;
@@ -1237,12 +1236,12 @@ smg_status smg_setup_noalloc(const smg_config* cfg, const double* coeffs, void* 
   const char* why = check_cfg(cfg);
   if (why) return fail(nullptr, SMG_EINVAL, "%s", why);
   int nlev = 0, nc = 0;
-  size_t core = 0;
-  const size_t need = plan_bytes(*cfg, &nlev, &nc, &core);
+  const size_t need = plan_bytes(*cfg, &nlev, &nc);
   if (need == 0) return fail(nullptr, SMG_EINVAL, "coarsest level has %d unknowns (> max_coarse)", nc);
-  if (core > SMG_SCRATCH_BYTES || need > SCRATCH_ALL)
+  const size_t counted = plan_bytes(*cfg, &nlev, &nc, true);
+  if (counted > SMG_SCRATCH_BYTES || need > SCRATCH_ALL)
     return fail(nullptr, SMG_ENOMEM,
-                "hierarchy needs %zu bytes; the static scratch array holds %zu (use smg_setup with a workspace)", core,
+                "hierarchy needs %zu bytes; the static scratch array holds %zu (use smg_setup with a workspace)", counted,
                 (size_t)SMG_SCRATCH_BYTES);
   void* p = nullptr;
   const smg_status s = scratch_address(&p);
