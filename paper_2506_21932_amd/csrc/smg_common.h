@@ -52,7 +52,8 @@ __host__ __device__ constexpr int pat_slot(int pat, int dx, int dy, int dz) {
 __host__ __device__ constexpr int hp_wx(int pat) { return pat == 7 ? 1 : (pat == 19 ? 3 : 4); }
 __host__ __device__ constexpr int hp_wy(int pat) { return pat == 7 ? 1 : 2; }
 
-// Sentinels marking "not yet written in this sweep" in wavefront outputs:
+// Sentinels marking "not yet written in this sweep" in the buffers through
+// which workgroups exchange values (strips; line sweeps: their outputs):
 // signalling NaNs with a fixed payload.  Arithmetic never produces a
 // signalling NaN, so a computed value can never equal them.
 constexpr uint64_t SENT64 = 0xFFF5A5A55A5AA5A5ull;

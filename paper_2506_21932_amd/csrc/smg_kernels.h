@@ -33,7 +33,7 @@ struct WfArgs {
   unsigned* par;             // bit 0 names the buffer of the level's next sweep (it holds sentinels)
   const V* addv;             // optional: addout = addv + x
   V* addout;
-  unsigned* ctr;             // [0] ticket counter, [1] exit counter; zero between launches
+  unsigned* ctr;             // [0] ticket counter; zero between launches
   unsigned* err;             // watchdog flag (bit 0)
   int sys;                   // grouped sweeps: system of this grid
 };

@@ -133,8 +133,8 @@ const char* check_cfg(const smg_config* c) {
   return nullptr;
 }
 
-// Words of the handle's counter block: the sweeps' ticket and exit counters,
-// then one strip-buffer word per level.
+// Words of the handle's counter block: the sweeps' ticket counter, the line
+// sweep's exit counter, then one strip-buffer word per level.
 constexpr int CTR_WORDS = 64, CTR_PAR = 8;
 static_assert(CTR_PAR + MAXLEV <= CTR_WORDS, "counter block too small");
 

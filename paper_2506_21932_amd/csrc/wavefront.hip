@@ -641,7 +641,7 @@ struct WfRuns {
   __device__ static unsigned off_in(const Base& b, const Step& t, int g) {
     return (unsigned)(t.e + g * b.gy) * (unsigned)sizeof(V);
   }
-  // Chunks whose 256 x 16 positions are all points (a full tile, away from
+  // Chunks whose 128 x 16 positions are all points (a full tile, away from
   // both ends of its columns): one lane offset for the whole tile plus a
   // uniform byte offset per group, so a group costs no vector arithmetic.
   unsigned vin;          // lane part
@@ -842,7 +842,8 @@ __global__ __launch_bounds__(WF_THREADS) void k_wavefront(WfArgs<typename WfVal<
     unsigned ticket;
     if (!tk.take(&ticket)) return false;
     w->a = a;
-    // (one tile per workgroup: all are resident, any order will do)
+    // (one tile per workgroup: in the order of their index, which is a
+    // dependence order too, so it needs no residence of all of them)
     const unsigned r = tk.single ? ticket : sweep_tile(ticket, a.t.sh, a.t.ntx, a.t.nty);
     w->tile = DIR > 0 ? r : tk.ntiles - 1u - r;
     w->par = tk.par;
