@@ -63,8 +63,12 @@ int hp_plan(const Grid& g, int pat, int vbytes, std::vector<int>* pts) {
 
 // One workgroup pays per hyperplane (0.15 us with 7 points and few of them in
 // a hyperplane to 0.8 us where it fills the workgroup), tiles a launch's start
-// and hand-offs between them, then 0.1-0.15 us per hyperplane.  Both measured
-// in V-cycles of two levels, every precision; us a sweep that one workgroup
+// and hand-offs between them, then 0.1-0.15 us per hyperplane.  Where the rest of
+// the cycle has flushed the level's data out of the 256 MB last-level cache, one
+// compute unit fetches them too slowly (cold): at 78 hyperplanes (12^3, 27
+// points, under 192^3 and 96^3) one workgroup takes 14 us more than tiles in
+// FP64 and 7 in FP32, at 70 (12x10x8, FP64) 26.5 against 30.  In a cycle that
+// fits (hot), measured in V-cycles of two levels, us a sweep that one workgroup
 // takes less (-) or more (+) than tiles:
 //  7 points, FP64 / FP32: 4x4x90 -10 / -10, 4x4x160 (2560 points) -2 / -9,
 //    4x4x200 (3200) +2 / -3, 6x6x100 (3600) 0 / -1, 8x8x60 (3840) -1 / -2, 8x8x70
@@ -81,7 +85,8 @@ int hp_plan(const Grid& g, int pat, int vbytes, std::vector<int>* pts) {
 //    more than FP32 everywhere.
 //  Few points, 19 and 27: 4x4x80 (1280 points, 98) 0 / -3.5, 2x2x90 (96) -6 / -10,
 //    4x4x100 (118) +3.5 / +0.5.
-int hp_max_steps(const Grid& g, int pat, int vbytes) {
+int hp_max_steps(const Grid& g, int pat, int vbytes, bool hot) {
+  if (!hot) return 72;
   const long n = g.N();
   if (pat == 7) return n <= (vbytes == 8 ? 3000 : 4400) ? (int)n : (vbytes == 8 || n <= 5400 ? 72 : 0);
   if (n <= 1280) return 96;

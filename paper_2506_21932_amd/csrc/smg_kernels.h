@@ -84,7 +84,9 @@ hipError_t launch_wavefront_group(int pat, int dir, const WfArgs<typename WfVal<
 // FP64 data, 2: FP16 row-scaled storage); launch_hpsweep runs a forward
 // (dir > 0) or backward Gauss-Seidel sweep x = S(h) of the level.
 int hp_plan(const Grid& g, int pat, int vbytes, std::vector<int>* pts);
-int hp_max_steps(const Grid& g, int pat, int vbytes);  // most hyperplanes at which it runs instead of the tiled sweep
+// most hyperplanes at which it runs instead of the tiled sweep; hot: the cycle's
+// data stay in the last-level cache
+int hp_max_steps(const Grid& g, int pat, int vbytes, bool hot);
 hipError_t launch_hp_pack(int pat, int src, const Grid& g, int nsteps, int dir, const int* pts, const double* A,
                           const double* rd, const __half* a16, const float* sc, const float* rd32, void* out,
                           hipStream_t st);

@@ -138,6 +138,23 @@ const char* check_cfg(const smg_config* c) {
 constexpr int CTR_WORDS = 64, CTR_PAR = 8;
 static_assert(CTR_PAR + MAXLEV <= CTR_WORDS, "counter block too small");
 
+// Bytes that a V-cycle of GS sweeps on scalar levels touches, and the most of them
+// for which small levels find theirs in the 256 MB last-level cache again: the
+// outer iteration's matrix and vectors take up to 100 MB of it (104^3, 7 points,
+// FP32: 139 MB, still hot; 96^3, 27 points, FP16 165 MB and FP64, 7 points 214
+// MB: level; beyond, cold).
+constexpr size_t HOT_CYCLE_BYTES = 160u << 20;
+size_t cycle_bytes(const smg_config& cfg, const Level* L, int nlev) {
+  const size_t eb = cfg.prec == SMG_FP64 ? 8 : (cfg.prec == SMG_FP32 ? 4 : 2), vb = cfg.prec == SMG_FP64 ? 8 : 4;
+  size_t n = 0;
+  for (int l = 0; l + 1 < nlev; ++l) {
+    WfTiling t;
+    wf_tiling(L[l].g, L[l].S, &t);
+    n += (L[l].S * eb + 4 * vb) * L[l].N + (2 * 16 * (size_t)wf_pack_count(L[l].S, (int)eb) + (eb == 2 ? 8 : 0)) * t.nsk;
+  }
+  return n;
+}
+
 // Lays out every device array of the handle in the workspace (base == null:
 // size only).  Returns the number of bytes.  counted (size only): the bytes
 // that the limit of smg_setup_noalloc counts, which do not depend on the sweeps'
@@ -172,6 +189,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
   if (nlev_out) *nlev_out = nlev;
   if (nc_out) *nc_out = (int)nc;
   if (nc > maxc) return 0;
+  const bool hot = bs == 1 && cycle_bytes(cfg, L, nlev) <= HOT_CYCLE_BYTES;
   for (int l = 0; l < nlev; ++l) {
     Level& v = L[l];
     const long N = v.N;
@@ -226,7 +244,7 @@ size_t plan(const smg_config& cfg, smg_handle_s* H, char* base, int* nlev_out, i
       v.pk[1] = ar.take<char>(pbytes);
       if (cfg.prec == SMG_FP16_ROWSCALE) v.psd = ar.take<float>((size_t)2 * v.nsk_cap);
       const int hp = cfg.smoother == SMG_SMOOTH_GS ? hp_plan(v.g, v.S, (int)vsz, nullptr) : 0;
-      v.hp_steps = hp <= hp_max_steps(v.g, v.S, (int)vsz) ? hp : 0;
+      v.hp_steps = hp <= hp_max_steps(v.g, v.S, (int)vsz, hot) ? hp : 0;
       if (counted ? hp > 0 : v.hp_steps > 0) {
         v.hp_pts = ar.take<int>((size_t)hp * 256);
         const size_t kv = 16 / vsz, npk = (v.S / 2 + 1 + kv - 1) / kv;  // 16-byte packs per point
