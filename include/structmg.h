@@ -70,7 +70,8 @@ typedef struct {
                           after the coarse correction), ILU(0) on each level's mask, or
                           symmetric line GS over z-columns (Sec. 4.4: column right-hand
                           side from the neighbouring columns, Thomas solve per column;
-                          scalar systems, FP64 or FP32, nz <= 2047) */
+                          scalar systems, FP64 or FP32, nz <= 2047; at most
+                          32768 tiles of columns in x and 65536 rows of them) */
   int coarsen;         /* smg_coarsen: coarsen x,y,z (full), only x,y (semi), or x,y while
                           the level's z coupling stays weak (auto, Sec. 4.1 P2 fixed-stride
                           coarsening chosen per level): with rho the ratio of the finest
@@ -289,7 +290,8 @@ smg_status smg_timing_report(smg_handle h, double* ms, int* counts, int max_leve
  * and the host reads the systems' flags once per graph; a system stops on the
  * device at its convergence or at maxit.
  * Pointer arrays are host arrays of nsys device pointers.  At most 4095
- * systems. */
+ * systems, each with at most 2^20 sweep tiles (8 x 16 columns) and
+ * prolongation blocks (8 x 8 x 32 points) on a level. */
 typedef struct smg_batch_s* smg_batch;
 
 /* Workspace bytes for the batch (every cfgs[k] as for smg_workspace_size). */
